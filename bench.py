@@ -56,8 +56,8 @@ def log(msg):
 
 # Stage names the library times (ECOKV_STAGE_TIMING=1) and the kernels behind them.
 STAGE_KERNELS = {
-    "sweep1_stream": ["k_fs1s"], "sweep1_block": ["k_fs1", "k_pass1"], "reduce1": ["k_reduce1"],
-    "sweep2_stream": ["k_fs2s"], "sweep2_block": ["k_fs2", "k_pass2"], "epilogue": ["k_epi_unit"],
+    "sweep1_stream": ["k_fs1s"], "sweep1_rows": ["k_rows1"], "reduce1": ["k_reduce1"],
+    "sweep2_stream": ["k_fs2s"], "sweep2_rows": ["k_rows2"], "epilogue": ["k_epi_unit"],
     "epilogue1": ["k_epi1"], "epilogue2": ["k_epi2"],
     "select": ["k_select_reg", "k_select", "k_sel_digit", "k_sel_count", "k_sel_emit"], "compact": ["k_compact"], "vnorm": ["k_vnorm"],
     "dquant": ["k_dquant", "k_dquant_reg"], "decode": ["k_decode_mx", "k_decode"], "decode_merge": ["k_decode_merge"],
@@ -334,8 +334,8 @@ def main():
     }
     # what each kernel must move at minimum (scratch between kernels is not counted)
     stage_algo = {
-        "sweep1_stream": bytes_k + bytes_q, "sweep1_block": bytes_k + bytes_q,
-        "sweep2_stream": bytes_k + bytes_q, "sweep2_block": bytes_k + bytes_q,
+        "sweep1_stream": bytes_k + bytes_q, "sweep1_rows": bytes_k + bytes_q,
+        "sweep2_stream": bytes_k + bytes_q, "sweep2_rows": bytes_k + bytes_q,
         "reduce1": 0, "epilogue": bytes_scores,
         "epilogue1": 0, "epilogue2": bytes_scores, "select": bytes_scores + bytes_idx,
         "compact": bytes_gather + bytes_idx,

@@ -1,6 +1,6 @@
 // Device helpers shared by the score kernels (gfx950): vector types, unit
-// addressing, log2-domain softmax merging and the LDS tile geometry of the
-// bf16 / head_dim 128 path.  Not part of the ABI.
+// addressing, log2-domain softmax merging, the anchors of the second sweep and
+// the LDS stage geometry of the bf16 / head_dim 128 path.  Not part of the ABI.
 #pragma once
 
 #include "ecokv_internal.h"
@@ -40,6 +40,61 @@ __device__ __forceinline__ void softmax_merge2(float &m, float &s, float m2, flo
     s = a + b;
 }
 
+// Component c of kbar from the sum of the unit's T keys: divided by T, or,
+// with the centroid over the non-window keys, the w window rows taken out
+// and divided by P.
+__device__ __forceinline__ float centroid_component(const ScoreArgs &a, const Unit &un, int T, int c, float s)
+{
+    if (!a.centroid_prefix) return s / (float)T;
+    const int64_t r0 = unit_row0(a, un) + (T - a.w);
+    float ws = 0.f;
+    for (int j = 0; j < a.w; ++j) {
+        const int64_t off = (r0 + j) * a.D + c;
+        ws += a.kbf16 ? __uint_as_float((uint32_t)static_cast<const uint16_t *>(a.K)[off] << 16)
+                      : static_cast<const float *>(a.K)[off];
+    }
+    return (s - ws) / (float)(T - a.w);
+}
+
+// Anchor column c of unit u (the layout of a.anchors: kbar, mu, the window
+// rows' base-2 references and sums): from the workspace after the first sweep,
+// or converted from the sums a prefill handed over (ecokv_score_pre: plain
+// sums over the T keys, references in natural units).
+__device__ __forceinline__ float anchor_value(const ScoreArgs &a, const Unit &un, int u, int T, int c)
+{
+    const int64_t at = (int64_t)u * (2 * a.D + 2 * a.R) + c;
+    if (!a.pre) return a.anchors[at];
+    const float v = a.pre[at];
+    if (c < a.D) return centroid_component(a, un, T, c, v);
+    if (c < 2 * a.D) return v / (float)T;
+    if (c < 2 * a.D + a.R) return v * kLog2e;
+    return v;
+}
+
+// The unit's anchors for a sweep-2 block: the workspace row after the first
+// sweep, or, with handed-over sums, the converted row staged in `lds` (every
+// thread of the block calls it; a.pre is the same for the whole launch).
+__device__ __forceinline__ const float *unit_anchors(const ScoreArgs &a, const Unit &un, int u, int T, float *lds)
+{
+    if (!a.pre) return a.anchors + (int64_t)u * (2 * a.D + 2 * a.R);
+    for (int c = threadIdx.x; c < 2 * a.D + 2 * a.R; c += blockDim.x) lds[c] = anchor_value(a, un, u, T, c);
+    __syncthreads();
+    return lds;
+}
+
+// The workspace's exchange tag, bumped once per score call by the second
+// sweep's first block and read by the split epilogue after it, so that every
+// call (every replay of a captured call included) tags its exchanges afresh
+// and never reads an older call's words (0 is skipped: the status word
+// records the tag of a call whose wait gave up).
+__device__ __forceinline__ void bump_call_tag(const ScoreArgs &a)
+{
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
+        const unsigned t = *a.tagw + 1u;
+        *a.tagw = t ? t : 1u;
+    }
+}
+
 namespace fast {
 
 // Hot-loop transcendentals as single instructions (v_exp_f32, v_rsq_f32,
@@ -50,7 +105,6 @@ __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_ex
 
 constexpr int kD = 128;
 constexpr int kChunks = 16;           // 16-byte chunks per key row
-constexpr int kTile = 128;            // keys per LDS tile (4 waves x 32 keys)
 
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
@@ -136,35 +190,6 @@ __device__ __forceinline__ void mu_operand(const float *v, int which, int h, bf1
         }
         op[s] = __builtin_bit_cast(bf16x8, q);
     }
-}
-
-// The centroid's components at the 64 dimensions a lane holds in that layout.
-__device__ __forceinline__ void centroid_lane(const float *kbar, int h, float (&kb)[8][8])
-{
-#pragma unroll
-    for (int s = 0; s < 8; ++s) {
-        const float4 *src = reinterpret_cast<const float4 *>(kbar + 8 * (2 * s + h));
-        const float4 x = src[0], y = src[1];
-        kb[s][0] = x.x; kb[s][1] = x.y; kb[s][2] = x.z; kb[s][3] = x.w;
-        kb[s][4] = y.x; kb[s][5] = y.y; kb[s][6] = y.z; kb[s][7] = y.w;
-    }
-}
-
-// Sum over the lane's 64 dimensions of (k_d - kbar_d)^2, the differences
-// formed in fp32 (exact for bf16 keys near the centroid); two partial sums.
-__device__ __forceinline__ float dist2_lane(const u32x4 (&b)[8], const float (&kb)[8][8])
-{
-    float s0 = 0.f, s1 = 0.f;
-#pragma unroll
-    for (int s = 0; s < 8; ++s)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const float d0 = __uint_as_float(b[s][e] << 16) - kb[s][2 * e];
-            const float d1 = __uint_as_float(b[s][e] & 0xffff0000u) - kb[s][2 * e + 1];
-            s0 = fmaf(d0, d0, s0);
-            s1 = fmaf(d1, d1, s1);
-        }
-    return s0 + s1;
 }
 
 }  // namespace fast

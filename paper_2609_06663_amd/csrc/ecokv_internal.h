@@ -191,6 +191,12 @@ int decode_parts(int max_count);
 // Sets a.nparts and a.wave_rows, then launches the decode and merge kernels.
 hipError_t decode_launch(DecodeArgs a, bool bf16, hipStream_t st);
 
+// The sweeps of ecokv_sweep.hip (every dtype, head_dim and number of window
+// rows): pass 1 or 2 over blocks of a.rpb1 / a.rpb2 keys, a power of two from
+// 128 (bf16: 256) to sweep_rows_max_keys.
+int sweep_rows_max_keys(bool bf16);
+void sweep_rows_launch(int pass, const ScoreArgs &a, int blocks, hipStream_t st);
+
 WsLayout score_ws_layout(int L, int Hkv, int B, int D, int R, int64_t Ptot, int maxT, bool bf16, bool vnorm);
 hipError_t score_launch(ScoreArgs a, char *ws, const WsLayout &lay, int maxT, hipStream_t st, bool bf16);
 
@@ -230,8 +236,6 @@ __device__ __forceinline__ void lds_barrier()
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
-
-__device__ __forceinline__ float bf16_to_f32(uint16_t x) { return __uint_as_float((uint32_t)x << 16); }
 
 // Lane moves within 16-lane rows (DPP, no LDS round trip): quad permutes, the
 // mirrored lane within each 8 and within each 16.
@@ -325,42 +329,6 @@ __device__ __forceinline__ float seg16_sum(float x) { return row_reduce<16>(x, O
 __device__ __forceinline__ float wave_sum(float x) { return row_reduce<64>(x, OpAdd{}); }
 __device__ __forceinline__ float wave_min(float x) { return row_reduce<64>(x, OpMin{}); }
 __device__ __forceinline__ float wave_max(float x) { return row_reduce<64>(x, OpMax{}); }
-
-// Load the VEC = D/16 elements of segment c of a key row as float.
-template <int D, bool BF>
-__device__ __forceinline__ void load_seg(const void *row, int c, float *v)
-{
-    constexpr int VEC = D / 16;
-    if constexpr (BF) {
-        const uint16_t *p = static_cast<const uint16_t *>(row) + c * VEC;
-        if constexpr (VEC == 8) {
-            const uint4 q = *reinterpret_cast<const uint4 *>(p);
-            const uint32_t w4[4] = {q.x, q.y, q.z, q.w};
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                v[2 * e] = __uint_as_float(w4[e] << 16);
-                v[2 * e + 1] = __uint_as_float(w4[e] & 0xffff0000u);
-            }
-        } else {
-            const uint2 q = *reinterpret_cast<const uint2 *>(p);
-            v[0] = __uint_as_float(q.x << 16);
-            v[1] = __uint_as_float(q.x & 0xffff0000u);
-            v[2] = __uint_as_float(q.y << 16);
-            v[3] = __uint_as_float(q.y & 0xffff0000u);
-        }
-    } else {
-        const float *p = static_cast<const float *>(row) + c * VEC;
-        if constexpr (VEC == 8) {
-            const float4 a = reinterpret_cast<const float4 *>(p)[0];
-            const float4 b = reinterpret_cast<const float4 *>(p)[1];
-            v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
-            v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
-        } else {
-            const float4 a = reinterpret_cast<const float4 *>(p)[0];
-            v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
-        }
-    }
-}
 
 // A value the caller knows to be equal in every lane of the wave, made
 // visibly so to the compiler (read from the first active lane): buffer

@@ -15,15 +15,10 @@
 //            lambda (Eq. (6)); pooled S_imp (Table 6), s_E (Eq. (2)), s_C,
 //            S_div (Eq. (3)); the rescale of Sec. 5.2 and S (Eq. (7)).
 //
-// Two implementations of the sweeps:
-//   * bf16 with head_dim 128 (the shapes of the paper's models): a 128-key
-//     tile is staged through LDS (XOR-swizzled 16-byte chunks, conflict free
-//     for both read patterns).  Geometry runs on the VALU with 16 lanes per
-//     key row (DPP row reductions); the window logits run on the matrix
-//     cores, v_mfma_f32_32x32x16_bf16 with the window rows as the 32-row A
-//     operand and 32 keys per wave as the B operand.
-//   * any other case (fp32 inputs, head_dim 64): a plain VALU sweep with 16
-//     lanes per key row and window dot products reduced across the row.
+// The sweeps of bf16 keys with head_dim 128 whose window rows fit one 32-row
+// operand are here: each wave streams its own keys, v_mfma_f32_32x32x16_bf16
+// with 32 window rows against 32 keys.  Those of every other shape are in
+// ecokv_sweep.hip.
 #include <stdlib.h>
 #include <string.h>
 
@@ -31,344 +26,10 @@
 
 namespace ecokv {
 
-constexpr int kThreads = 256;
-constexpr int kCh = 128;        // key rows per block, generic sweeps
-
-// Component c of kbar from the sum of the unit's T keys: divided by T, or,
-// with the centroid over the non-window keys, the w window rows taken out
-// and divided by P.
-__device__ __forceinline__ float centroid_component(const ScoreArgs &a, const Unit &un, int T, int c, float s)
-{
-    if (!a.centroid_prefix) return s / (float)T;
-    const int64_t r0 = unit_row0(a, un) + (T - a.w);
-    float ws = 0.f;
-    for (int j = 0; j < a.w; ++j) {
-        const int64_t off = (r0 + j) * a.D + c;
-        ws += a.kbf16 ? __uint_as_float((uint32_t)static_cast<const uint16_t *>(a.K)[off] << 16)
-                      : static_cast<const float *>(a.K)[off];
-    }
-    return (s - ws) / (float)(T - a.w);
-}
-
-// Anchor column c of unit u (the layout of a.anchors: kbar, mu, the window
-// rows' base-2 references and sums): from the workspace after the first sweep,
-// or converted from the sums a prefill handed over (ecokv_score_pre: plain
-// sums over the T keys, references in natural units).
-__device__ __forceinline__ float anchor_value(const ScoreArgs &a, const Unit &un, int u, int T, int c)
-{
-    const int64_t at = (int64_t)u * (2 * a.D + 2 * a.R) + c;
-    if (!a.pre) return a.anchors[at];
-    const float v = a.pre[at];
-    if (c < a.D) return centroid_component(a, un, T, c, v);
-    if (c < 2 * a.D) return v / (float)T;
-    if (c < 2 * a.D + a.R) return v * kLog2e;
-    return v;
-}
-
-// The unit's anchors for a sweep-2 block: the workspace row after the first
-// sweep, or, with handed-over sums, the converted row staged in `lds` (every
-// thread of the block calls it; a.pre is the same for the whole launch).
-__device__ __forceinline__ const float *unit_anchors(const ScoreArgs &a, const Unit &un, int u, int T, float *lds)
-{
-    if (!a.pre) return a.anchors + (int64_t)u * (2 * a.D + 2 * a.R);
-    for (int c = threadIdx.x; c < 2 * a.D + 2 * a.R; c += blockDim.x) lds[c] = anchor_value(a, un, u, T, c);
-    __syncthreads();
-    return lds;
-}
-
 // ---------------------------------------------------------------------------
-// Generic sweeps (fp32 or head_dim 64): 16 lanes per key row.
-// ---------------------------------------------------------------------------
-template <int D, bool BF>
-__device__ void load_window_rows(const ScoreArgs &a, const Unit &un, float *q)
-{
-    for (int idx = threadIdx.x; idx < a.R * D; idx += blockDim.x) {
-        const int r = idx / D, d = idx % D;
-        const int64_t qrow = window_row(a, un, r);
-        float v;
-        if constexpr (BF)
-            v = bf16_to_f32(static_cast<const uint16_t *>(a.Q)[qrow * D + d]);
-        else
-            v = static_cast<const float *>(a.Q)[qrow * D + d];
-        q[r * D + d] = v;
-    }
-}
-
-template <int D, bool BF>
-__global__ __launch_bounds__(kThreads) void k_pass1(ScoreArgs a)
-{
-    constexpr int VEC = D / 16;
-    constexpr int ESZ = BF ? 2 : 4;
-    __shared__ float q_lds[ECOKV_MAX_ROWS * D];
-    __shared__ float lg[ECOKV_MAX_ROWS * (kCh + 1)];
-    __shared__ float red[2][16][D];
-
-    const int u = blockIdx.y;
-    const Unit un = unit_of(u, a.Hkv, a.B);
-    const int T = a.seq.cu[un.s + 1] - a.seq.cu[un.s];
-    const int P = T - a.w;
-    const int row0 = blockIdx.x * kCh;
-    if (row0 >= T) return;
-
-    load_window_rows<D, BF>(a, un, q_lds);
-    __syncthreads();
-
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int c = lane & 15, sub = lane >> 4;
-    const char *k0 = static_cast<const char *>(a.K) + unit_row0(a, un) * D * ESZ;
-    float sk[VEC], skh[VEC];
-#pragma unroll
-    for (int e = 0; e < VEC; ++e) sk[e] = skh[e] = 0.f;
-
-    for (int it = 0; it < kCh / 16; ++it) {
-        const int rl = it * 16 + wv * 4 + sub;
-        const int i = row0 + rl;
-        const bool valid = i < T;
-        float v[VEC];
-        if (valid) {
-            load_seg<D, BF>(k0 + (int64_t)i * D * ESZ, c, v);
-        } else {
-#pragma unroll
-            for (int e = 0; e < VEC; ++e) v[e] = 0.f;
-        }
-        float n2 = 0.f;
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) n2 += v[e] * v[e];
-        n2 = seg16_sum(n2);
-        const float inv = 1.f / fmaxf(sqrtf(n2), 1e-12f);
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) {
-            sk[e] += v[e];
-            skh[e] += v[e] * inv;
-        }
-        for (int r = 0; r < a.R; ++r) {
-            const float *qr = q_lds + r * D + c * VEC;
-            float d = 0.f;
-#pragma unroll
-            for (int e = 0; e < VEC; ++e) d += qr[e] * v[e];
-            d = seg16_sum(d);
-            const int j = r % a.w;
-            const bool vis = valid && (!a.causal || i <= P + j);
-            if (c == 0) lg[r * (kCh + 1) + rl] = vis ? d * (a.inv_sqrt_d * kLog2e) : -INFINITY;
-        }
-    }
-#pragma unroll
-    for (int e = 0; e < VEC; ++e) {
-        red[0][wv * 4 + sub][c * VEC + e] = sk[e];
-        red[1][wv * 4 + sub][c * VEC + e] = skh[e];
-    }
-    __syncthreads();
-
-    const int stride = 2 * D + 2 * a.R;
-    float *part = a.part1 + ((int64_t)u * a.nch1 + blockIdx.x) * stride;
-    for (int r = threadIdx.x; r < a.R; r += blockDim.x) {
-        float m = -INFINITY;
-        for (int t = 0; t < kCh; ++t) m = fmaxf(m, lg[r * (kCh + 1) + t]);
-        float s = 0.f;
-        if (m > -INFINITY)
-            for (int t = 0; t < kCh; ++t) s += exp2f(lg[r * (kCh + 1) + t] - m);
-        part[2 * D + r] = m;
-        part[2 * D + a.R + r] = s;
-    }
-    for (int d = threadIdx.x; d < D; d += blockDim.x) {
-        float s0 = 0.f, s1 = 0.f;
-        for (int g = 0; g < 16; ++g) {
-            s0 += red[0][g][d];
-            s1 += red[1][g][d];
-        }
-        part[d] = s0;
-        part[D + d] = s1;
-    }
-}
-
-// The workspace's exchange tag, bumped once per score call by the second
-// sweep's first block and read by the split epilogue after it, so that every
-// call (every replay of a captured call included) tags its exchanges afresh
-// and never reads an older call's words (0 is skipped: the status word
-// records the tag of a call whose wait gave up).
-__device__ __forceinline__ void bump_call_tag(const ScoreArgs &a)
-{
-    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
-        const unsigned t = *a.tagw + 1u;
-        *a.tagw = t ? t : 1u;
-    }
-}
-
-template <int D, bool BF>
-__global__ __launch_bounds__(kThreads) void k_pass2(ScoreArgs a)
-{
-    bump_call_tag(a);
-    constexpr int VEC = D / 16;
-    constexpr int ESZ = BF ? 2 : 4;
-    __shared__ float q_lds[ECOKV_MAX_ROWS * D];
-    __shared__ float kb[D], mu[D], rm[ECOKV_MAX_ROWS], rs_inv[ECOKV_MAX_ROWS];
-    __shared__ float wred[4][kThreads / kWave];
-
-    const int u = blockIdx.y;
-    const Unit un = unit_of(u, a.Hkv, a.B);
-    const int T = a.seq.cu[un.s + 1] - a.seq.cu[un.s];
-    const int P = T - a.w;
-    const int row0 = blockIdx.x * kCh;
-    if (row0 >= T) return;
-    load_window_rows<D, BF>(a, un, q_lds);
-    for (int d = threadIdx.x; d < D; d += blockDim.x) {
-        kb[d] = anchor_value(a, un, u, T, d);
-        mu[d] = anchor_value(a, un, u, T, D + d);
-    }
-    for (int r = threadIdx.x; r < a.R; r += blockDim.x) {
-        rm[r] = anchor_value(a, un, u, T, 2 * D + r);
-        rs_inv[r] = 1.f / anchor_value(a, un, u, T, 2 * D + a.R + r);
-    }
-    __syncthreads();
-
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int c = lane & 15, sub = lane >> 4;
-    const char *k0 = static_cast<const char *>(a.K) + unit_row0(a, un) * D * ESZ;
-    const int64_t obase = unit_out_base(a, un);
-    const float inv_r = 1.f / (float)a.R;
-    float dsum = 0.f, dsq = 0.f, dmin = INFINITY, dmax = -INFINITY;
-
-    for (int it = 0; it < kCh / 16; ++it) {
-        const int i = row0 + it * 16 + wv * 4 + sub;
-        const bool valid = i < T;
-        float v[VEC];
-        if (valid) {
-            load_seg<D, BF>(k0 + (int64_t)i * D * ESZ, c, v);
-        } else {
-#pragma unroll
-            for (int e = 0; e < VEC; ++e) v[e] = 0.f;
-        }
-        float d2 = 0.f, n2 = 0.f, km = 0.f;
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) {
-            const float df = v[e] - kb[c * VEC + e];
-            d2 += df * df;
-            n2 += v[e] * v[e];
-            km += v[e] * mu[c * VEC + e];
-        }
-        d2 = seg16_sum(d2);
-        n2 = seg16_sum(n2);
-        km = seg16_sum(km);
-        const float dE = sqrtf(d2);
-        const float cm = km / fmaxf(sqrtf(n2), 1e-12f);
-        float att = 0.f;
-        for (int r = 0; r < a.R; ++r) {
-            const float *qr = q_lds + r * D + c * VEC;
-            float d = 0.f;
-#pragma unroll
-            for (int e = 0; e < VEC; ++e) d += qr[e] * v[e];
-            d = seg16_sum(d);
-            if (i < P) att += exp2f(d * (a.inv_sqrt_d * kLog2e) - rm[r]) * rs_inv[r];
-        }
-        if (valid) {
-            dsum += (c == 0) ? dE : 0.f;
-            dsq += (c == 0) ? dE * dE : 0.f;
-            if (i < P) {
-                dmin = fminf(dmin, dE);
-                dmax = fmaxf(dmax, dE);
-                if (c == 0) {
-                    a.bufA[obase + i] = dE;
-                    a.bufB[obase + i] = cm;
-                    a.bufC[obase + i] = att * inv_r;
-                }
-            }
-        }
-    }
-    dsum = wave_sum(dsum);
-    dsq = wave_sum(dsq);
-    dmin = wave_min(dmin);
-    dmax = wave_max(dmax);
-    if (lane == 0) {
-        wred[0][wv] = dsum;
-        wred[1][wv] = dmin;
-        wred[2][wv] = dmax;
-        wred[3][wv] = dsq;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        float s = 0.f, s2 = 0.f, mn = INFINITY, mx = -INFINITY;
-        for (int k = 0; k < kThreads / kWave; ++k) {
-            s += wred[0][k];
-            mn = fminf(mn, wred[1][k]);
-            mx = fmaxf(mx, wred[2][k]);
-            s2 += wred[3][k];
-        }
-        float *pp = a.part2 + ((int64_t)u * a.nch2 + blockIdx.x) * 4;
-        pp[0] = s;
-        pp[1] = mn;
-        pp[2] = mx;
-        pp[3] = s2;
-    }
-}
-
-// ---------------------------------------------------------------------------
-// bf16, head_dim 128: LDS-staged tiles, matrix-core window logits and
-// projections.
+// bf16, head_dim 128, one 32-row window operand.
 // ---------------------------------------------------------------------------
 namespace fast {
-
-constexpr float kRebase = 16.f;       // log2 headroom of a lazily moved softmax reference
-constexpr int kTilesPerBlock = 8;  // tiles per block (1024 keys)
-constexpr int kSweep1Depth = 2;    // tiles in flight ahead of the one in use
-constexpr int kSweep2Depth = 2;
-constexpr int kRows = kTile * kTilesPerBlock;
-constexpr int kSmallRows = 2 * kTile;  // keys per block when 1024-key blocks would be too few to fill the device
-
-// One 128-key tile into registers: 16 lanes per 256-byte row, coalesced.
-// Rows outside the descriptor's range come back as zero.
-__device__ __forceinline__ void tile_load(u32x4 (&pf)[8], __amdgpu_buffer_rsrc_t rs, int tr0, int g, int c)
-{
-#pragma unroll
-    for (int j = 0; j < 8; ++j)
-        pf[j] = __builtin_amdgcn_raw_buffer_load_b128(rs, (tr0 + j * 16 + g) * (kD * 2) + c * 16, 0, 2);  // nt: read once
-}
-
-__device__ __forceinline__ void tile_store(u32x4 *kt, const u32x4 (&pf)[8], int g, int c)
-{
-#pragma unroll
-    for (int j = 0; j < 8; ++j) kt[sw(j * 16 + g, c)] = pf[j];
-}
-
-// The first DEPTH 128-key tiles of a block into registers: issued before the
-// block's set-up loads (window rows, anchors), so that their latencies overlap.
-template <int DEPTH>
-__device__ __forceinline__ void tile_prefetch(u32x4 (&pf)[DEPTH][8], __amdgpu_buffer_rsrc_t rs, int row_base, int g,
-                                              int c)
-{
-#pragma unroll
-    for (int d = 0; d < DEPTH; ++d) tile_load(pf[d], rs, row_base + d * kTile, g, c);
-}
-
-// Calls body(tr0) for each of the block's `ntiles` 128-key tiles with the tile
-// in kt, the first DEPTH of them already in pf (tile_prefetch).  DEPTH tiles
-// are in flight in registers while one is processed.  The prefetch is
-// unconditional (the descriptor ends at the block's last row), so every
-// barrier waits only for LDS and the oldest tile.
-template <int DEPTH, class F>
-__device__ __forceinline__ void tile_pipeline(u32x4 (&pf)[DEPTH][8], u32x4 *kt, __amdgpu_buffer_rsrc_t rs,
-                                              int row_base, int ntiles, int g, int c, F &&body)
-{
-    // The loop over groups of DEPTH tiles is kept rolled (code size); the
-    // loads are unconditional, so the outstanding-load count is the same on
-    // every path and each barrier waits only for the oldest tile.
-    // Whole groups only: a tile past the block's range reads as zeros from the
-    // descriptor and adds nothing (callers mask keys at or past T), so every
-    // iteration is identical and no path re-enters the loop with fewer loads
-    // in flight.
-    const int ngroups = (ntiles + DEPTH - 1) / DEPTH;
-#pragma unroll 1
-    for (int grp = 0; grp < ngroups; ++grp) {
-#pragma unroll
-        for (int d = 0; d < DEPTH; ++d) {
-            const int tile = grp * DEPTH + d;
-            tile_store(kt, pf[d], g, c);
-            lds_barrier();
-            tile_load(pf[d], rs, row_base + (tile + DEPTH) * kTile, g, c);
-            body(row_base + tile * kTile);
-            lds_barrier();
-        }
-    }
-}
 
 // Window rows 32t + (lane & 31) as MFMA A operands (zero beyond R): for k-step
 // s the lane holds elements 8*(2s + lane/32) .. +7.
@@ -388,351 +49,6 @@ __device__ __forceinline__ void load_query_operands(const ScoreArgs &a, const Un
             const u32x4 z = {0u, 0u, 0u, 0u};
             aq[t][s] = __builtin_bit_cast(bf16x8, ok ? q[s] : z);
         }
-    }
-}
-
-// Sweep 1, per block of a.rpb1 keys (kRows, or kSmallRows for calls with few blocks):
-//  * window logits on the matrix cores (window rows x 32 keys per wave) with
-//    per-row online softmax statistics, x = log2(e) q.k / sqrt(d_k);
-//  * |k|^2 from v_dot2 on the same B registers, and 1/|k| per key;
-//  * the column sums sum_k k and sum_k k/|k| also on the matrix cores: the
-//    A operand rows are (1, 1/|k| high bf16, 1/|k| remainder) over 16 keys and
-//    the B operand is 16 keys x 32 dimensions, read transposed from the LDS
-//    tile with ds_read_b64_tr_b16 (each 16-lane group returns the 4 x 4
-//    transpose of the 8-byte pieces its lanes address).
-template <int MT>
-__global__ __launch_bounds__(256, MT == 1 ? 2 : 1) void k_fs1(ScoreArgs a)
-{
-    __shared__ u32x4 kt[kTile * kChunks];                   // 32 KiB key tile
-    __shared__ __attribute__((aligned(16))) uint16_t aw[4][kTile];  // ones, 1/|k| high, remainder, zeros
-
-    const int u = blockIdx.y;
-    const Unit un = unit_of(u, a.Hkv, a.B);
-    const int T = a.seq.cu[un.s + 1] - a.seq.cu[un.s];
-    const int P = T - a.w;
-    const int row_base = blockIdx.x * a.rpb1;
-    if (row_base >= T) return;
-
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int c = tid & 15, g = tid >> 4, h = lane >> 5;
-    const uint16_t *krow0 = static_cast<const uint16_t *>(a.K) + unit_row0(a, un) * kD;
-    const float sc = a.inv_sqrt_d * kLog2e;
-    const __amdgpu_buffer_rsrc_t rs = key_rows_rsrc(krow0, min(T, row_base + a.rpb1));
-    u32x4 pf[kSweep1Depth][8];
-    tile_prefetch(pf, rs, row_base, g, c);
-
-    bf16x8 aq[MT][8];
-    load_query_operands<MT>(a, un, lane, aq);
-    for (int i = tid; i < kTile; i += blockDim.x) {
-        aw[0][i] = 0x3f80;  // 1.0
-        aw[3][i] = 0;
-    }
-
-    // Per-lane addresses of the transposed reads (constant over the block):
-    // lane X reads 4 dimensions 32 wv + 16 ((X/16) % 2) + 4 (X % 4) of key
-    // 8 (X/32) + ((X % 16) / 4) (+4 for the second read) of each 16-key step.
-    const int tr_key = 8 * (lane >> 5) + ((lane & 15) >> 2);
-    const int tr_dim = 32 * wv + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
-    const int aw_row = (lane & 31) < 3 ? (lane & 31) : 3;
-
-    float ms[MT][16], ss[MT][16];
-#pragma unroll
-    for (int t = 0; t < MT; ++t)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            ms[t][i] = -INFINITY;
-            ss[t][i] = 0.f;
-        }
-    f32x16 csum = (f32x16){};
-
-    const int ntiles = min(a.rpb1 / kTile, (T - row_base + kTile - 1) / kTile);
-    tile_pipeline(pf, kt, rs, row_base, ntiles, g, c, [&](int tr0) {
-        // window logits and |k|^2 of this wave's 32 keys
-        f32x16 acc[MT];
-#pragma unroll
-        for (int t = 0; t < MT; ++t) acc[t] = (f32x16){};
-        float n2 = 0.f;
-        {
-            const int r = 32 * wv + (lane & 31);
-#pragma unroll
-            for (int s = 0; s < 8; ++s) {
-                const u32x4 bq = kt[sw(r, 2 * s + h)];
-                n2 = dot2sq(bq[0], dot2sq(bq[1], dot2sq(bq[2], dot2sq(bq[3], n2))));
-                const bf16x8 b = __builtin_bit_cast(bf16x8, bq);
-#pragma unroll
-                for (int t = 0; t < MT; ++t)
-                    acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(aq[t][s], b, acc[t], 0, 0, 0);
-            }
-        }
-        n2 += __shfl_xor(n2, 32, kWave);
-        if (h == 0) {
-            const float inv = __builtin_amdgcn_rsqf(fmaxf(n2, 1e-24f));
-            const unsigned hi = bf16_rne(inv);
-            aw[1][32 * wv + lane] = (uint16_t)hi;
-            aw[2][32 * wv + lane] = (uint16_t)bf16_rne(inv - __uint_as_float(hi << 16));
-        }
-
-        // online softmax statistics.  (ms, ss) keeps ss = sum 2^(x - ms) over the
-        // values seen so far, where ms is a reference that stays within
-        // kRebase of the running maximum instead of tracking it exactly: the
-        // reference moves only when a value exceeds it by more than kRebase,
-        // so after the first tile almost every tile takes the cheap branch.
-        const int gi = tr0 + 32 * wv + (lane & 31);
-        if (tr0 + kTile <= P) {
-            // every key of the tile is a non-window key, visible to every row
-            if (tr0 == row_base) {
-                // first tile of the block: each value is its own reference
-#pragma unroll
-                for (int t = 0; t < MT; ++t)
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) {
-                        ms[t][i] = acc[t][i] * sc;
-                        ss[t][i] = 1.f;
-                    }
-            } else {
-                float d[MT][16];
-                float dmax = -INFINITY;
-#pragma unroll
-                for (int t = 0; t < MT; ++t)
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) {
-                        d[t][i] = fmaf(acc[t][i], sc, -ms[t][i]);
-                        dmax = fmaxf(dmax, d[t][i]);
-                    }
-                if (!__any(dmax > kRebase)) {
-#pragma unroll
-                    for (int t = 0; t < MT; ++t)
-#pragma unroll
-                        for (int i = 0; i < 16; ++i) ss[t][i] += fast_exp2(d[t][i]);
-                } else {
-#pragma unroll
-                    for (int t = 0; t < MT; ++t)
-#pragma unroll
-                        for (int i = 0; i < 16; ++i) {
-                            if (d[t][i] > kRebase) {
-                                ss[t][i] = fmaf(ss[t][i], fast_exp2(-d[t][i]), 1.f);
-                                ms[t][i] = acc[t][i] * sc;
-                            } else {
-                                ss[t][i] += fast_exp2(d[t][i]);
-                            }
-                        }
-                }
-            }
-        } else {
-#pragma unroll
-            for (int t = 0; t < MT; ++t)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    const int m = 32 * t + 8 * (i >> 2) + 4 * h + (i & 3);
-                    const bool ok = gi < T && (!a.causal || gi <= P + (m % a.w));
-                    const float x = acc[t][i] * sc;
-                    const float dd = x - ms[t][i];
-                    const float e = fast_exp2(-fabsf(dd));
-                    const float s_new = dd > 0.f ? fmaf(ss[t][i], e, 1.f) : ss[t][i] + e;
-                    if (ok) {
-                        ss[t][i] = s_new;
-                        ms[t][i] = fmaxf(ms[t][i], x);
-                    }
-                }
-        }
-        lds_barrier();  // 1/|k| of the tile is in aw
-
-        // column sums on the matrix cores: this wave's 32 dimensions, 8 steps of 16 keys
-#pragma unroll
-        for (int ks = 0; ks < 8; ++ks) {
-            const bf16x8 wa = *reinterpret_cast<const bf16x8 *>(&aw[aw_row][16 * ks + 8 * h]);
-            const int key0 = 16 * ks + tr_key;
-            typedef short s16x4 __attribute__((ext_vector_type(4)));
-            const uint16_t *p0 = reinterpret_cast<const uint16_t *>(kt) + key0 * kD +
-                                 (((tr_dim >> 3) ^ (key0 & 15)) << 3) + (tr_dim & 7);
-            const uint16_t *p1 = reinterpret_cast<const uint16_t *>(kt) + (key0 + 4) * kD +
-                                 (((tr_dim >> 3) ^ ((key0 + 4) & 15)) << 3) + (tr_dim & 7);
-            const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-                (__attribute__((address_space(3))) s16x4 *)(const_cast<uint16_t *>(p0)));
-            const s16x4 hi4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-                (__attribute__((address_space(3))) s16x4 *)(const_cast<uint16_t *>(p1)));
-            const short __attribute__((ext_vector_type(8))) kb8 = {lo[0], lo[1], lo[2], lo[3],
-                                                                    hi4[0], hi4[1], hi4[2], hi4[3]};
-            csum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa, __builtin_bit_cast(bf16x8, kb8), csum, 0, 0, 0);
-        }
-    });
-
-    const int stride = 2 * kD + 2 * a.R;
-    float *part = a.part1 + ((int64_t)u * a.nch1 + blockIdx.x) * stride;
-    if (h == 0) {
-        part[32 * wv + lane] = csum[0];              // sum of k
-        part[kD + 32 * wv + lane] = csum[1] + csum[2];  // sum of k / |k|
-    }
-    // per-row softmax partials: a row's 128 (reference, sum) pairs (32 lanes
-    // of each of the 4 waves) go through the key tile, free now, and 8 threads
-    // per row merge 16 of them each, then by a 3-step DPP butterfly: the
-    // row's largest reference, each sum moved onto it, summed.  (Butterflies
-    // over the 32 lanes that hold a row, one row at a time, took 5 of this
-    // block's 12 us on one 8192-token layer: 64 dependent chains in 4 waves.)
-    // (pair p of row r at r * 128 + (p ^ 8 (r % 8)): the 8 rows a wave reads at
-    // once fall on different banks)
-    float2 *scr = reinterpret_cast<float2 *>(kt);  // [32 rows][4 waves x 32 lanes]
-#pragma unroll
-    for (int t = 0; t < MT; ++t) {
-        if (t) lds_barrier();  // the previous rows' readers are done
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const int r = 8 * (i >> 2) + 4 * h + (i & 3);
-            scr[r * 128 + ((32 * wv + (lane & 31)) ^ (8 * (r & 7)))] = make_float2(ms[t][i], ss[t][i]);
-        }
-        lds_barrier();
-        const int row = tid >> 3, q = tid & 7;
-        float2 v[16];
-#pragma unroll
-        for (int j = 0; j < 16; ++j) v[j] = scr[row * 128 + ((8 * j + q) ^ (8 * (row & 7)))];
-        float m = -INFINITY, s = 0.f;
-#pragma unroll
-        for (int j = 0; j < 16; ++j) m = fmaxf(m, v[j].x);
-#pragma unroll
-        for (int j = 0; j < 16; ++j) s += v[j].x == -INFINITY ? 0.f : v[j].y * fast_exp2(v[j].x - m);
-        const float mg = row_reduce<8>(m, OpMax{});
-        s = row_reduce<8>(m == -INFINITY ? 0.f : s * fast_exp2(m - mg), OpAdd{});
-        if (q == 0 && 32 * t + row < a.R) {
-            part[2 * kD + 32 * t + row] = mg;
-            part[2 * kD + a.R + 32 * t + row] = s;
-        }
-    }
-}
-
-// Sweep 2.  The A operand carries the window rows and, in its last two rows,
-// mu split into a bf16 high part and a bf16 remainder, so that one MFMA chain
-// gives q.k for the window rows together with k.mu to about 2^-17 relative.
-// |k|^2 comes from v_dot2 on the same B registers; khat.mu = k.mu / |k|.
-// d_E = |k - kbar| is summed directly from the differences in fp32 (each lane
-// over the 64 dimensions it holds): the expansion |k|^2 - 2 k.kbar + |kbar|^2
-// would lose the distance to cancellation when the keys share a large common
-// offset (mean cosine near 1, Sec. 4).
-template <int MT>
-__global__ __launch_bounds__(256, MT == 1 ? 2 : 1) void k_fs2(ScoreArgs a)
-{
-    bump_call_tag(a);
-    constexpr int kAnc = 32 * MT - 2;  // first anchor row of the A operand
-    __shared__ u32x4 kt[kTile * kChunks];
-    __shared__ float rowM[32 * MT], rowIS[32 * MT];
-    __shared__ float wred[4][4];
-
-    const int u = blockIdx.y;
-    const Unit un = unit_of(u, a.Hkv, a.B);
-    const int T = a.seq.cu[un.s + 1] - a.seq.cu[un.s];
-    const int P = T - a.w;
-    const int row_base = blockIdx.x * a.rpb2;
-    if (row_base >= T) return;
-
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int c = tid & 15, g = tid >> 4, h = lane >> 5;
-    const uint16_t *krow0 = static_cast<const uint16_t *>(a.K) + unit_row0(a, un) * kD;
-    const int64_t obase = unit_out_base(a, un);
-    const __amdgpu_buffer_rsrc_t rs = key_rows_rsrc(krow0, min(T, row_base + a.rpb2));
-    u32x4 pf[kSweep2Depth][8];
-    tile_prefetch(pf, rs, row_base, g, c);
-    __shared__ __attribute__((aligned(16))) float sanc[2 * kD + 2 * ECOKV_MAX_ROWS];
-    const float *anc = unit_anchors(a, un, u, T, sanc);
-    const float sc = a.inv_sqrt_d * kLog2e;
-
-    bf16x8 aq[MT][8];
-    load_query_operands<MT>(a, un, lane, aq);
-    {
-        // anchor rows: kAnc + 0: mu high, +1: mu remainder
-        const int rr = 32 * (MT - 1) + (lane & 31);
-        if (rr >= kAnc) mu_operand(anc + kD, rr - kAnc, h, aq[MT - 1]);
-    }
-    float kbv[8][8];  // kbar at the 64 dimensions this lane holds
-    centroid_lane(anc, h, kbv);
-    if (tid < 32 * MT) {
-        const bool ok = tid < a.R;
-        rowM[tid] = ok ? anc[2 * kD + tid] : 0.f;
-        rowIS[tid] = ok ? 1.f / anc[2 * kD + a.R + tid] : 0.f;
-    }
-
-    float dsum = 0.f, dsq = 0.f, dmn = INFINITY, dmx = -INFINITY;
-    const float inv_r = 1.f / (float)a.R;
-    const int ntiles = min(a.rpb2 / kTile, (T - row_base + kTile - 1) / kTile);
-    tile_pipeline(pf, kt, rs, row_base, ntiles, g, c, [&](int tr0) {
-
-        f32x16 acc[MT];
-#pragma unroll
-        for (int t = 0; t < MT; ++t) acc[t] = (f32x16){};
-        float n2 = 0.f;
-        {
-            const int r = 32 * wv + (lane & 31);
-#pragma unroll
-            for (int s = 0; s < 8; ++s) {
-                const u32x4 bq = kt[sw(r, 2 * s + h)];
-                n2 = dot2sq(bq[0], dot2sq(bq[1], dot2sq(bq[2], dot2sq(bq[3], n2))));
-                const bf16x8 b = __builtin_bit_cast(bf16x8, bq);
-#pragma unroll
-                for (int t = 0; t < MT; ++t)
-                    acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(aq[t][s], b, acc[t], 0, 0, 0);
-            }
-        }
-        float att = 0.f;
-#pragma unroll
-        for (int t = 0; t < MT; ++t)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const int m = 32 * t + 8 * (i >> 2) + 4 * h + (i & 3);
-                if (m < a.R) att = fmaf(fast_exp2(fmaf(acc[t][i], sc, -rowM[m])), rowIS[m], att);
-            }
-        float kmu = h ? acc[MT - 1][14] + acc[MT - 1][15] : 0.f;
-        float d2;
-        {
-            const int r = 32 * wv + (lane & 31);
-            u32x4 bq[8];
-#pragma unroll
-            for (int s = 0; s < 8; ++s) bq[s] = kt[sw(r, 2 * s + h)];
-            d2 = dist2_lane(bq, kbv);
-        }
-        n2 += __shfl_xor(n2, 32, kWave);
-        att += __shfl_xor(att, 32, kWave);
-        kmu += __shfl_xor(kmu, 32, kWave);
-        d2 += __shfl_xor(d2, 32, kWave);
-        const float dE = __builtin_amdgcn_sqrtf(d2);
-        const float cm = kmu * __builtin_amdgcn_rsqf(fmaxf(n2, 1e-24f));
-        const int gi = tr0 + 32 * wv + (lane & 31);
-        if (h == 0) {
-            if (gi < T) {
-                dsum += dE;
-                dsq += dE * dE;
-            }
-            if (gi < P) {
-                dmn = fminf(dmn, dE);
-                dmx = fmaxf(dmx, dE);
-                a.bufA[obase + gi] = dE;
-                a.bufB[obase + gi] = cm;
-                a.bufC[obase + gi] = att * inv_r;
-            }
-        }
-    });
-
-    dsum = wave_sum(dsum);
-    dsq = wave_sum(dsq);
-    dmn = wave_min(dmn);
-    dmx = wave_max(dmx);
-    if (lane == 0) {
-        wred[0][wv] = dsum;
-        wred[1][wv] = dmn;
-        wred[2][wv] = dmx;
-        wred[3][wv] = dsq;
-    }
-    lds_barrier();
-    if (tid == 0) {
-        float s = 0.f, s2 = 0.f, mn = INFINITY, mx = -INFINITY;
-        for (int k = 0; k < 4; ++k) {
-            s += wred[0][k];
-            mn = fminf(mn, wred[1][k]);
-            mx = fmaxf(mx, wred[2][k]);
-            s2 += wred[3][k];
-        }
-        float *pp = a.part2 + ((int64_t)u * a.nch2 + blockIdx.x) * 4;
-        pp[0] = s;
-        pp[1] = mn;
-        pp[2] = mx;
-        pp[3] = s2;
     }
 }
 
@@ -1834,15 +1150,31 @@ hipError_t status_clear(unsigned *status, hipStream_t st)
 
 bool score_fast_path(int D, bool bf16) { return bf16 && D == fast::kD; }
 
-static int rows_per_block(int D, bool bf16) { return score_fast_path(D, bf16) ? fast::kRows : kCh; }
+// Fewest keys per block of any sweep of a shape (the workspace holds a partial
+// for each block).
+static int min_block_keys(int D, bool bf16) { return score_fast_path(D, bf16) ? 256 : 128; }
 
-// Key rows per block of the block sweeps for a call: 256-key blocks when
-// 1024-key ones would be fewer than 1024 (one 8192-token layer: 32 blocks
-// on 256 compute units).
-static int block_sweep_rows(int D, bool bf16, int U, int maxT)
+// Blocks of `keys` keys over every unit of a call.
+static int64_t work_blocks(const ScoreArgs &a, int keys)
 {
-    if (!score_fast_path(D, bf16)) return kCh;
-    return (int64_t)U * ((maxT + fast::kRows - 1) / fast::kRows) >= 1024 ? fast::kRows : fast::kSmallRows;
+    int64_t nb = 0;
+    for (int s = 0; s < a.B; ++s) nb += (a.seq.cu[s + 1] - a.seq.cu[s] + keys - 1) / keys;
+    return nb * a.L * a.Hkv;
+}
+
+// Keys per block of ecokv_sweep.hip's sweeps: the most that give every
+// compute unit a block.  Longer blocks pay their set-up (window rows,
+// anchors, first loads) and their partial less often, fewer than 256 leave
+// compute units idle (sweep 2, us, at 512 / 1024 / 2048 keys: 12 layers of 4
+// heads x 16384 x 64 bf16 37.5 / 33.8 / 29.5; 14 layers of 4 x 32768 x 128,
+// 56 window rows, 158 / 130 / 128; one layer of 4 x 32768 x 128 14.0 / 18.1 /
+// 29.2; 4 layers of 4 x 8192 x 128 fp32 at 256 / 512 / 1024: 29.6 / 25.1 / 39.8).
+// A wave's quarter is at least one batch of keys: 256 per block for bf16, 128 for fp32.
+static int rows_block_keys(const ScoreArgs &a, bool bf16)
+{
+    int keys = sweep_rows_max_keys(bf16);
+    while (keys > (bf16 ? 256 : 128) && work_blocks(a, keys) < 256) keys /= 2;
+    return keys;
 }
 
 // ---------------------------------------------------------------------------
@@ -1918,9 +1250,7 @@ WsLayout score_ws_layout(int L, int Hkv, int B, int D, int R, int64_t Ptot, int 
 {
     WsLayout w{};
     const int64_t U = (int64_t)L * Hkv * B;
-    // the smallest key block of any sweep: the block sweeps' small blocks
-    // (the streaming sweeps' are larger)
-    const int rpb = min(rows_per_block(D, bf16), fast::kSmallRows);
+    const int rpb = min_block_keys(D, bf16);
     const int64_t nch1 = (maxT + rpb - 1) / rpb;
     const int64_t nch2 = nch1;
     const int64_t nch3 = (maxT + kEpiKeys - 1) / kEpiKeys;
@@ -1941,41 +1271,6 @@ WsLayout score_ws_layout(int L, int Hkv, int B, int D, int R, int64_t Ptot, int 
     w.epiT = o; o = align256(o + sizeof(unsigned long long) * U * kEpiSplitMax * 4);
     w.total = o;
     return w;
-}
-
-template <int MT1, int MT2>
-static void launch_fast_sweep(int pass, const ScoreArgs &a, dim3 grid, hipStream_t st)
-{
-    if (pass == 1)
-        hipLaunchKernelGGL((fast::k_fs1<MT1>), grid, dim3(256), 0, st, a);
-    else
-        hipLaunchKernelGGL((fast::k_fs2<MT2>), grid, dim3(256), 0, st, a);
-}
-
-static void launch_sweep(int pass, const ScoreArgs &a, dim3 grid, hipStream_t st, bool bf16)
-{
-    if (score_fast_path(a.D, bf16)) {
-        // MT1 = ceil(R / 32) tiles of window rows; MT2 also holds the 2 rows of mu.
-        const int mt1 = (a.R + 31) / 32, mt2 = (a.R + 2 + 31) / 32;
-        if (pass == 1) {
-            if (mt1 == 1) launch_fast_sweep<1, 1>(1, a, grid, st);
-            else launch_fast_sweep<2, 1>(1, a, grid, st);
-        } else {
-            if (mt2 == 1) launch_fast_sweep<1, 1>(2, a, grid, st);
-            else if (mt2 == 2) launch_fast_sweep<1, 2>(2, a, grid, st);
-            else launch_fast_sweep<1, 3>(2, a, grid, st);
-        }
-        return;
-    }
-    if (pass == 1) {
-        if (bf16) hipLaunchKernelGGL((k_pass1<64, true>), grid, dim3(kThreads), 0, st, a);
-        else if (a.D == 128) hipLaunchKernelGGL((k_pass1<128, false>), grid, dim3(kThreads), 0, st, a);
-        else hipLaunchKernelGGL((k_pass1<64, false>), grid, dim3(kThreads), 0, st, a);
-    } else {
-        if (bf16) hipLaunchKernelGGL((k_pass2<64, true>), grid, dim3(kThreads), 0, st, a);
-        else if (a.D == 128) hipLaunchKernelGGL((k_pass2<128, false>), grid, dim3(kThreads), 0, st, a);
-        else hipLaunchKernelGGL((k_pass2<64, false>), grid, dim3(kThreads), 0, st, a);
-    }
 }
 
 // Blocks of k_epi_unit<SPLIT, KVEC> that the current device holds at once (cached per device).
@@ -2028,18 +1323,10 @@ hipError_t score_launch(ScoreArgs a, char *ws, const WsLayout &lay, int maxT, hi
     // fewer than four per compute unit (1024 blocks) and the 1024-key ones at
     // least two (one layer over 8 sequences of 4k-32k tokens: the pass
     // 186 -> 174 us against 512-key blocks); else 512-key ones
-    auto work_blocks = [&](int keys) {
-        int64_t nb = 0;
-        for (int s = 0; s < a.B; ++s) nb += (a.seq.cu[s + 1] - a.seq.cu[s] + keys - 1) / keys;
-        return nb * a.L * a.Hkv;
-    };
-    const int sblock = work_blocks(fast::kS2Keys) >= 1024  ? fast::kS2Keys
-                       : work_blocks(fast::kS2KeysMid) >= 512 ? fast::kS2KeysMid
+    const int sblock = work_blocks(a, fast::kS2Keys) >= 1024  ? fast::kS2Keys
+                       : work_blocks(a, fast::kS2KeysMid) >= 512 ? fast::kS2KeysMid
                                                               : fast::kS2KeysSmall;
     {
-        a.rpb1 = block_sweep_rows(a.D, bf16, U, maxT);
-        a.nch1 = (maxT + a.rpb1 - 1) / a.rpb1;
-        const dim3 grid(a.nch1, U);
         if (a.pre) {
             // the first sweep's sums come from the caller: K is read once (the
             // sweep-2 blocks and the epilogue convert them as they read them)
@@ -2058,7 +1345,9 @@ hipError_t score_launch(ScoreArgs a, char *ws, const WsLayout &lay, int maxT, hi
                     ECOKV_TIMED("sweep1_stream", st,
                                 hipLaunchKernelGGL((fast::k_fs1s<fast::kS2KeysSmall, false>), dim3(a.nch1, U), dim3(256), 0, st, a));
             } else {
-                ECOKV_TIMED("sweep1_block", st, launch_sweep(1, a, grid, st, bf16));
+                a.rpb1 = rows_block_keys(a, bf16);
+                a.nch1 = (maxT + a.rpb1 - 1) / a.rpb1;
+                ECOKV_TIMED("sweep1_rows", st, sweep_rows_launch(1, a, a.nch1, st));
             }
             if ((e = hipGetLastError()) != hipSuccess) return e;
             if (reduce1_lanes(a.nch1) == 4)
@@ -2083,10 +1372,9 @@ hipError_t score_launch(ScoreArgs a, char *ws, const WsLayout &lay, int maxT, hi
                 ECOKV_TIMED("sweep2_stream", st,
                             hipLaunchKernelGGL(fast::k_fs2s<fast::kS2KeysSmall>, dim3(a.nch2, U), dim3(256), 0, st, a));
         } else {
-            // block sweep 2: the chunking of the block sweeps (grid)
-            a.rpb2 = block_sweep_rows(a.D, bf16, U, maxT);
+            a.rpb2 = rows_block_keys(a, bf16);
             a.nch2 = (maxT + a.rpb2 - 1) / a.rpb2;
-            ECOKV_TIMED("sweep2_block", st, launch_sweep(2, a, grid, st, bf16));
+            ECOKV_TIMED("sweep2_rows", st, sweep_rows_launch(2, a, a.nch2, st));
         }
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
@@ -2215,7 +1503,7 @@ size_t prefill_ws_bytes(int L, int Hkv, int B, int D, int R, int maxT, bool bf16
 {
     // the block partials of sweep 1 (part1), for its smallest key block (as
     // in the score's layout)
-    const int rpb = min(rows_per_block(D, bf16), fast::kSmallRows);
+    const int rpb = min_block_keys(D, bf16);
     const size_t nch1 = (size_t)((maxT + rpb - 1) / rpb);
     return align256(sizeof(float) * (size_t)L * Hkv * B * nch1 * (size_t)(2 * D + 2 * R));
 }
@@ -2250,9 +1538,9 @@ hipError_t prefill_launch(ScoreArgs a, const void *Vsrc, void *Vdst, char *ws, i
                                        static_cast<char *>(const_cast<void *>(a.K)), a.D * es, a.L, a.Hkv, a.B, a.Ttot,
                                        a.seq));
         if ((e = hipGetLastError()) != hipSuccess) return e;
-        a.rpb1 = block_sweep_rows(a.D, bf16, U, maxT);
+        a.rpb1 = rows_block_keys(a, bf16);
         a.nch1 = (maxT + a.rpb1 - 1) / a.rpb1;
-        ECOKV_TIMED("prefill_sweep", st, launch_sweep(1, a, dim3(a.nch1, U), st, bf16));
+        ECOKV_TIMED("prefill_sweep", st, sweep_rows_launch(1, a, a.nch1, st));
     }
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (Vsrc) {

@@ -1,0 +1,124 @@
+"""The sweeps over K of every dtype, head_dim and number of window rows, at the
+edges of their tiles: 16-key tiles and 16-row window tiles, batches of 16 to
+64 keys, blocks of 128 to 2048.
+
+  sums    ecokv_prefill_write's key sums against float64.  A sum over T keys
+          is at most 32 + 4 + 4 additions per lane, wave and block and
+          T / 128 / 16 + 4 over the blocks, each rounding by 2^-24 of at most
+          the column's absolute mass: 2^-24 (44 + T / 2048) of it; the sum of
+          k / |k| adds a few roundings per term (|k|^2 over D / 4 + 2 terms,
+          halved by the square root, and the bf16 streaming form's 1 / |k| in
+          two bf16 parts, 2^-17): 2^-16 of the mass in all.
+  lse     the window rows' log-sum-exp against float64: a logit is a sum of D
+          products, each of its roundings at most 2^-24 of |q| |k| / sqrt(D).
+  scores  the whole call against the oracle (parity_utils' tolerances).
+"""
+import math
+import sys
+
+import pytest
+import torch
+
+import oracle
+import workloads as W
+from parity_utils import gpu_pass
+from test_gpu_parity import check_per_head
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _need_gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2609_06663_amd  # noqa: F401  (fails loudly if the library is not built)
+    oracle.build(force=False)
+
+
+def say(msg):
+    print(f"[gpu-sweeps] {msg}", file=sys.stderr, flush=True)
+
+
+def make(dtype, L, Hkv, G, D, w, lens, seed=0, offset_elems=0):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    cu = [0]
+    for t in lens:
+        cu.append(cu[-1] + t)
+    k = torch.randn(L, Hkv, cu[-1], D, generator=g, device="cuda") + torch.randn(L, Hkv, 1, D, generator=g, device="cuda")
+    q = torch.randn(L, Hkv * G, len(lens), w, D, generator=g, device="cuda")
+    out = []
+    for x in (k, q):
+        buf = torch.empty(x.numel() + offset_elems, dtype=dtype, device="cuda")
+        v = buf[offset_elems:].view(x.shape)
+        v.copy_(x)
+        out.append(v)
+    return cu, out[0], out[1]
+
+
+def scores(shape, K, Q):
+    import paper_2609_06663_amd as P
+    S = torch.full((shape.score_numel(),), math.nan, device="cuda")
+    lam = torch.full((shape.units,), math.nan, device="cuda")
+    st = torch.full((shape.units, P.NSTATS), math.nan, device="cuda")
+    P.ecokv_score(K, Q, shape, P.Params(), S, lam, st)
+    torch.cuda.synchronize()
+    return S, lam, st
+
+
+@pytest.mark.parametrize("dtype,D", [("f32", 128), ("f32", 64), ("bf16", 128), ("bf16", 64)])
+@pytest.mark.parametrize("G,w", [(1, 1), (4, 4), (1, 17), (8, 4), (3, 11), (8, 8)])
+@pytest.mark.parametrize("lens", [[18, 33, 128], [129, 255, 257, 1027]])
+def test_sums_and_scores_at_tile_edges(dtype, D, G, w, lens):
+    import paper_2609_06663_amd as P
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    L, Hkv, R = 1, 2, G * w
+    say(f"{dtype} D={D} R={R} T={lens}: sums")
+    cu, K, Q = make(tdt, L, Hkv, G, D, w, lens, seed=R)
+    shape = P.Shape(L, G * Hkv, Hkv, D, w, cu)
+    Kc = torch.zeros_like(K)
+    pre = torch.full((shape.units, 2 * D + 2 * R), math.nan, device="cuda")
+    P.ecokv_prefill_write(K.transpose(1, 2).contiguous(), None, Q, shape, P.Params(), Kc, None, pre)
+    assert torch.equal(Kc, K)
+    for h in range(Hkv):
+        for s, T in enumerate(lens):
+            p = pre[h * len(lens) + s].double()
+            k = K[0, h, cu[s]:cu[s + 1]].double()
+            kh = k / k.norm(dim=1, keepdim=True)
+            u = 2.0 ** -24
+            assert ((p[:D] - k.sum(0)).abs() <= u * (44 + T / 2048) * k.abs().sum(0)).all(), (h, s)
+            assert ((p[D:2 * D] - kh.sum(0)).abs() <= 2.0 ** -16 * kh.abs().sum(0)).all(), (h, s)
+            q = Q[0, h * G:(h + 1) * G, s].reshape(R, D).double()
+            x = q @ k.t() / math.sqrt(D)
+            j = torch.arange(R, device="cuda") % w
+            x.masked_fill_(torch.arange(T, device="cuda")[None] > (T - w + j)[:, None], -math.inf)
+            tol = 2 * u * D * (q.norm(dim=1) * k.norm(dim=1).max()) / math.sqrt(D) + 16 * u
+            err = (p[2 * D:2 * D + R] + p[2 * D + R:].log() - x.logsumexp(1)).abs()
+            assert (err <= tol).all(), (h, s, float((err / tol).max()))
+    say("  scores")
+    wl = W.custom(7 + R, L=1, Hq=G * Hkv, Hkv=Hkv, D=D, w=w, seqlens=lens, dtype=dtype,
+                  budget=[max(w, t // 4) for t in lens], group=16)
+    check_per_head(wl, gpu_pass(wl))
+
+
+@pytest.mark.parametrize("dtype,D,T", [("f32", 64, 4100), ("f32", 128, 4100), ("bf16", 64, 8200), ("bf16", 128, 8200)])
+def test_longest_blocks(dtype, D, T):
+    # 64 units: enough keys for the longest blocks (1024 fp32 keys, 2048 bf16),
+    # the last of each unit nearly empty; w 8 and G 5, 40 window rows
+    wl = W.custom(31, L=8, Hq=40, Hkv=8, D=D, w=8, seqlens=[T], dtype=dtype, budget=[T // 5], group=256)
+    say(f"{dtype} D={D} T={T}: longest blocks")
+    check_per_head(wl, gpu_pass(wl))
+
+
+@pytest.mark.parametrize("D", [64, 128])
+def test_keys_at_any_element(D):
+    # a view at an odd element: the same scores, bit for bit
+    import paper_2609_06663_amd as P
+    say(f"D={D}: keys and queries at 2-byte alignment")
+    lens = [700, 90]
+    cu, K, Q = make(torch.bfloat16, 2, 2, 4, D, 4, lens, seed=5)
+    cu, K1, Q1 = make(torch.bfloat16, 2, 2, 4, D, 4, lens, seed=5, offset_elems=1)
+    assert K1.data_ptr() % 4 == 2 and torch.equal(K, K1)
+    shape = P.Shape(2, 8, 2, D, 4, cu)
+    for a, b in zip(scores(shape, K, Q), scores(shape, K1, Q1)):
+        assert torch.equal(a, b)
