@@ -248,6 +248,22 @@ __device__ __forceinline__ void tile_operand(const u32x4 *wst, int nt, int lane,
     for (int st = 0; st < G::NCH; ++st) kx[st] = wst[G::pos(16 * nt + (lane & 15), 4 * st + (lane >> 4))];
 }
 
+// Sums over the four 16-lane groups of four values at once: group 0 gets the
+// total of a over the lanes of its column, group 1 of b, group 2 of c and
+// group 3 of d.  Each swap gives both halves of two values to one addition:
+// three swaps and three additions instead of eight lane moves and eight.
+__device__ __forceinline__ float groups_sum4(float a, float b, float c, float d)
+{
+    // lanes 32..63 of the first with lanes 0..31 of the second
+    const auto ac = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(c), false, false);
+    const auto bd = __builtin_amdgcn_permlane32_swap(__float_as_uint(b), __float_as_uint(d), false, false);
+    const float x = __uint_as_float(ac[0]) + __uint_as_float(ac[1]);
+    const float y = __uint_as_float(bd[0]) + __uint_as_float(bd[1]);
+    // the odd 16-lane rows of the first with the even rows of the second
+    const auto xy = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+    return __uint_as_float(xy[0]) + __uint_as_float(xy[1]);
+}
+
 __device__ __forceinline__ float groups_sum(float x)
 {
     x += __shfl_xor(x, 16, kWave);
@@ -510,23 +526,25 @@ __global__ __launch_bounds__(kThreads, 2) void k_rows2(ScoreArgs a)
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
                     att = fmaf(fast::fast_exp2(fmaf(acc[mt][nt][r], sc, -rm[mt][r])), rs[mt][r], att);
-            const float n2 = groups_sum((n2p[0] + n2p[1]) + (n2p[2] + n2p[3]));
-            const float km = groups_sum((kmp[0] + kmp[1]) + (kmp[2] + kmp[3]));
-            const float d2 = groups_sum((d2p[0] + d2p[1]) + (d2p[2] + d2p[3]));
-            att = groups_sum(att);
-            const float dE = BF ? __builtin_amdgcn_sqrtf(d2) : sqrtf(d2);
-            const float cm = BF ? km * __builtin_amdgcn_rsqf(fmaxf(n2, 1e-24f)) : km / fmaxf(sqrtf(n2), 1e-12f);
+            // totals over the four lane groups, one per group: |k - kbar|^2, k.mu,
+            // |k|^2 and the attention of key lane % 16
+            const float t4 = groups_sum4((d2p[0] + d2p[1]) + (d2p[2] + d2p[3]), (kmp[0] + kmp[1]) + (kmp[2] + kmp[3]),
+                                         (n2p[0] + n2p[1]) + (n2p[2] + n2p[3]), att);
+            const float root = BF ? __builtin_amdgcn_sqrtf(t4) : sqrtf(t4);  // group 0: d_E; group 2: |k|
+            const float len = BF ? __builtin_amdgcn_rsqf(fmaxf(t4, 1e-24f)) : fmaxf(root, 1e-12f);
+            const float klen = __shfl(len, 32 + (lane & 15), kWave);
+            const float val = g4 == 0 ? root : g4 == 1 ? (BF ? t4 * klen : t4 / klen) : t4 * inv_r;
             const int gi = key0 + 16 * t + (lane & 15);
-            if (g4 == 0 && gi < T) {
-                dsum += dE;
-                dsq += dE * dE;
-                if (gi < P) {
-                    dmn = fminf(dmn, dE);
-                    dmx = fmaxf(dmx, dE);
+            if (gi < T) {
+                if (g4 != 2) outs[g4 < 2 ? g4 : 2][gi - row_base] = val;
+                if (g4 == 0) {
+                    dsum += val;
+                    dsq += val * val;
+                    if (gi < P) {
+                        dmn = fminf(dmn, val);
+                        dmx = fmaxf(dmx, val);
+                    }
                 }
-                outs[0][gi - row_base] = dE;
-                outs[1][gi - row_base] = cm;
-                outs[2][gi - row_base] = att * inv_r;
             }
         }
     });
