@@ -336,7 +336,10 @@ int ecokv_compact(const void *K, const void *V, int dtype, const ecokv_shape *sh
                   const int32_t *budget, const int32_t *idx, const int32_t *counts,
                   const int32_t *offsets, void *Kc, void *Vc, void *stream);
 
-/* Workspace bytes of ecokv_decode for this shape and max_count (>= 1). */
+/* Workspace bytes of ecokv_decode for this shape and max_count (>= 1): room to
+ * split the rows over the whole device.  ecokv_decode also takes less, down to
+ * one chunk for every 768 rows of max_count, that is L H_q B
+ * ceil(max_count / 768) (D + 2) floats, and then splits into fewer chunks. */
 int ecokv_decode_workspace_size(const ecokv_shape *shape, int32_t max_count, size_t *bytes);
 
 /* Decode attention over the compressed cache: the generation step that reads
@@ -352,7 +355,8 @@ int ecokv_decode_workspace_size(const ecokv_shape *shape, int32_t max_count, siz
  *           the work is split into chunks of rows up to it.  A unit with more
  *           rows gets NaN outputs.
  *   O       [L][H_q][B][D] float32 output;  lse [L][H_q][B] float32, may be NULL
- *   workspace of ecokv_decode_workspace_size bytes, 256-byte aligned.
+ *   workspace of ecokv_decode_workspace_size bytes, 256-byte aligned
+ *           (ECOKV_EWORKSPACE below the least it can do with).
  * Q_dec, Kc and Vc must be 16-byte aligned.  Arithmetic: fp32 accumulation;
  * the softmax is computed online per row chunk and the chunks are merged by
  * their log-sum-exp. */

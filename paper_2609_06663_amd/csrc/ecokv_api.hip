@@ -765,7 +765,7 @@ int ecokv_decode_workspace_size(const ecokv_shape *shape, int32_t max_count, siz
     if (rc) return rc;
     if (!bytes) return fail(ECOKV_EINVAL, "bytes is NULL");
     if (max_count < 1) return fail(ECOKV_EINVAL, "max_count %d < 1", max_count);
-    *bytes = sizeof(float) * (size_t)si.L * si.Hq * si.B * (size_t)ecokv::decode_parts(max_count) * (si.D + 2);
+    *bytes = ecokv::decode_ws_bytes((int64_t)si.L * si.Hkv * si.B, si.G, si.D, max_count, false);
     return ECOKV_OK;
 }
 
@@ -778,9 +778,10 @@ int ecokv_decode(const void *Q_dec, const void *Kc, const void *Vc, int dtype, c
     if (rc) return rc;
     if (dtype != ECOKV_BF16 && dtype != ECOKV_F32) return fail(ECOKV_EUNSUPPORTED, "dtype %d", dtype);
     if (max_count < 1) return fail(ECOKV_EINVAL, "max_count %d < 1", max_count);
-    size_t need = 0;
-    if ((rc = ecokv_decode_workspace_size(shape, max_count, &need))) return rc;
     if (si.L == 0) return ECOKV_OK;
+    // a smaller workspace than ecokv_decode_workspace_size says (one sized for
+    // another max_count, say) will do down to `need`: fewer, longer chunks
+    const size_t need = ecokv::decode_ws_bytes((int64_t)si.L * si.Hkv * si.B, si.G, si.D, max_count, true);
     if (!Q_dec || !Kc || !Vc || !counts || !offsets || !O)
         return fail(ECOKV_EINVAL, "Q_dec, Kc, Vc, counts, offsets and O must be non-NULL");
     if (!workspace) return fail(ECOKV_EINVAL, "workspace is NULL");
@@ -798,7 +799,6 @@ int ecokv_decode(const void *Q_dec, const void *Kc, const void *Vc, int dtype, c
     a.offsets = offsets;
     a.O = O;
     a.lse = lse;
-    a.part = static_cast<float *>(workspace);
     a.L = si.L;
     a.Hq = si.Hq;
     a.Hkv = si.Hkv;
@@ -806,9 +806,9 @@ int ecokv_decode(const void *Q_dec, const void *Kc, const void *Vc, int dtype, c
     a.B = si.B;
     a.D = si.D;
     a.max_count = max_count;
-    a.nparts = ecokv::decode_parts(max_count);
     a.qscale = 1.4426950408889634f / sqrtf((float)si.D);
-    const hipError_t e = ecokv::decode_launch(a, dtype == ECOKV_BF16, static_cast<hipStream_t>(stream));
+    const hipError_t e = ecokv::decode_launch(a, static_cast<char *>(workspace), workspace_bytes, dtype == ECOKV_BF16,
+                                             static_cast<hipStream_t>(stream));
     if (e != hipSuccess) return hip_fail(e, "ecokv_decode launch");
     return ECOKV_OK;
 }

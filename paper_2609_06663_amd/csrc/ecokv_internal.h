@@ -181,15 +181,18 @@ struct DecodeArgs {
     const int32_t *offsets;  // [L][Hkv][B]
     float *O;             // [L][Hq][B][D]
     float *lse;           // [L][Hq][B] or null
-    float *part;          // [L][Hq][B][nparts][D + 2]: max, sum, acc per row chunk
+    float *part;          // [blocks][G][D + 2]: max, sum, acc of each block's rows per query head
+    int2 *tab;            // [U] first block and blocks of each unit (balanced plan)
     int L, Hq, Hkv, G, B, D;
-    int max_count, nparts;  // nparts: chunks per query row in part (decode_parts(max_count))
-    int wave_rows;        // rows per wave; a chunk is the rows of a block's waves
+    int max_count;
+    int plan;             // blocks per chunk of a balanced plan (groups of query heads), 0: fixed chunks
+    int np;               // fixed chunks per unit at most
     float qscale;         // log2(e) / sqrt(D)
 };
-int decode_parts(int max_count);
-// Sets a.nparts and a.wave_rows, then launches the decode and merge kernels.
-hipError_t decode_launch(DecodeArgs a, bool bf16, hipStream_t st);
+// Workspace bytes of a call; with `least`, what it can do with (fixed chunks).
+size_t decode_ws_bytes(int64_t units, int G, int D, int max_count, bool least);
+// Plans within ws_bytes (at least the least) and launches the decode and merge kernels.
+hipError_t decode_launch(DecodeArgs a, char *ws, size_t ws_bytes, bool bf16, hipStream_t st);
 
 // The sweeps of ecokv_sweep.hip (every dtype, head_dim and number of window
 // rows): pass 1 or 2 over blocks of a.rpb1 / a.rpb2 keys, a power of two from

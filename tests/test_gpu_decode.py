@@ -135,3 +135,55 @@ def test_decode_many_units_ragged():
     say(f"224 units, ragged counts up to 6000, {int(counts.sum())} rows")
     O, lse = run(c, L, Hq, Hkv, B, D, "bf16", max_count=6000)
     check(c, O, lse, L, Hq, Hkv, B, D, "bf16")
+
+
+@pytest.mark.parametrize("dtype,D,Hq,Hkv,B,counts,max_count", [
+    # fixed chunks of 32 rows per wave (few units), their edges and one row past
+    ("bf16", 128, 28, 4, 1, [128, 129, 6553, 2049], 6553),
+    ("f32", 128, 14, 2, 1, [1, 4097], 4097),
+    # the balanced plan: one round, two rounds, past two (fixed chunks again); units without rows
+    ("bf16", 128, 28, 4, 4, [4000, 1, 0, 9000, 127, 128, 129, 2500, 16, 17, 640, 1536, 768, 769, 3000, 5], 9000),
+    ("f32", 64, 32, 16, 4, list(range(60, 60 + 64 * 113, 113)), 9001),
+    ("bf16", 64, 8, 8, 8, [6144 + 31 * i for i in range(64)], 12000),
+    ("bf16", 64, 8, 8, 8, [12000 - i for i in range(64)], 12000),
+    # two groups of query heads; one unit more than a plan takes
+    ("bf16", 64, 48, 4, 1, [3000, 20, 900, 1700], 3000),
+    ("f32", 64, 257, 257, 1, [1600 + i % 7 for i in range(257)], 1606),
+])
+def test_decode_plans(dtype, D, Hq, Hkv, B, counts, max_count):
+    """The same outputs however the rows are split: with the workspace that the
+    call asks for and with the least it takes.  Both are sums of the same
+    products, each row's weight rounded a few times: 2e-6 of max |Vc| apart at most."""
+    import ctypes
+    import paper_2609_06663_amd as P
+    from paper_2609_06663_amd import ecokv as E
+    say(f"{dtype} D={D} Hq={Hq} Hkv={Hkv} B={B}: {len(counts)} units of up to {max(counts)} rows, max_count {max_count}")
+    c = make_cache(14, 1, Hq, Hkv, B, D, counts, dtype, kscale=1.5)
+    shape = P.Shape(1, Hq, Hkv, D, 1, [0] + list(np.cumsum([2] * B)))
+    Q, Kc, Vc = dev(c["Q"], dtype), dev(c["Kc"], dtype), dev(c["Vc"], dtype)
+    n = torch.from_numpy(c["counts"].reshape(-1)).cuda()
+    off = torch.from_numpy(c["offsets"].reshape(-1)).cuda()
+    full = P.ecokv_decode_workspace_size(shape, max_count)
+    least = 4 * Hq * B * ((max_count + 767) // 768) * (D + 2)
+    assert full >= least
+    outs = []
+    for size in (full, least):
+        O = torch.full((1, Hq, B, D), -7.0, device="cuda")
+        lse = torch.full((1, Hq, B), -7.0, device="cuda")
+        ws = torch.full((max(size, 256),), 0xAB, dtype=torch.uint8, device="cuda")  # no initial contents needed
+        p = lambda t: ctypes.c_void_p(t.data_ptr())
+        rc = E.lib.ecokv_decode(p(Q), p(Kc), p(Vc), 0 if dtype == "bf16" else 1, ctypes.byref(shape.c), p(n), p(off),
+                                max_count, p(O), p(lse), p(ws), size, None)
+        assert rc == 0
+        torch.cuda.synchronize()
+        outs.append((O.cpu().numpy(), lse.cpu().numpy()))
+    assert E.lib.ecokv_decode(p(Q), p(Kc), p(Vc), 0 if dtype == "bf16" else 1, ctypes.byref(shape.c), p(n), p(off),
+                              max_count, p(O), p(lse), p(ws), least - 1, None) == -2
+    V = np.abs(c["Vc"].astype(np.float32) if dtype == "f32" else (c["Vc"].astype(np.uint32) << 16).view(np.float32)).max()
+    np.testing.assert_allclose(outs[0][0], outs[1][0], atol=2e-6 * V, rtol=0)
+    empty = np.repeat(c["counts"].reshape(Hkv, B), Hq // Hkv, axis=0) == 0  # [Hq][B]
+    assert (outs[0][0][0][empty] == 0).all() and np.isneginf(outs[0][1][0][empty]).all()
+    keep = ~empty
+    np.testing.assert_allclose(outs[0][1][0][keep], outs[1][1][0][keep], atol=1e-5, rtol=1e-6)
+    if not empty.any():
+        check(c, *outs[0], 1, Hq, Hkv, B, D, dtype)
