@@ -151,61 +151,134 @@ __device__ void radix_threshold(const Src &key, int64_t n, int64_t k, uint32_t k
     *need_eq_out = rem;
 }
 
-// radix_threshold for the streaming select of large groups, with the later
-// digits over a gathered list: after the first digit, the keys that keep the
-// chosen prefix (usually a small part of the group) are written to cand (one
-// LDS atomic per wave and load, positions by mbcnt), and the later digits
-// count only them into the first histogram, which the scanning wave reads
-// directly.  If more than cap keys keep the prefix, every digit reads all
-
 // ---------------------------------------------------------------------------
-// Register-resident radix select: thread t holds keys kk[0..KPT) at positions
-// v0 .. v0+KPT-1 of n (positions >= n are not keys).
+// Register-resident radix select: every thread holds KPT keys kk[0..KPT).
 // ---------------------------------------------------------------------------
-// Block-wide min and max of the keys (mm: LDS, 2 x kSelWaves).
-template <int KPT>
-__device__ __forceinline__ void reg_extremes(const uint32_t (&kk)[KPT], int v0, int n, uint32_t (*mm)[kSelWaves],
-                                             uint32_t *kmin_out, uint32_t *kmax_out)
+// Block-wide extremes from each thread's (mm: LDS, 2 x kSelWaves).
+__device__ __forceinline__ void block_extremes(uint32_t lmin, uint32_t lmax, uint32_t (*mm)[kSelWaves],
+                                               uint32_t *kmin_out, uint32_t *kmax_out)
 {
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    uint32_t kmin = 0xffffffffu, kmax = 0u;
-#pragma unroll
-    for (int q = 0; q < KPT; ++q)
-        if (v0 + q < n) {
-            kmin = min(kmin, kk[q]);
-            kmax = max(kmax, kk[q]);
-        }
-    kmin = wave_min_u(kmin);
-    kmax = wave_max_u(kmax);
+    lmin = wave_min_u(lmin);
+    lmax = wave_max_u(lmax);
     if (lane == 0) {
-        mm[0][wv] = kmin;
-        mm[1][wv] = kmax;
+        mm[0][wv] = lmin;
+        mm[1][wv] = lmax;
     }
     __syncthreads();
-    kmin = mm[0][0];
-    kmax = mm[1][0];
+    lmin = mm[0][0];
+    lmax = mm[1][0];
+#pragma unroll
     for (int q = 1; q < kSelWaves; ++q) {
-        kmin = min(kmin, mm[0][q]);
-        kmax = max(kmax, mm[1][q]);
+        lmin = min(lmin, mm[0][q]);
+        lmax = max(lmax, mm[1][q]);
     }
-    *kmin_out = kmin;
-    *kmax_out = kmax;
+    __syncthreads();  // mm is free again
+    *kmin_out = lmin;
+    *kmax_out = lmax;
 }
 
-// The k-th largest key (k >= 1): digits of up to 8 bits below the common
-// prefix of kmin and kmax, one LDS histogram of 256 counters per wave (hist:
-// kSelWaves of them), three barriers per pass (the histograms are cleared by
-// the threads that fold them, and the chosen digit alternates between two
-// slots).  Returns the threshold and how many keys equal to it are taken.
+// Extremes of the n keys, thread t holding keys v0 .. v0+KPT-1; the places at
+// or past n then hold kmin, so that no later pass has to look at n: they rank
+// below every key, or equal the smallest and come after it.
 template <int KPT>
-__device__ __forceinline__ void reg_radix_select(const uint32_t (&kk)[KPT], int v0, int n, int k, uint32_t kmin,
-                                                 uint32_t kmax, uint32_t *hist, uint32_t *hsum,
-                                                 uint32_t (*bc)[2], uint32_t *thr_out, int *need_eq_out)
+__device__ __forceinline__ void reg_extremes(uint32_t (&kk)[KPT], int v0, int n, uint32_t (*mm)[kSelWaves],
+                                             uint32_t *kmin_out, uint32_t *kmax_out)
 {
-    constexpr int HS = 256;
-    constexpr int NH = kSelWaves;
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    uint32_t *const myh = hist + wv * HS;
+    uint32_t lmin = 0xffffffffu, lmax = 0u;
+    if (v0 + KPT <= n) {
+#pragma unroll
+        for (int q = 0; q < KPT; ++q) {
+            lmin = min(lmin, kk[q]);
+            lmax = max(lmax, kk[q]);
+        }
+    } else {
+#pragma unroll
+        for (int q = 0; q < KPT; ++q)
+            if (v0 + q < n) {
+                lmin = min(lmin, kk[q]);
+                lmax = max(lmax, kk[q]);
+            }
+    }
+    block_extremes(lmin, lmax, mm, kmin_out, kmax_out);
+    if (v0 + KPT > n) {
+#pragma unroll
+        for (int q = 0; q < KPT; ++q)
+            if (v0 + q >= n) kk[q] = *kmin_out;
+    }
+}
+
+// Wave 0 (all 64 lanes): the digit of the rem-th largest key from a 256-bin
+// histogram h, counts above it into slot[1], keys in its bin into slot[2]; the
+// bins are zeroed.
+__device__ __forceinline__ void pick_digit(uint32_t *h, int rem, uint32_t *slot)
+{
+    const int lane = threadIdx.x & 63;
+    // lane owns bins 255-4l .. 252-4l (descending digit order)
+    uint32_t c4[4], loc = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        c4[q] = h[255 - 4 * lane - q];
+        h[255 - 4 * lane - q] = 0u;
+        loc += c4[q];
+    }
+    uint32_t inc = wave_incl_scan(loc);
+    const uint32_t before = inc - loc;
+    if ((int)before < rem && rem <= (int)inc) {
+        uint32_t cum = before;
+        for (int q = 0; q < 4; ++q) {
+            if ((int)(cum + c4[q]) >= rem) {
+                slot[0] = 255u - 4u * lane - q;
+                slot[1] = cum;
+                slot[2] = c4[q];
+                break;
+            }
+            cum += c4[q];
+        }
+    }
+}
+
+// The k-th largest of the block's keys, kk[0..KPT) in every thread (extremes
+// kmin, kmax; places without a key hold kmin), for a block whose stage
+// (lds, KPT words per thread) is free during the selection:
+//  * first digit, the 11 bits below the common prefix of kmin and kmax: of
+//    positive floats some 8 bins an octave, where a digit of 8 bits holds
+//    little more than the exponent, most keys sharing a bin or two (a serial
+//    chain of LDS atomics, and a later list of nearly all keys).  kCopies
+//    histograms, by lane, each two banks further on than the one before,
+//    folded and scanned by the whole block;
+//  * then each wave lists its keys that carry the chosen prefix -- usually a
+//    few in a hundred -- in its own part of the stage, and the later digits, 8
+//    bits each, count the lists only, into one histogram (h1) that the
+//    scanning wave reads and clears: two barriers per digit and no fold.
+// Returns the threshold key and how many keys equal to it are taken.  With
+// CLASS, kTakeAll in the place of that number when every key at or above
+// the returned threshold is taken: the digits stop at a bin that is taken
+// whole.
+// Bound by the vector instructions per key of one compute unit: hence no look
+// at n in any pass, one mask for the emission where all of a class is taken,
+// and lists without counting first.  (us, 8-bit first digit, gathered list and
+// n looked at for every key -> now: 4 groups of 32764 keys 23.9 -> 17.3, 112
+// of them 30.1 -> 21.3, 4 of 8184 11.7 -> 8.7; the two stages of 32 groups of
+// 65528, 2040 kept, 15.1 and 17.2 -> 12.6 and 13.6; MAD quantiles of 48 units
+// of up to 29997 35.1 -> 25.1.)
+constexpr int kTakeAll = 0x7fffffff;
+constexpr int kH1Bits = 11;
+constexpr int kH1Bins = 1 << kH1Bits;
+constexpr int kH1Stride = kH1Bins + 2;
+static_assert(kH1Bins == 2 * kSelThreads, "two bins per thread");
+
+template <int KPT, bool CLASS>
+__device__ __forceinline__ void reg_radix_select(const uint32_t (&kk)[KPT], int k, uint32_t kmin, uint32_t kmax,
+                                                 uint32_t *lds, uint32_t *h1, uint32_t *wsum, uint32_t (*bc)[3],
+                                                 uint32_t *thr_out, int *need_eq_out)
+{
+    typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
+    typedef unsigned u32x2_t __attribute__((ext_vector_type(2)));
+    constexpr int kCopies = KPT >= 32 ? 8 : KPT >= 16 ? 4 : 2;
+    static_assert(kCopies * kH1Stride <= KPT * kSelThreads && KPT <= 32 && kCopies * kH1Stride % 4 == 0,
+                  "histograms and lists must fit the stage");
+    const int tid = threadIdx.x, lane = tid & 63, wv = uniform_i32(tid >> 6);
     const uint32_t diff = kmin ^ kmax;
     if (diff == 0) {
         *thr_out = kmin;
@@ -216,57 +289,77 @@ __device__ __forceinline__ void reg_radix_select(const uint32_t (&kk)[KPT], int 
     uint32_t mask = hi == 31 ? 0u : ~((2u << hi) - 1u);
     uint32_t prefix = kmin & mask;
     int rem = k;
-    for (int b = tid; b < NH * HS; b += blockDim.x) hist[b] = 0;
+    for (int b = tid; b < kCopies * kH1Stride / 4; b += kSelThreads)
+        reinterpret_cast<u32x4_t *>(lds)[b] = (u32x4_t){0u, 0u, 0u, 0u};
+    if (tid < 256) h1[tid] = 0u;
     __syncthreads();
-    int par = 0;
-    while (hi >= 0) {
-        const int lo = hi >= 7 ? hi - 7 : 0;
+    {
+        // first digit (every key lies in [kmin, kmax], so all carry the prefix)
+        const int lo = hi >= kH1Bits - 1 ? hi - (kH1Bits - 1) : 0;
         const uint32_t nb = 1u << (hi - lo + 1);
+        uint32_t *const myh = lds + (lane & (kCopies - 1)) * kH1Stride;
 #pragma unroll
-        for (int q = 0; q < KPT; ++q)
-            if (v0 + q < n && (kk[q] & mask) == prefix) atomicAdd(&myh[(kk[q] >> lo) & (nb - 1u)], 1u);
+        for (int q = 0; q < KPT; ++q) atomicAdd(&myh[(kk[q] >> lo) & (nb - 1u)], 1u);
         __syncthreads();
-        if (tid < 256) {
-            uint32_t c = 0;
+        // thread t: bins 2047 - 2t and 2046 - 2t (descending digit order)
+        uint32_t c1 = 0, c0 = 0;
 #pragma unroll
-            for (int w2 = 0; w2 < NH; ++w2) {
-                c += hist[w2 * HS + tid];
-                hist[w2 * HS + tid] = 0;
-            }
-            hsum[tid] = c;
+        for (int c = 0; c < kCopies; ++c) {
+            const u32x2_t v = *reinterpret_cast<const u32x2_t *>(&lds[c * kH1Stride + kH1Bins - 2 - 2 * tid]);
+            c0 += v[0];
+            c1 += v[1];
+        }
+        const uint32_t inc = wave_incl_scan(c1 + c0);
+        if (lane == kWave - 1) wsum[wv] = inc;
+        __syncthreads();
+        uint32_t before = inc - (c1 + c0);
+#pragma unroll
+        for (int w2 = 0; w2 < kSelWaves; ++w2) before += w2 < wv ? wsum[w2] : 0u;
+        if ((int)before < rem && rem <= (int)(before + c1 + c0)) {
+            const bool first = (int)(before + c1) >= rem;
+            bc[0][0] = (uint32_t)(kH1Bins - 1 - 2 * tid - (first ? 0 : 1));
+            bc[0][1] = before + (first ? 0u : c1);
+            bc[0][2] = first ? c1 : c0;
         }
         __syncthreads();
-        if (tid < kWave) {
-            // lane owns bins 255-4l .. 252-4l (descending digit order)
-            uint32_t c4[4], loc = 0;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                c4[q] = hsum[255 - 4 * lane - q];
-                loc += c4[q];
-            }
-            uint32_t inc = wave_incl_scan(loc);
-            const uint32_t before = inc - loc;
-            if ((int)before < rem && rem <= (int)inc) {
-                uint32_t cum = before;
-                for (int q = 0; q < 4; ++q) {
-                    if ((int)(cum + c4[q]) >= rem) {
-                        bc[par][0] = 255u - 4u * lane - q;
-                        bc[par][1] = cum;
-                        break;
-                    }
-                    cum += c4[q];
-                }
-            }
-        }
-        __syncthreads();
-        prefix |= bc[par][0] << lo;
-        rem -= (int)bc[par][1];
+        prefix |= bc[0][0] << lo;
+        rem -= (int)bc[0][1];
         mask |= (nb - 1u) << lo;
         hi = lo - 1;
-        par ^= 1;
+    }
+    bool whole = rem == (int)bc[0][2];
+    if (hi >= 0 && !(CLASS && whole)) {
+        // this wave's keys that carry the prefix (at most all of them: its part holds 64 KPT)
+        uint32_t *const cand = lds + wv * (kWave * KPT);
+        int nw = 0;
+#pragma unroll
+        for (int q = 0; q < KPT; ++q) {
+            const bool m = (kk[q] & mask) == prefix;
+            const uint64_t b = __ballot(m);
+            if (m) cand[nw + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u))] = kk[q];
+            nw += __popcll(b);
+        }
+        int par = 1;
+        while (hi >= 0 && !(CLASS && whole)) {
+            const int lo = hi >= 7 ? hi - 7 : 0;
+            const uint32_t nb = 1u << (hi - lo + 1);
+            for (int i = lane; i < nw; i += kWave) {
+                const uint32_t key = cand[i];
+                if ((key & mask) == prefix) atomicAdd(&h1[(key >> lo) & (nb - 1u)], 1u);
+            }
+            __syncthreads();
+            if (tid < kWave) pick_digit(h1, rem, bc[par]);
+            __syncthreads();
+            prefix |= bc[par][0] << lo;
+            rem -= (int)bc[par][1];
+            whole = rem == (int)bc[par][2];
+            mask |= (nb - 1u) << lo;
+            hi = lo - 1;
+            par ^= 1;
+        }
     }
     *thr_out = prefix;
-    *need_eq_out = rem;
+    *need_eq_out = CLASS && whole ? kTakeAll : rem;
 }
 
 // ---------------------------------------------------------------------------
@@ -373,72 +466,82 @@ __global__ __launch_bounds__(kSelThreads) void k_dquant(DQuantArgs a)
     }
 }
 
-// The q quantile of the keys held in registers (extremes kmin, kmax; mm as
-// in reg_extremes).
+// The q quantile of n keys held in registers (extremes kmin, kmax; places
+// without a key hold kmin).
 template <int KPT>
-__device__ float reg_quantile(const uint32_t (&kk)[KPT], int v0, int n, double q, uint32_t kmin, uint32_t kmax,
-                              uint32_t (*hist)[256], uint32_t *hsum, uint32_t (*bc)[2], uint32_t (*mm)[kSelWaves])
+__device__ float reg_quantile(const uint32_t (&kk)[KPT], int n, double q, uint32_t kmin, uint32_t kmax, uint32_t *lds,
+                              uint32_t *h1, uint32_t *wsum, uint32_t (*bc)[3], uint32_t (*mm)[kSelWaves])
 {
     const double h = q * (double)(n - 1);
     const int j = (int)floor(h);
     uint32_t thr;
     int need_eq;
-    reg_radix_select<KPT>(kk, v0, n, n - j, kmin, kmax, &hist[0][0], hsum, bc, &thr, &need_eq);
+    reg_radix_select<KPT, false>(kk, n - j, kmin, kmax, lds, h1, wsum, bc, &thr, &need_eq);
     const float x = key_value(thr);
     if (j + 1 >= n || need_eq >= 2) return x;  // x_(j+1) = x_(j), or no x_(j+1)
-    uint32_t m = 0xffffffffu;
+    uint32_t m = 0xffffffffu, mx;
 #pragma unroll
     for (int k = 0; k < KPT; ++k)
-        if (v0 + k < n && kk[k] > thr) m = min(m, kk[k]);
-    m = wave_min_u(m);
-    if ((threadIdx.x & 63) == 0) mm[0][threadIdx.x >> 6] = m;
-    __syncthreads();
-    m = mm[0][0];
-    for (int w2 = 1; w2 < kSelWaves; ++w2) m = min(m, mm[0][w2]);
-    __syncthreads();
+        if (kk[k] > thr) m = min(m, kk[k]);
+    block_extremes(m, 0u, mm, &m, &mx);
     return x + (float)(h - (double)j) * (key_value(m) - x);
 }
 
-// Register-resident form for units of at most 32 Ki non-window keys: thread t
-// holds d_E of keys 32t .. 32t+31 for every pass.
+// Register-resident form for units of at most 32 Ki non-window keys: every
+// thread holds 32 of the d_E for every pass, in the order of coalesced 16-byte
+// loads (which key a thread holds makes no difference here).
 constexpr int kDqKeys = 32 * kSelThreads;
 
 __global__ __launch_bounds__(kSelThreads) void k_dquant_reg(DQuantArgs a)
 {
     constexpr int KPT = 32;
-    __shared__ uint32_t hist[kSelWaves][256];
-    __shared__ uint32_t hsum[256];
-    __shared__ uint32_t bc[2][2];
+    typedef float f32x4_t __attribute__((ext_vector_type(4)));
+    __shared__ __attribute__((aligned(16))) uint32_t stg[32 * kSelThreads];  // the radix scratch
+    __shared__ uint32_t h1[256];
+    __shared__ uint32_t bc[2][3];
+    __shared__ uint32_t wsum[kSelWaves];
     __shared__ uint32_t mm[2][kSelWaves];
     const Unit un = unit_of(blockIdx.x, a.Hkv, a.B);
     const int P = a.seq.cu[un.s + 1] - a.seq.cu[un.s] - a.w;  // <= kDqKeys (checked on the host)
     const float *d = a.d + ((int64_t)un.l * a.Hkv + un.h) * a.Ptot + (a.seq.cu[un.s] - (int64_t)un.s * a.w);
-    const int v0 = threadIdx.x * KPT;
+    const int tid = threadIdx.x;
     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<float *>(uniform_ptr(d)), (short)0, uniform_i32(P) * 4, 0x00020000);
-    typedef float f32x4_t __attribute__((ext_vector_type(4)));
     float dv[KPT];
     uint32_t kk[KPT];
 #pragma unroll
     for (int q = 0; q < KPT / 4; ++q) {
-        const f32x4_t x = __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rs, (v0 + 4 * q) * 4, 0, 0));
+        const f32x4_t x =
+            __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rs, (q * kSelThreads + tid) * 16, 0, 0));
 #pragma unroll
         for (int e = 0; e < 4; ++e) dv[4 * q + e] = x[e];
     }
-#pragma unroll
-    for (int q = 0; q < KPT; ++q) kk[q] = score_key(dv[q]);
     uint32_t kmin, kmax;
-    reg_extremes<KPT>(kk, v0, P, mm, &kmin, &kmax);
+    // the keys of |d - c| (with dev) or of d, their extremes, and kmin in the places past P
+    auto make_keys = [&](float c, bool dev) {
+        uint32_t lmin = 0xffffffffu, lmax = 0u;
+#pragma unroll
+        for (int q = 0; q < KPT; ++q) {
+            kk[q] = score_key(dev ? fabsf(dv[q] - c) : dv[q]);
+            if (((q / 4) * kSelThreads + tid) * 4 + q % 4 < P) {
+                lmin = min(lmin, kk[q]);
+                lmax = max(lmax, kk[q]);
+            }
+        }
+        block_extremes(lmin, lmax, mm, &kmin, &kmax);
+#pragma unroll
+        for (int q = 0; q < KPT; ++q)
+            if (((q / 4) * kSelThreads + tid) * 4 + q % 4 >= P) kk[q] = kmin;
+    };
+    make_keys(0.f, false);
     float o0, o1;
     if (a.mode == ECOKV_NORM_WINSOR) {
-        o0 = reg_quantile<KPT>(kk, v0, P, (double)a.q, kmin, kmax, hist, hsum, bc, mm);
-        o1 = reg_quantile<KPT>(kk, v0, P, 1.0 - (double)a.q, kmin, kmax, hist, hsum, bc, mm);
+        o0 = reg_quantile<KPT>(kk, P, (double)a.q, kmin, kmax, stg, h1, wsum, bc, mm);
+        o1 = reg_quantile<KPT>(kk, P, 1.0 - (double)a.q, kmin, kmax, stg, h1, wsum, bc, mm);
     } else {
-        o0 = reg_quantile<KPT>(kk, v0, P, 0.5, kmin, kmax, hist, hsum, bc, mm);  // median
-#pragma unroll
-        for (int q = 0; q < KPT; ++q) kk[q] = score_key(fabsf(dv[q] - o0));
-        reg_extremes<KPT>(kk, v0, P, mm, &kmin, &kmax);
-        o1 = reg_quantile<KPT>(kk, v0, P, 0.5, kmin, kmax, hist, hsum, bc, mm);  // median absolute deviation
+        o0 = reg_quantile<KPT>(kk, P, 0.5, kmin, kmax, stg, h1, wsum, bc, mm);  // median
+        make_keys(o0, true);
+        o1 = reg_quantile<KPT>(kk, P, 0.5, kmin, kmax, stg, h1, wsum, bc, mm);  // median absolute deviation
     }
     if (threadIdx.x == 0) {
         a.out[2 * (int64_t)blockIdx.x] = o0;
@@ -514,199 +617,47 @@ struct GroupView {
 // The selection group of this block: layer l, heads h0 .. h0+nh-1 of
 
 
-// Wave 0 (all 64 lanes): the digit of the rem-th largest key from a 256-bin
-// histogram h, counts above it into slot[1]; with clear, the bins are zeroed.
-__device__ __forceinline__ void pick_digit(uint32_t *h, bool clear, int rem, uint32_t *slot)
-{
-    const int lane = threadIdx.x & 63;
-    // lane owns bins 255-4l .. 252-4l (descending digit order)
-    uint32_t c4[4], loc = 0;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        c4[q] = h[255 - 4 * lane - q];
-        if (clear) h[255 - 4 * lane - q] = 0u;
-        loc += c4[q];
-    }
-    uint32_t inc = wave_incl_scan(loc);
-    const uint32_t before = inc - loc;
-    if ((int)before < rem && rem <= (int)inc) {
-        uint32_t cum = before;
-        for (int q = 0; q < 4; ++q) {
-            if ((int)(cum + c4[q]) >= rem) {
-                slot[0] = 255u - 4u * lane - q;
-                slot[1] = cum;
-                break;
-            }
-            cum += c4[q];
-        }
-    }
-}
-
-// The k-th largest key, as reg_radix_select, for a block whose 128 KiB
-// stage (lds) is free during the selection:
-//  * first digit: four histograms per wave (lane l of wave w counts into
-//    histogram 4 w + l % 4; 257 words apart, so lanes that share a digit hit
-//    different banks), folded by 256 threads;
-//  * then the keys that still carry the chosen prefix -- usually a small part
-//    of the group -- are gathered into the stage (a wave scan of the
-//    per-thread counts and one LDS atomic per wave place them), and the later
-//    digits count only them, into one shared histogram that the scanning wave
-//    reads and clears: two barriers per digit and no fold.  When they do not
-//    fit, the later digits count the registers into that histogram instead.
-constexpr int kStHistC = 4;
-constexpr int kStHistWords = kSelWaves * kStHistC * 257;
-constexpr int kStCandOff = kStHistWords + 256;
-constexpr int kStCandCap = 32 * kSelThreads - kStCandOff;
-
-template <int KPT>
-__device__ __forceinline__ void reg_radix_select_staged(const uint32_t (&kk)[KPT], int v0, int n, int k,
-                                                        uint32_t kmin, uint32_t kmax, uint32_t *lds,
-                                                        uint32_t *hsum, uint32_t (*bc)[2], uint32_t *ccount,
-                                                        uint32_t *thr_out, int *need_eq_out)
-{
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const uint32_t diff = kmin ^ kmax;
-    if (diff == 0) {
-        *thr_out = kmin;
-        *need_eq_out = k;
-        return;
-    }
-    int hi = 31 - __clz(diff);
-    uint32_t mask = hi == 31 ? 0u : ~((2u << hi) - 1u);
-    uint32_t prefix = kmin & mask;
-    int rem = k;
-    uint32_t *const h1 = lds + kStHistWords;
-    uint32_t *const cand = lds + kStCandOff;
-    for (int b = tid; b < kStHistWords + 256; b += blockDim.x) lds[b] = 0u;
-    if (tid == 0) *ccount = 0u;
-    __syncthreads();
-    {
-        // first digit (every key lies in [kmin, kmax], so all carry the prefix)
-        const int lo = hi >= 7 ? hi - 7 : 0;
-        const uint32_t nb = 1u << (hi - lo + 1);
-        uint32_t *const myh = lds + (wv * kStHistC + (lane & (kStHistC - 1))) * 257;
-#pragma unroll
-        for (int q = 0; q < KPT; ++q)
-            if (v0 + q < n) atomicAdd(&myh[(kk[q] >> lo) & (nb - 1u)], 1u);
-        __syncthreads();
-        if (tid < 256) {
-            uint32_t c = 0;
-#pragma unroll 8
-            for (int w2 = 0; w2 < kSelWaves * kStHistC; ++w2) c += lds[w2 * 257 + tid];
-            hsum[tid] = c;
-        }
-        __syncthreads();
-        if (tid < kWave) pick_digit(hsum, false, rem, bc[0]);
-        __syncthreads();
-        prefix |= bc[0][0] << lo;
-        rem -= (int)bc[0][1];
-        mask |= (nb - 1u) << lo;
-        hi = lo - 1;
-    }
-    if (hi >= 0) {
-        // gather the keys that carry the prefix
-        uint32_t cnt = 0;
-#pragma unroll
-        for (int q = 0; q < KPT; ++q) cnt += (v0 + q < n && (kk[q] & mask) == prefix) ? 1u : 0u;
-        uint32_t inc = wave_incl_scan(cnt);
-        const uint32_t wtot = (uint32_t)__builtin_amdgcn_readlane((int)inc, kWave - 1);
-        uint32_t base = 0;
-        if (lane == kWave - 1 && wtot > 0) base = atomicAdd(ccount, wtot);
-        base = (uint32_t)__builtin_amdgcn_readlane((int)base, kWave - 1);
-        uint32_t pos = base + inc - cnt;
-#pragma unroll
-        for (int q = 0; q < KPT; ++q)
-            if (v0 + q < n && (kk[q] & mask) == prefix) {
-                if (pos < (uint32_t)kStCandCap) cand[pos] = kk[q];
-                ++pos;
-            }
-        __syncthreads();
-        const uint32_t ncand = *ccount;
-        const bool use_cand = ncand <= (uint32_t)kStCandCap;
-        int par = 1;
-        while (hi >= 0) {
-            const int lo = hi >= 7 ? hi - 7 : 0;
-            const uint32_t nb = 1u << (hi - lo + 1);
-            if (use_cand) {
-                for (uint32_t i = tid; i < ncand; i += kSelThreads) {
-                    const uint32_t key = cand[i];
-                    if ((key & mask) == prefix) atomicAdd(&h1[(key >> lo) & (nb - 1u)], 1u);
-                }
-            } else {
-#pragma unroll
-                for (int q = 0; q < KPT; ++q)
-                    if (v0 + q < n && (kk[q] & mask) == prefix) atomicAdd(&h1[(kk[q] >> lo) & (nb - 1u)], 1u);
-            }
-            __syncthreads();
-            if (tid < kWave) pick_digit(h1, true, rem, bc[par]);
-            __syncthreads();
-            prefix |= bc[par][0] << lo;
-            rem -= (int)bc[par][1];
-            mask |= (nb - 1u) << lo;
-            hi = lo - 1;
-            par ^= 1;
-        }
-    }
-    *thr_out = prefix;
-    *need_eq_out = rem;
-}
-
-
 // Ordered emission of one head's chosen keys from the registers (thread t
-// holds keys v0 .. v0+KPT-1 of n): bit q of gtm[c] / eqm[c] marks key
-// v0 + 32 c + q above / equal to the threshold; the thread's taken keys go to
-// consecutive slots from the number taken before its run, put(slot, key
-// index); equal keys are taken in key order while fewer than need_eq precede
-// them.
+// holds keys v0 .. v0+KPT-1): the thread's taken keys go to consecutive slots
+// from the number taken before its run, put(slot, key index).  Bit q of a mask
+// marks key v0 + q: at or above the threshold when all of those are taken, else
+// above it, and equal keys in key order while fewer than need_eq precede them.
 template <int KPT, class F>
-__device__ __forceinline__ void emit_ordered(const uint32_t (&kk)[KPT], int v0, int n, uint32_t thr, int need_eq,
+__device__ __forceinline__ void emit_ordered(const uint32_t (&kk)[KPT], int v0, uint32_t thr, int need_eq,
                                              uint32_t *wsum, F &&put)
 {
-    constexpr int NC = (KPT + 31) / 32;      // 32-key words per thread
-    constexpr int QW = KPT < 32 ? KPT : 32;  // keys per word
-    uint32_t gtm[NC], eqm[NC];
-    uint32_t cg = 0, ce = 0;
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-        gtm[c] = 0u;
-        eqm[c] = 0u;
-#pragma unroll
-        for (int q = 0; q < QW; ++q)
-            if (v0 + 32 * c + q < n) {
-                gtm[c] |= kk[32 * c + q] > thr ? 1u << q : 0u;
-                eqm[c] |= kk[32 * c + q] == thr ? 1u << q : 0u;
-            }
-        cg += (uint32_t)__builtin_popcount(gtm[c]);
-        ce += (uint32_t)__builtin_popcount(eqm[c]);
-    }
+    static_assert(KPT <= 32, "one mask per thread");
+    uint32_t take = 0u;
     uint32_t eg, ee, tg, te;
-    block_exscan2(cg, ce, wsum, eg, ee, tg, te);
+    int o;
+    if (need_eq == kTakeAll) {
+#pragma unroll
+        for (int q = 0; q < KPT; ++q) take |= kk[q] >= thr ? 1u << q : 0u;
+        block_exscan2((uint32_t)__builtin_popcount(take), 0u, wsum, eg, ee, tg, te);
+        o = (int)eg;
+    } else {
+        uint32_t eqm = 0u;
+#pragma unroll
+        for (int q = 0; q < KPT; ++q) {
+            take |= kk[q] > thr ? 1u << q : 0u;
+            eqm |= kk[q] == thr ? 1u << q : 0u;
+        }
+        const int ce = __builtin_popcount(eqm);
+        block_exscan2((uint32_t)__builtin_popcount(take), (uint32_t)ce, wsum, eg, ee, tg, te);
+        const int eq_take = min(ce, max(need_eq - (int)ee, 0));
+        for (int r = 0; r < eq_take; ++r) {
+            take |= eqm & (~eqm + 1u);
+            eqm &= eqm - 1u;
+        }
+        o = (int)eg + min((int)ee, need_eq);
+    }
     (void)tg;
     (void)te;
-    const int eq_take = min((int)ce, max(need_eq - (int)ee, 0));
-    uint32_t take[NC];
-#pragma unroll
-    for (int c = 0; c < NC; ++c) take[c] = gtm[c];
-    for (int r = 0; r < eq_take; ++r) {
-        bool done = false;
-#pragma unroll
-        for (int c = 0; c < NC; ++c)
-            if (!done && eqm[c]) {
-                const uint32_t low = eqm[c] & (~eqm[c] + 1u);
-                take[c] |= low;
-                eqm[c] ^= low;
-                done = true;
-            }
+    while (take) {
+        put(o, v0 + __builtin_ctz(take));
+        take &= take - 1u;
+        ++o;
     }
-    int o = (int)eg + min((int)ee, need_eq);
-#pragma unroll
-    for (int c = 0; c < NC; ++c)
-        while (take[c]) {
-            const int q = 32 * c + __builtin_ctz(take[c]);
-            take[c] &= take[c] - 1u;
-            put(o, v0 + q);
-            ++o;
-        }
 }
 
 // ---------------------------------------------------------------------------
@@ -720,20 +671,17 @@ __device__ __forceinline__ void emit_ordered(const uint32_t (&kk)[KPT], int v0, 
 template <int KPT>
 __global__ __launch_bounds__(kSelThreads) void k_select_reg(SelectArgs a)
 {
-    // the radix histograms and the gathered keys live in stg
-    __shared__ uint32_t hsum[256];
-    __shared__ uint32_t bc[2][2];
+    // the radix histograms and the listed keys live in stg
+    __shared__ uint32_t h1[256];
+    __shared__ uint32_t bc[2][3];
     __shared__ uint32_t wsum[2 * kSelWaves + 2];
     __shared__ uint32_t mm[2][kSelWaves];
-    __shared__ uint32_t ccount;
     __shared__ int64_t through[kMaxFlatHeads];
     typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
-    // 128 KiB: with KPT == 32 the stage of the coalesced score load, then of
-    // the radix histograms and gathered keys, then of the output (the
-    // barriers of the extremes and of the radix passes separate the three
-    // uses); with KPT == 64 the radix scratch only
-    __shared__ u32x4_t stg[8 * kSelThreads];
-    static_assert(kStCandCap > 0, "histograms must fit the stage");
+    // With KPT == 32 the stage of the coalesced score load, then of
+    // the radix histograms and listed keys, then of the output (the barriers
+    // of the extremes and of the radix passes separate the three uses)
+    __shared__ u32x4_t stg[KPT * kSelThreads / 4];
 
     const SelGroup grp = sel_group(a, blockIdx.x);
     const int l = grp.l, h0 = grp.h0, s = grp.s, nh = grp.nh;
@@ -765,46 +713,44 @@ __global__ __launch_bounds__(kSelThreads) void k_select_reg(SelectArgs a)
 
     for (int h = tid; h < nh; h += blockDim.x) through[h] = 0;
     uint32_t kk[KPT];
-    bool ext_done = false;  // the extremes are in mm (reduced with the load's barrier)
+    uint32_t kmin = 0u, kmax = 0u;
     if (nh == 1 && KPT == 32) {
         // Coalesced load through LDS: the block reads the group's scores as
-        // consecutive 16-byte pieces (1 KiB per wave instruction) into a
-        // swizzled stage (piece g at g ^ ((g >> 3) & 7)), then each thread takes
-        // its 32 consecutive scores from it.
+        // consecutive 16-byte pieces (1 KiB per wave instruction) and puts their
+        // keys into a swizzled stage (piece g at g ^ ((g >> 3) & 7)), then each
+        // thread takes its 32 consecutive keys from it.
         const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
             const_cast<float *>(uniform_ptr(g.base)), (short)0, uniform_i32(n) * 4, 0x00020000);
         u32x4_t x[KPT / 4];
 #pragma unroll
         for (int q = 0; q < KPT / 4; ++q)
             x[q] = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rs, (q * kSelThreads + tid) * 16, 0, 0));
-        // the extremes of the loaded keys (the same set as the thread's run
-        // after the stage) ride on the stage's barrier
         uint32_t lmin = 0xffffffffu, lmax = 0u;
 #pragma unroll
-        for (int q = 0; q < KPT / 4; ++q)
+        for (int q = 0; q < KPT / 4; ++q) {
+            const int left = n - (q * kSelThreads + tid) * 4;  // keys from this piece on
 #pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if ((q * kSelThreads + tid) * 4 + e < n) {
-                    const uint32_t kv = score_key(__uint_as_float(x[q][e]));
-                    lmin = min(lmin, kv);
-                    lmax = max(lmax, kv);
-                }
-        lmin = wave_min_u(lmin);
-        lmax = wave_max_u(lmax);
-        if (lane == 0) {
-            mm[0][wv] = lmin;
-            mm[1][wv] = lmax;
+            for (int e = 0; e < 4; ++e) {
+                x[q][e] = score_key(__uint_as_float(x[q][e]));
+                lmin = e < left ? min(lmin, x[q][e]) : lmin;
+                lmax = e < left ? max(lmax, x[q][e]) : lmax;
+            }
+            stg[q * kSelThreads + (tid ^ ((tid >> 3) & 7))] = x[q];
         }
-#pragma unroll
-        for (int q = 0; q < KPT / 4; ++q) stg[q * kSelThreads + (tid ^ ((tid >> 3) & 7))] = x[q];
-        lds_barrier();
-        ext_done = true;
+        // (its first barrier orders the stage's writes before the reads below)
+        block_extremes(lmin, lmax, mm, &kmin, &kmax);
 #pragma unroll
         for (int q = 0; q < KPT / 4; ++q) {
             const u32x4_t y = stg[(KPT / 4) * tid + (q ^ (tid & 7))];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) kk[4 * q + e] = score_key(__uint_as_float(y[e]));
+            for (int e = 0; e < 4; ++e) kk[4 * q + e] = y[e];
         }
+        if (v0 + KPT > n) {
+#pragma unroll
+            for (int q = 0; q < KPT; ++q)
+                if (v0 + q >= n) kk[q] = kmin;
+        }
+        __syncthreads();  // the stage is read: the selection clears it
     } else if (nh == 1) {
         const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
             const_cast<float *>(uniform_ptr(g.base)), (short)0, uniform_i32(n) * 4, 0x00020000);
@@ -826,24 +772,13 @@ __global__ __launch_bounds__(kSelThreads) void k_select_reg(SelectArgs a)
     uint32_t thr = 0xffffffffu;
     int need_eq = 0;
     if (k > 0) {
-        uint32_t kmin, kmax;
-        if (ext_done) {
-            kmin = mm[0][0];
-            kmax = mm[1][0];
-            for (int q = 1; q < kSelWaves; ++q) {
-                kmin = min(kmin, mm[0][q]);
-                kmax = max(kmax, mm[1][q]);
-            }
-        } else {
-            reg_extremes<KPT>(kk, v0, n, mm, &kmin, &kmax);
-        }
+        if (nh > 1 || KPT < 32) reg_extremes<KPT>(kk, v0, n, mm, &kmin, &kmax);
         // radix select of the k-th largest key
-        reg_radix_select_staged<KPT>(kk, v0, n, k, kmin, kmax, reinterpret_cast<uint32_t *>(stg), hsum, bc, &ccount,
-                                     &thr, &need_eq);
+        reg_radix_select<KPT, true>(kk, k, kmin, kmax, reinterpret_cast<uint32_t *>(stg), h1, wsum, bc, &thr, &need_eq);
     }
     if (k > 0 && nh == 1) {
         // ordered emission of one head
-        emit_ordered<KPT>(kk, v0, n, thr, need_eq, wsum, [&](int o, int v) {
+        emit_ordered<KPT>(kk, v0, thr, need_eq, wsum, [&](int o, int v) {
             if (staged) ost[o] = (uint32_t)v;
             else out[o] = v;
         });
@@ -931,13 +866,12 @@ __device__ __forceinline__ const float *head_scores(const SelectArgs &a, const S
 
 __global__ __launch_bounds__(kSelThreads) void k_sel_cand(SelectArgs a)
 {
-    __shared__ uint32_t hsum[256];
-    __shared__ uint32_t bc[2][2];
+    __shared__ uint32_t h1[256];
+    __shared__ uint32_t bc[2][3];
     __shared__ uint32_t wsum[2 * kSelWaves + 2];
     __shared__ uint32_t mm[2][kSelWaves];
-    __shared__ uint32_t ccount;
     typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
-    __shared__ u32x4_t stg[8 * kSelThreads];  // the radix scratch
+    __shared__ u32x4_t stg[kCandSlice / 4];  // the radix scratch
     const int gi = blockIdx.x / a.c_slices, j = blockIdx.x - gi * a.c_slices;
     const SelGroup grp = sel_group(a, gi);
     const int T = a.seq.cu[grp.s + 1] - a.seq.cu[grp.s];
@@ -959,8 +893,8 @@ __global__ __launch_bounds__(kSelThreads) void k_sel_cand(SelectArgs a)
     uint32_t kmin, kmax, thr;
     int need_eq;
     reg_extremes<kCandKPT>(kk, v0, n, mm, &kmin, &kmax);
-    reg_radix_select_staged<kCandKPT>(kk, v0, n, min(k, n), kmin, kmax, reinterpret_cast<uint32_t *>(stg), hsum, bc,
-                                      &ccount, &thr, &need_eq);
+    reg_radix_select<kCandKPT, true>(kk, min(k, n), kmin, kmax, reinterpret_cast<uint32_t *>(stg), h1, wsum, bc, &thr,
+                                     &need_eq);
     // the keys through LDS (free again after the selection), so that the
     // emission can write each chosen key beside its position
     uint32_t *kst = reinterpret_cast<uint32_t *>(stg);
@@ -972,7 +906,7 @@ __global__ __launch_bounds__(kSelThreads) void k_sel_cand(SelectArgs a)
     const int64_t cb = (int64_t)gi * a.c_slices * kCandSlice + (int64_t)j * min(k, kCandSlice);
     int32_t *cp = a.c_pos + cb;
     uint32_t *ck = a.c_key + cb;
-    emit_ordered<kCandKPT>(kk, v0, n, thr, need_eq, wsum, [&](int o, int v) {
+    emit_ordered<kCandKPT>(kk, v0, thr, need_eq, wsum, [&](int o, int v) {
         cp[o] = s0 + v;
         ck[o] = kst[v];
     });
@@ -981,13 +915,12 @@ __global__ __launch_bounds__(kSelThreads) void k_sel_cand(SelectArgs a)
 template <int KPT>
 __global__ __launch_bounds__(kSelThreads) void k_sel_final(SelectArgs a)
 {
-    __shared__ uint32_t hsum[256];
-    __shared__ uint32_t bc[2][2];
+    __shared__ uint32_t h1[256];
+    __shared__ uint32_t bc[2][3];
     __shared__ uint32_t wsum[2 * kSelWaves + 2];
     __shared__ uint32_t mm[2][kSelWaves];
-    __shared__ uint32_t ccount;
     typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
-    __shared__ u32x4_t stg[8 * kSelThreads];  // the radix scratch
+    __shared__ u32x4_t stg[KPT * kSelThreads / 4];  // the radix scratch
     const int gi = blockIdx.x;
     const SelGroup grp = sel_group(a, gi);
     const int T = a.seq.cu[grp.s + 1] - a.seq.cu[grp.s];
@@ -1024,9 +957,8 @@ __global__ __launch_bounds__(kSelThreads) void k_sel_final(SelectArgs a)
         uint32_t kmin, kmax, thr;
         int need_eq;
         reg_extremes<KPT>(kk, v0, nc, mm, &kmin, &kmax);
-        reg_radix_select_staged<KPT>(kk, v0, nc, k, kmin, kmax, reinterpret_cast<uint32_t *>(stg), hsum, bc, &ccount,
-                                     &thr, &need_eq);
-        emit_ordered<KPT>(kk, v0, nc, thr, need_eq, wsum, [&](int o, int v) { out[o] = a.c_pos[cb + v]; });
+        reg_radix_select<KPT, true>(kk, k, kmin, kmax, reinterpret_cast<uint32_t *>(stg), h1, wsum, bc, &thr, &need_eq);
+        emit_ordered<KPT>(kk, v0, thr, need_eq, wsum, [&](int o, int v) { out[o] = a.c_pos[cb + v]; });
     }
     // the window, count and offset
     for (int e = tid; e < a.w; e += blockDim.x) out[max(k, 0) + e] = P + e;
@@ -1505,8 +1437,8 @@ hipError_t select_launch(SelectArgs a, char *ws, hipStream_t st)
     }
     if (maxn <= 32 * kSelThreads) {
         // one block per group: for groups this small, one launch beats five
-        // short ones (28-layer stack, 112 groups of 32764 keys: 29 against 46 us;
-        // one layer, 4 groups: 25 against 33 us).  Keys per thread by group
+        // short ones (28-layer stack, 112 groups of 32764 keys: 21 against 46 us;
+        // one layer, 4 groups: 17 against 33 us).  Keys per thread by group
         // size, so that a small group's per-key work spreads over every wave
         if (maxn <= 8 * kSelThreads)
             ECOKV_TIMED("select", st, hipLaunchKernelGGL(k_select_reg<8>, dim3((unsigned)groups), dim3(kSelThreads),
