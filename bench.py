@@ -74,7 +74,7 @@ def stage_of_kernel(kname):
     if not m:
         return None
     # the prefill cache write's forms of sweep 1 and its reduction, and its copies
-    if m.group(1) in ("k_fs1s", "k_reduce1") and ", true>" in kname:
+    if m.group(1) in ("k_fs1s", "k_reduce1") and "true>" in kname:
         return "prefill_sweep" if m.group(1) == "k_fs1s" else "prefill_reduce"
     if m.group(1) == "k_rows_copy":
         return "prefill_copy"

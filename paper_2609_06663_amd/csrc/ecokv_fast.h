@@ -28,6 +28,33 @@ __device__ __forceinline__ int64_t window_row(const ScoreArgs &a, const Unit &un
     return (((int64_t)un.l * a.Hq + (int64_t)un.h * a.G + g) * a.B + un.s) * a.w + j;
 }
 
+// The unit u and the block x of its keys that this block of a sweep takes.
+// The grid holds exactly the blocks that have keys (a.bl): with a place for
+// every block of the longest sequence in every unit, ragged calls end up
+// with unequal numbers of working blocks on the eight XCDs, to which
+// consecutive blocks are dealt in turn.
+struct SweepBlock {
+    Unit un;
+    int u, x;
+};
+__device__ __forceinline__ SweepBlock sweep_block(const ScoreArgs &a)
+{
+    SweepBlock b;
+    const int per = a.bl[a.B], lh = blockIdx.x / per, r = blockIdx.x - lh * per;
+    int s = 0;
+    for (int n = a.B; n > 1;) {  // the last s with bl[s] <= r
+        const int half = n >> 1;
+        if (a.bl[s + half] <= r) s += half;
+        n -= half;
+    }
+    b.un.s = s;
+    b.un.l = lh / a.Hkv;
+    b.un.h = lh - b.un.l * a.Hkv;
+    b.u = lh * a.B + s;
+    b.x = r - a.bl[s];
+    return b;
+}
+
 constexpr float kLog2e = 1.4426950408889634f;
 
 // Combine two softmax partials (max, sum of 2^(x - max)), x in log2 units.
@@ -89,7 +116,7 @@ __device__ __forceinline__ const float *unit_anchors(const ScoreArgs &a, const U
 // records the tag of a call whose wait gave up).
 __device__ __forceinline__ void bump_call_tag(const ScoreArgs &a)
 {
-    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
         const unsigned t = *a.tagw + 1u;
         *a.tagw = t ? t : 1u;
     }

@@ -64,6 +64,7 @@ struct ScoreArgs {
     int rpb1;        // key rows per sweep-1 block
     int nch2;        // sweep-2 blocks per unit (d_E partials in part2)
     int rpb2;        // key rows per sweep-2 block
+    int bl[ECOKV_MAX_SEQS + 1];  // blocks of one (layer, head) pair before each sequence (the sweep being launched)
     float alpha, beta, eps, tau, inv_sqrt_d, lambda_override;
     int use_override, pool_half, causal;
     int vnorm;       // S_imp = pool(a) * |v_i|_2
@@ -195,10 +196,10 @@ size_t decode_ws_bytes(int64_t units, int G, int D, int max_count, bool least);
 hipError_t decode_launch(DecodeArgs a, char *ws, size_t ws_bytes, bool bf16, hipStream_t st);
 
 // The sweeps of ecokv_sweep.hip (every dtype, head_dim and number of window
-// rows): pass 1 or 2 over blocks of a.rpb1 / a.rpb2 keys, a power of two from
-// 128 (bf16: 256) to sweep_rows_max_keys.
+// rows): pass 1 or 2 over blocks of a.rpb1 / a.rpb2 keys, a multiple of 128
+// (bf16: 256) up to sweep_rows_max_keys.
 int sweep_rows_max_keys(bool bf16);
-void sweep_rows_launch(int pass, const ScoreArgs &a, int blocks, hipStream_t st);
+void sweep_rows_launch(int pass, const ScoreArgs &a, unsigned blocks, hipStream_t st);
 
 WsLayout score_ws_layout(int L, int Hkv, int B, int D, int R, int64_t Ptot, int maxT, bool bf16, bool vnorm);
 hipError_t score_launch(ScoreArgs a, char *ws, const WsLayout &lay, int maxT, hipStream_t st, bool bf16);

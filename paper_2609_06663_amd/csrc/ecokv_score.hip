@@ -54,17 +54,18 @@ __device__ __forceinline__ void load_query_operands(const ScoreArgs &a, const Un
 
 // Sweep 2, streaming form (window rows + 2 rows of mu in one 32-row operand,
 // i.e. G*w <= 30): no LDS tile and no barrier in the key loop.  Each wave
-// streams its own 512 keys in groups of 32 from HBM into registers (three
-// groups in flight), re-lays them out through a wave-private LDS stage into
-// MFMA B operands (lane l: key l % 32, 16-byte chunks 2s + l / 32).  The
-// attention of row m is 2^(x - M'_m) with M'_m = M_m + log2(S_m), the
-// normaliser folded into the shift.  2048-key blocks (1024 and 4096 measured
-// no better); 1024- or 512-key blocks when a call has too few keys to fill
-// the device with 2048-key ones (one layer, say).
+// streams a quarter of the block's keys in groups of 32 from HBM into
+// registers (three groups in flight, the first three before the window rows
+// and anchors, so that their latencies overlap), re-lays them out through a
+// wave-private LDS stage into MFMA B operands (lane l: key l % 32, 16-byte
+// chunks 2s + l / 32).  The attention of row m is 2^(x - M'_m) with
+// M'_m = M_m + log2(S_m), the normaliser folded into the shift.  Bound by the
+// key stream and, within a few per cent of it, by the per-key arithmetic at
+// two waves per SIMD.
 constexpr int kS2Waves = 4;
-constexpr int kS2Keys = 2048;       // keys per block
-constexpr int kS2KeysMid = 1024;    // keys per block for calls with fewer blocks
-constexpr int kS2KeysSmall = 512;   // keys per block for calls with few blocks
+constexpr int kS2KeysMin = 256;     // keys per block at least
+constexpr int kS2KeysMax = 2048;    // and at most
+constexpr int kS2KeysCache = 512;   // of the sweep that writes the cache
 
 // Coalesced load of 32 key rows: instruction i covers rows 4i .. 4i+3, lane l
 // chunk l % 16 of row 4i + l / 16 (four whole 256-byte rows per instruction).
@@ -77,28 +78,48 @@ __device__ __forceinline__ void group_load(u32x4 (&b)[8], __amdgpu_buffer_rsrc_t
         b[i] = __builtin_amdgcn_raw_buffer_load_b128(rs, (key0 + 4 * i + (lane >> 4)) * (kD * 2) + (lane & 15) * 16, 0, 2);
 }
 
-template <int KEYS>
 __global__ __launch_bounds__(256, 2) void k_fs2s(ScoreArgs a)
 {
     bump_call_tag(a);
-    constexpr int kS2Groups = KEYS / (32 * kS2Waves);  // 32-key groups per wave
+    const int wave_keys = a.rpb2 / kS2Waves;  // a multiple of 32
     __shared__ float wred[4][kS2Waves];
     __shared__ u32x4 stage[kS2Waves][32 * kChunks];  // per wave: 32 rows, swizzled 16-byte chunks
     __shared__ float wd2[kS2Waves][32];               // per wave: |k - kbar|^2 of its 32 rows
     // the block's per-key outputs (d_E, khat.mu, a), written out once at the end:
     // a few long stores instead of three 128-byte stores per 32 keys, which
     // interleave with the read stream at a high price
-    __shared__ __attribute__((aligned(16))) float outs[3][KEYS];
-    const int u = blockIdx.y;
-    const Unit un = unit_of(u, a.Hkv, a.B);
+    __shared__ __attribute__((aligned(16))) float outs[3][kS2KeysMax];
+    const SweepBlock sb = sweep_block(a);
+    const int u = sb.u;
+    const Unit un = sb.un;
     const int T = a.seq.cu[un.s + 1] - a.seq.cu[un.s];
     const int P = T - a.w;
-    const int row_base = blockIdx.x * KEYS;
-    if (row_base >= T) return;
+    const int row_base = sb.x * a.rpb2;
     const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, kl = lane & 31;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint16_t *krow0 = static_cast<const uint16_t *>(a.K) + unit_row0(a, un) * kD;
     const int64_t obase = unit_out_base(a, un);
+    // this wave's keys [wbase, wbase + wave_keys) only: loads past them read zero, no traffic
+    const int wbase = row_base + wv * wave_keys;
+    const int wkeys = __builtin_amdgcn_readfirstlane(max(0, min(wave_keys, T - wbase)));
+    const __amdgpu_buffer_rsrc_t rs = key_rows_rsrc(krow0 + (int64_t)wbase * kD, wkeys);
+    // Four register buffers in a ring: three groups (24 KiB per wave) stay in
+    // flight while one is used.  Every load is unconditional (the descriptor
+    // zero-fills past the wave's keys), so the outstanding-load count is the
+    // same on every path and each wait covers only the group about to be used.
+    const int ng = (wkeys + 31) >> 5;
+    // Waves start at different groups of their range (rotation rot), so that
+    // at any moment they read different offsets rather than the same offset
+    // of equally sized, equally aligned ranges (which would crowd the same
+    // memory channels).  Slot g >= ng reads past the range: zeros, skipped.
+    const int rot = ng > 0 ? __builtin_amdgcn_readfirstlane(
+                                 (int)(((unsigned)(sb.x * kS2Waves + wv) * 2654435761u + u * 40503u) % (unsigned)ng))
+                           : 0;
+    auto goff = [&](int g) { return g < ng ? 32 * (g + rot < ng ? g + rot : g + rot - ng) : 32 * ng; };
+    u32x4 b0[8], b1[8], b2[8], b3[8];
+    group_load(b0, rs, goff(0), lane);
+    group_load(b1, rs, goff(1), lane);
+    group_load(b2, rs, goff(2), lane);
     __shared__ __attribute__((aligned(16))) float sanc[2 * kD + 2 * ECOKV_MAX_ROWS];
     const float *anc = unit_anchors(a, un, u, T, sanc);
     const float sc = a.inv_sqrt_d * kLog2e;
@@ -133,16 +154,12 @@ __global__ __launch_bounds__(256, 2) void k_fs2s(ScoreArgs a)
         }
     }
 
-    // this wave's keys [wbase, wbase + 32 kS2Groups) only: loads past them read zero, no traffic
-    const int wbase = row_base + wv * (32 * kS2Groups);
-    const int wkeys = __builtin_amdgcn_readfirstlane(max(0, min(32 * kS2Groups, T - wbase)));
-    const __amdgpu_buffer_rsrc_t rs = key_rows_rsrc(krow0 + (int64_t)wbase * kD, wkeys);
     float dsum = 0.f, dsq = 0.f, dmn = INFINITY, dmx = -INFINITY;
     const float inv_r = 1.f / (float)a.R;
 
     u32x4 *wst = stage[wv];
     float *wd = wd2[wv];
-    auto group = [&](const u32x4 (&ld)[8], int key0, bool valid) {
+    auto group = [&](const u32x4 (&ld)[8], int key0) {
         // |k - kbar|^2 in the load layout (lane l: chunk l % 16 of rows 4i + l / 16):
         // the differences in fp32, summed over the lane's 8 dimensions, then
         // over the 16 lanes of a row by DPP; one lane per row parks the sum
@@ -189,7 +206,7 @@ __global__ __launch_bounds__(256, 2) void k_fs2s(ScoreArgs a)
         const float dE = __builtin_amdgcn_sqrtf(wd[kl]);
         const float cm = kmu * __builtin_amdgcn_rsqf(fmaxf(n2, 1e-24f));
         const int gi = key0 + kl;
-        if (valid && h == 0) {
+        if (h == 0) {
             if (gi < T) {
                 dsum += dE;
                 dsq += dE * dE;
@@ -204,37 +221,23 @@ __global__ __launch_bounds__(256, 2) void k_fs2s(ScoreArgs a)
         }
     };
 
-    // Four register buffers in a ring: three groups (24 KiB per wave) stay in
-    // flight while one is used.  Every load is unconditional (the descriptor
-    // zero-fills past the wave's keys), so the outstanding-load count is the
-    // same on every path and each wait covers only the group about to be used.
-    const int ng = (wkeys + 31) >> 5;
-    // Waves start at different groups of their range (rotation rot), so that
-    // at any moment they read different offsets rather than the same offset
-    // of equally sized, equally aligned ranges (which would crowd the same
-    // memory channels).  Slot g >= ng reads past the range: zeros, skipped.
-    const int rot = ng > 0 ? __builtin_amdgcn_readfirstlane(
-                                 (int)(((unsigned)(blockIdx.x * kS2Waves + wv) * 2654435761u + blockIdx.y * 40503u) % (unsigned)ng))
-                           : 0;
-    auto goff = [&](int g) { return g < ng ? 32 * (g + rot < ng ? g + rot : g + rot - ng) : 32 * ng; };
-    u32x4 b0[8], b1[8], b2[8], b3[8];
-    group_load(b0, rs, goff(0), lane);
-    group_load(b1, rs, goff(1), lane);
-    group_load(b2, rs, goff(2), lane);
 #pragma unroll 1
     for (int g = 0; g < ng; g += 4) {
         group_load(b3, rs, goff(g + 3), lane);
         __builtin_amdgcn_sched_barrier(0);  // keep the prefetch ahead of the use
-        group(b0, wbase + goff(g), g < ng);
+        group(b0, wbase + goff(g));
+        if (g + 1 >= ng) break;
         group_load(b0, rs, goff(g + 4), lane);
         __builtin_amdgcn_sched_barrier(0);
-        group(b1, wbase + goff(g + 1), g + 1 < ng);
+        group(b1, wbase + goff(g + 1));
+        if (g + 2 >= ng) break;
         group_load(b1, rs, goff(g + 5), lane);
         __builtin_amdgcn_sched_barrier(0);
-        group(b2, wbase + goff(g + 2), g + 2 < ng);
+        group(b2, wbase + goff(g + 2));
+        if (g + 3 >= ng) break;
         group_load(b2, rs, goff(g + 6), lane);
         __builtin_amdgcn_sched_barrier(0);
-        group(b3, wbase + goff(g + 3), g + 3 < ng);
+        group(b3, wbase + goff(g + 3));
     }
 
     dsum = wave_sum(dsum);
@@ -260,8 +263,7 @@ __global__ __launch_bounds__(256, 2) void k_fs2s(ScoreArgs a)
             // instead of lingering dirty in the caches while K streams in
             // (28-layer stack, sweep 2: default policy 173 us, nt 170, sc1 163;
             // sc0 175, nt + sc1 172)
-#pragma unroll
-            for (int i = 4 * tid; i < KEYS; i += 4 * 256) {
+            for (int i = 4 * tid; i < a.rpb2; i += 4 * 256) {
                 const f32x4v v = *reinterpret_cast<const f32x4v *>(&outs[t][i]);
                 __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), ro, (row_base + i) * 4, 0, 16);
             }
@@ -275,7 +277,7 @@ __global__ __launch_bounds__(256, 2) void k_fs2s(ScoreArgs a)
             mx = fmaxf(mx, wred[2][k]);
             s2 += wred[3][k];
         }
-        float *pp = a.part2 + ((int64_t)u * a.nch2 + blockIdx.x) * 4;
+        float *pp = a.part2 + ((int64_t)u * a.nch2 + sb.x) * 4;
         pp[0] = s;
         pp[1] = mn;
         pp[2] = mx;
@@ -284,7 +286,7 @@ __global__ __launch_bounds__(256, 2) void k_fs2s(ScoreArgs a)
 }
 
 // Sweep 1, streaming form (bf16, head_dim 128, G*w <= 32): like the streaming
-// sweep 2, each wave streams its own 512 keys in 32-key groups (coalesced
+// sweep 2, each wave streams its own keys in 32-key groups (coalesced
 // loads, three register buffers in flight, a wave-private LDS stage) and no
 // barrier is needed until the final merge of the four waves.
 //  * window logits: v_mfma_f32_32x32x16_bf16 with the keys as the A operand and
@@ -302,36 +304,29 @@ constexpr float kRebase1 = 16.f;  // log2 headroom of the lazily moved row refer
 // from the token-major new rows a.Ksrc and the loaded registers are written to
 // the head-major cache a.K on arrival, before the group is used: one read and
 // one write of K, and the sweep rides on them.
-template <int KEYS, bool CACHE>
+template <bool CACHE>
 __global__ __launch_bounds__(256, 2) void k_fs1s(ScoreArgs a)
 {
-    constexpr int kS2Groups = KEYS / (32 * kS2Waves);  // 32-key groups per wave
+    const int wave_keys = a.rpb1 / kS2Waves;  // a multiple of 32
     __shared__ u32x4 stage[kS2Waves][32 * kChunks];
     __shared__ __attribute__((aligned(16))) uint16_t wts[kS2Waves][4][32];  // 1, 1/|k| hi, remainder, 0
     __shared__ float wcs[kS2Waves][2][kD];                                 // per-wave column sums
     __shared__ float wm[kS2Waves][32], wsm[kS2Waves][32];                  // per-wave row max / sum
 
-    const int u = blockIdx.y;
-    const Unit un = unit_of(u, a.Hkv, a.B);
+    const SweepBlock sb = sweep_block(a);
+    const int u = sb.u;
+    const Unit un = sb.un;
     const int T = a.seq.cu[un.s + 1] - a.seq.cu[un.s];
     const int P = T - a.w;
-    const int row_base = blockIdx.x * KEYS;
-    if (row_base >= T) return;
+    const int row_base = sb.x * a.rpb1;
     const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, kl = lane & 31;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint16_t *krow0 = static_cast<const uint16_t *>(a.K) + unit_row0(a, un) * kD;
     const float sc = a.inv_sqrt_d * kLog2e;
     const int lim = a.causal ? P + kl % a.w : T - 1;  // last key visible to window row kl
 
-    bf16x8 aq[1][8];
-    load_query_operands<1>(a, un, lane, aq);
-    if (lane < 32) {
-        wts[wv][0][lane] = 0x3f80;
-        wts[wv][3][lane] = 0;
-    }
-
-    const int wbase = row_base + wv * (32 * kS2Groups);
-    const int wkeys = __builtin_amdgcn_readfirstlane(max(0, min(32 * kS2Groups, T - wbase)));
+    const int wbase = row_base + wv * wave_keys;
+    const int wkeys = __builtin_amdgcn_readfirstlane(max(0, min(wave_keys, T - wbase)));
     // CACHE: key i of the unit at row (l Ttot + cu[s] + i) Hkv + h of the new rows
     const int src_row_bytes = CACHE ? a.Hkv * kD * 2 : kD * 2;
     const __amdgpu_buffer_rsrc_t rs =
@@ -343,6 +338,21 @@ __global__ __launch_bounds__(256, 2) void k_fs1s(ScoreArgs a)
               : key_rows_rsrc(krow0 + (int64_t)wbase * kD, wkeys);
     const __amdgpu_buffer_rsrc_t rdst = key_rows_rsrc(krow0 + (int64_t)wbase * kD, CACHE ? wkeys : 0);
     u32x4 *wst = stage[wv];
+    const int ng = (wkeys + 31) >> 5;
+    const int rot = ng > 0 ? __builtin_amdgcn_readfirstlane(
+                                 (int)(((unsigned)(sb.x * kS2Waves + wv) * 2654435761u + u * 40503u) % (unsigned)ng))
+                           : 0;
+    auto goff = [&](int g) { return g < ng ? 32 * (g + rot < ng ? g + rot : g + rot - ng) : 32 * ng; };
+    u32x4 b0[8], b1[8], b2[8];
+    group_load_rows(b0, rs, goff(0), lane, src_row_bytes);
+    group_load_rows(b1, rs, goff(1), lane, src_row_bytes);
+
+    bf16x8 aq[1][8];
+    load_query_operands<1>(a, un, lane, aq);
+    if (lane < 32) {
+        wts[wv][0][lane] = 0x3f80;
+        wts[wv][3][lane] = 0;
+    }
 
     float ms = -INFINITY, ss = 0.f;  // window row kl over this lane's keys
     typedef float f32x4v __attribute__((ext_vector_type(4)));
@@ -355,7 +365,7 @@ __global__ __launch_bounds__(256, 2) void k_fs1s(ScoreArgs a)
     const int tr_row = 8 * (lane >> 4) + ((lane & 15) >> 2), tr_b = lane & 3;
     const int w_row = (lane & 15) < 3 ? (lane & 15) : 3;
 
-    auto group = [&](const u32x4 (&ld)[8], int key0, bool valid) {
+    auto group = [&](const u32x4 (&ld)[8], int key0) {
         if constexpr (CACHE) group_store(ld, rdst, key0 - wbase, lane);  // (rows past the wave's end are dropped)
 #pragma unroll
         for (int i = 0; i < 8; ++i) wst[sw(4 * i + (lane >> 4), lane & 15)] = ld[i];
@@ -377,7 +387,7 @@ __global__ __launch_bounds__(256, 2) void k_fs1s(ScoreArgs a)
             wts[wv][2][kl] = (uint16_t)bf16_rne(inv - __uint_as_float(hi << 16));
         }
         // softmax statistics of row kl over keys key0 + 8(r/4) + 4h + r%4
-        if (valid) {
+        {
             float x[16];
             float mx = -INFINITY;
             if (key0 + 32 <= P) {
@@ -423,25 +433,19 @@ __global__ __launch_bounds__(256, 2) void k_fs1s(ScoreArgs a)
         }
     };
 
-    const int ng = (wkeys + 31) >> 5;
-    const int rot = ng > 0 ? __builtin_amdgcn_readfirstlane(
-                                 (int)(((unsigned)(blockIdx.x * kS2Waves + wv) * 2654435761u + blockIdx.y * 40503u) % (unsigned)ng))
-                           : 0;
-    auto goff = [&](int g) { return g < ng ? 32 * (g + rot < ng ? g + rot : g + rot - ng) : 32 * ng; };
-    u32x4 b0[8], b1[8], b2[8];
-    group_load_rows(b0, rs, goff(0), lane, src_row_bytes);
-    group_load_rows(b1, rs, goff(1), lane, src_row_bytes);
 #pragma unroll 1
     for (int g = 0; g < ng; g += 3) {
         group_load_rows(b2, rs, goff(g + 2), lane, src_row_bytes);
         __builtin_amdgcn_sched_barrier(0);  // keep the prefetch ahead of the use
-        group(b0, wbase + goff(g), g < ng);
+        group(b0, wbase + goff(g));
+        if (g + 1 >= ng) break;
         group_load_rows(b0, rs, goff(g + 3), lane, src_row_bytes);
         __builtin_amdgcn_sched_barrier(0);
-        group(b1, wbase + goff(g + 1), g + 1 < ng);
+        group(b1, wbase + goff(g + 1));
+        if (g + 2 >= ng) break;
         group_load_rows(b1, rs, goff(g + 4), lane, src_row_bytes);
         __builtin_amdgcn_sched_barrier(0);
-        group(b2, wbase + goff(g + 2), g + 2 < ng);
+        group(b2, wbase + goff(g + 2));
     }
 
     // merge: halves of a row, then the four waves (fixed order)
@@ -462,7 +466,7 @@ __global__ __launch_bounds__(256, 2) void k_fs1s(ScoreArgs a)
     }
     __syncthreads();
     const int stride = 2 * kD + 2 * a.R;
-    float *part = a.part1 + ((int64_t)u * a.nch1 + blockIdx.x) * stride;
+    float *part = a.part1 + ((int64_t)u * a.nch1 + sb.x) * stride;
     for (int i = tid; i < 2 * kD; i += blockDim.x) {
         const int which = i / kD, d = i % kD;
         float s = 0.f;
@@ -1162,6 +1166,40 @@ static int64_t work_blocks(const ScoreArgs &a, int keys)
     return nb * a.L * a.Hkv;
 }
 
+// Fills a.bl for blocks of `keys` keys; returns the grid of the sweep.
+static unsigned sweep_grid(ScoreArgs &a, int keys)
+{
+    a.bl[0] = 0;
+    for (int s = 0; s < a.B; ++s) a.bl[s + 1] = a.bl[s] + (a.seq.cu[s + 1] - a.seq.cu[s] + keys - 1) / keys;
+    return (unsigned)((int64_t)a.bl[a.B] * a.L * a.Hkv);
+}
+
+// Keys per block of the streaming sweeps: a multiple of 128 (whole 32-key
+// groups in every wave) with the least rounds of blocks over the device's
+// places times block length, set-up included: a second round that is nearly
+// empty takes as long as a full one.  (us, 1024-key blocks, 1.2 rounds, ->
+// one round of 1280: 8 packed sequences, 613 Ki keys, sweep 1 39.0 -> 31.3,
+// sweep 2 52.9 -> 37.0; with 1536, 743 Ki keys, 40.1 -> 35.8 and 54.9 -> 42.4.)
+// Calls of two rounds of the longest blocks and more take those (sweep 2 of 28
+// layers of 4 x 32768 keys takes 7 to 15 us longer with 1536, 1792 or 2304 to
+// 3584 keys, of 32 x 65536 keys as long or longer).
+static int stream_block_keys(const ScoreArgs &a)
+{
+    constexpr int64_t kPlaces = 512;  // two blocks per compute unit
+    constexpr int kSetUp = 128;
+    if (work_blocks(a, fast::kS2KeysMax) >= 2 * kPlaces) return fast::kS2KeysMax;
+    int best = 0;
+    int64_t least = INT64_MAX;
+    for (int keys = fast::kS2KeysMax; keys >= fast::kS2KeysMin; keys -= 128) {
+        const int64_t cost = (work_blocks(a, keys) + kPlaces - 1) / kPlaces * (keys + kSetUp);
+        if (cost < least) {
+            least = cost;
+            best = keys;
+        }
+    }
+    return best;
+}
+
 // Keys per block of ecokv_sweep.hip's sweeps: the most that give every
 // compute unit a block.  Longer blocks pay their set-up (window rows,
 // anchors, first loads) and their partial less often, fewer than 256 leave
@@ -1169,11 +1207,18 @@ static int64_t work_blocks(const ScoreArgs &a, int keys)
 // heads x 16384 x 64 bf16 37.5 / 33.8 / 29.5; 14 layers of 4 x 32768 x 128,
 // 56 window rows, 158 / 130 / 128; one layer of 4 x 32768 x 128 14.0 / 18.1 /
 // 29.2; 4 layers of 4 x 8192 x 128 fp32 at 256 / 512 / 1024: 29.6 / 25.1 / 39.8).
-// A wave's quarter is at least one batch of keys: 256 per block for bf16, 128 for fp32.
+// A wave's quarter is whole batches of keys: multiples of 256 per block for
+// bf16, 128 for fp32.  Where the longest blocks leave places of one round (two
+// per compute unit) free, the shortest that still make one round, if more than
+// half as long (12 layers of 4 heads x 16384 x 64 bf16: 384 blocks of 2048 keys
+// -> 480 of 1792, the call 69.8 -> 67.1).
 static int rows_block_keys(const ScoreArgs &a, bool bf16)
 {
-    int keys = sweep_rows_max_keys(bf16);
-    while (keys > (bf16 ? 256 : 128) && work_blocks(a, keys) < 256) keys /= 2;
+    const int step = bf16 ? 256 : 128, most = sweep_rows_max_keys(bf16);
+    int keys = most;
+    while (keys > step && work_blocks(a, keys) < 256) keys /= 2;
+    if (keys == most)
+        for (int k = most - step; k > most / 2 && work_blocks(a, k) <= 512; k -= step) keys = k;
     return keys;
 }
 
@@ -1319,13 +1364,6 @@ hipError_t score_launch(ScoreArgs a, char *ws, const WsLayout &lay, int maxT, hi
     const dim3 grid_e(a.nch3, U);
     hipError_t e;
 
-    // streaming sweeps: 2048-key blocks; 1024-key ones when those would be
-    // fewer than four per compute unit (1024 blocks) and the 1024-key ones at
-    // least two (one layer over 8 sequences of 4k-32k tokens: the pass
-    // 186 -> 174 us against 512-key blocks); else 512-key ones
-    const int sblock = work_blocks(a, fast::kS2Keys) >= 1024  ? fast::kS2Keys
-                       : work_blocks(a, fast::kS2KeysMid) >= 512 ? fast::kS2KeysMid
-                                                              : fast::kS2KeysSmall;
     {
         if (a.pre) {
             // the first sweep's sums come from the caller: K is read once (the
@@ -1333,21 +1371,14 @@ hipError_t score_launch(ScoreArgs a, char *ws, const WsLayout &lay, int maxT, hi
         } else {
             if (score_fast_path(a.D, bf16) && a.R <= 32) {
                 // streaming sweep 1: one 32-row window operand
-                a.rpb1 = sblock;
+                a.rpb1 = stream_block_keys(a);
                 a.nch1 = (maxT + a.rpb1 - 1) / a.rpb1;
-                if (sblock == fast::kS2Keys)
-                    ECOKV_TIMED("sweep1_stream", st,
-                                hipLaunchKernelGGL((fast::k_fs1s<fast::kS2Keys, false>), dim3(a.nch1, U), dim3(256), 0, st, a));
-                else if (sblock == fast::kS2KeysMid)
-                    ECOKV_TIMED("sweep1_stream", st,
-                                hipLaunchKernelGGL((fast::k_fs1s<fast::kS2KeysMid, false>), dim3(a.nch1, U), dim3(256), 0, st, a));
-                else
-                    ECOKV_TIMED("sweep1_stream", st,
-                                hipLaunchKernelGGL((fast::k_fs1s<fast::kS2KeysSmall, false>), dim3(a.nch1, U), dim3(256), 0, st, a));
+                ECOKV_TIMED("sweep1_stream", st,
+                            hipLaunchKernelGGL(fast::k_fs1s<false>, dim3(sweep_grid(a, a.rpb1)), dim3(256), 0, st, a));
             } else {
                 a.rpb1 = rows_block_keys(a, bf16);
                 a.nch1 = (maxT + a.rpb1 - 1) / a.rpb1;
-                ECOKV_TIMED("sweep1_rows", st, sweep_rows_launch(1, a, a.nch1, st));
+                ECOKV_TIMED("sweep1_rows", st, sweep_rows_launch(1, a, sweep_grid(a, a.rpb1), st));
             }
             if ((e = hipGetLastError()) != hipSuccess) return e;
             if (reduce1_lanes(a.nch1) == 4)
@@ -1360,21 +1391,14 @@ hipError_t score_launch(ScoreArgs a, char *ws, const WsLayout &lay, int maxT, hi
         if ((e = hipGetLastError()) != hipSuccess) return e;
         if (score_fast_path(a.D, bf16) && a.R <= kStreamMaxRows) {
             // streaming sweep 2: window rows and the four anchor rows in one operand
-            a.rpb2 = sblock;
+            a.rpb2 = stream_block_keys(a);
             a.nch2 = (maxT + a.rpb2 - 1) / a.rpb2;
-            if (sblock == fast::kS2Keys)
-                ECOKV_TIMED("sweep2_stream", st,
-                            hipLaunchKernelGGL(fast::k_fs2s<fast::kS2Keys>, dim3(a.nch2, U), dim3(256), 0, st, a));
-            else if (sblock == fast::kS2KeysMid)
-                ECOKV_TIMED("sweep2_stream", st,
-                            hipLaunchKernelGGL(fast::k_fs2s<fast::kS2KeysMid>, dim3(a.nch2, U), dim3(256), 0, st, a));
-            else
-                ECOKV_TIMED("sweep2_stream", st,
-                            hipLaunchKernelGGL(fast::k_fs2s<fast::kS2KeysSmall>, dim3(a.nch2, U), dim3(256), 0, st, a));
+            ECOKV_TIMED("sweep2_stream", st,
+                        hipLaunchKernelGGL(fast::k_fs2s, dim3(sweep_grid(a, a.rpb2)), dim3(256), 0, st, a));
         } else {
             a.rpb2 = rows_block_keys(a, bf16);
             a.nch2 = (maxT + a.rpb2 - 1) / a.rpb2;
-            ECOKV_TIMED("sweep2_rows", st, sweep_rows_launch(2, a, a.nch2, st));
+            ECOKV_TIMED("sweep2_rows", st, sweep_rows_launch(2, a, sweep_grid(a, a.rpb2), st));
         }
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
@@ -1521,16 +1545,10 @@ hipError_t prefill_launch(ScoreArgs a, const void *Vsrc, void *Vdst, char *ws, i
         // with the copy takes 326 us with them, as long as a plain copy of the
         // same rows, against 367 us with 2048-key blocks, whose 1792 blocks
         // leave the last of their 3.5 rounds half empty)
-        const int sblock = fast::kS2KeysSmall;
-        a.rpb1 = sblock;
+        a.rpb1 = fast::kS2KeysCache;
         a.nch1 = (maxT + a.rpb1 - 1) / a.rpb1;
-        if (sblock == fast::kS2Keys)
-            ECOKV_TIMED("prefill_sweep", st,
-                        hipLaunchKernelGGL((fast::k_fs1s<fast::kS2Keys, true>), dim3(a.nch1, U), dim3(256), 0, st, a));
-        else
-            ECOKV_TIMED("prefill_sweep", st,
-                        hipLaunchKernelGGL((fast::k_fs1s<fast::kS2KeysSmall, true>), dim3(a.nch1, U), dim3(256), 0, st,
-                                           a));
+        ECOKV_TIMED("prefill_sweep", st,
+                    hipLaunchKernelGGL(fast::k_fs1s<true>, dim3(sweep_grid(a, a.rpb1)), dim3(256), 0, st, a));
     } else {
         // other shapes: copy the rows, then the first sweep over the cache
         ECOKV_TIMED("prefill_copy", st,
@@ -1540,7 +1558,7 @@ hipError_t prefill_launch(ScoreArgs a, const void *Vsrc, void *Vdst, char *ws, i
         if ((e = hipGetLastError()) != hipSuccess) return e;
         a.rpb1 = rows_block_keys(a, bf16);
         a.nch1 = (maxT + a.rpb1 - 1) / a.rpb1;
-        ECOKV_TIMED("prefill_sweep", st, sweep_rows_launch(1, a, a.nch1, st));
+        ECOKV_TIMED("prefill_sweep", st, sweep_rows_launch(1, a, sweep_grid(a, a.rpb1), st));
     }
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (Vsrc) {

@@ -186,7 +186,7 @@ struct Stream {
         wbase = row_base + wv * per;
         wkeys = uniform_i32(max(0, min(per, T - wbase)));
         ng = (wkeys + G::BK - 1) / G::BK;
-        rot = ng > 0 ? uniform_i32((int)(((unsigned)(blockIdx.x * kWaves + wv) * 2654435761u + blockIdx.y * 40503u) %
+        rot = ng > 0 ? uniform_i32((int)(((unsigned)(blockIdx.x * kWaves + wv) * 2654435761u) %
                                          (unsigned)ng))
                      : 0;
         const char *p = uniform_ptr(static_cast<const char *>(a.K) + (unit_row0(a, un) + wbase) * G::RB);
@@ -285,12 +285,12 @@ __global__ __launch_bounds__(kThreads, 2) void k_rows1(ScoreArgs a)
     __shared__ __attribute__((aligned(16))) float wcs[kWaves][2][D];
     __shared__ float wm[kWaves][16 * MT], wsm[kWaves][16 * MT];
 
-    const int u = blockIdx.y;
-    const Unit un = unit_of(u, a.Hkv, a.B);
+    const SweepBlock sb = sweep_block(a);
+    const int u = sb.u;
+    const Unit un = sb.un;
     const int T = a.seq.cu[un.s + 1] - a.seq.cu[un.s];
     const int P = T - a.w;
-    const int row_base = blockIdx.x * a.rpb1;
-    if (row_base >= T) return;
+    const int row_base = sb.x * a.rpb1;
     const int lane = threadIdx.x & 63, wv = uniform_i32(threadIdx.x >> 6);
     const float sc = a.inv_sqrt_d * kLog2e;
     const Stream<BF, D> in(a, un, row_base, a.rpb1, T, wv);
@@ -412,7 +412,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_rows1(ScoreArgs a)
     }
     __syncthreads();
     const int tid = threadIdx.x;
-    float *part = a.part1 + ((int64_t)u * a.nch1 + blockIdx.x) * (2 * D + 2 * a.R);
+    float *part = a.part1 + ((int64_t)u * a.nch1 + sb.x) * (2 * D + 2 * a.R);
     if (tid < 2 * D) {
         float s = 0.f;
 #pragma unroll
@@ -448,12 +448,12 @@ __global__ __launch_bounds__(kThreads, 2) void k_rows2(ScoreArgs a)
     __shared__ __attribute__((aligned(16))) float rows[2][16 * MT];
     __shared__ float wred[4][kWaves];
 
-    const int u = blockIdx.y;
-    const Unit un = unit_of(u, a.Hkv, a.B);
+    const SweepBlock sb = sweep_block(a);
+    const int u = sb.u;
+    const Unit un = sb.un;
     const int T = a.seq.cu[un.s + 1] - a.seq.cu[un.s];
     const int P = T - a.w;
-    const int row_base = blockIdx.x * a.rpb2;
-    if (row_base >= T) return;
+    const int row_base = sb.x * a.rpb2;
     const int tid = threadIdx.x, lane = tid & 63, g4 = lane >> 4, wv = uniform_i32(tid >> 6);
     const int64_t obase = unit_out_base(a, un);
     const float sc = a.inv_sqrt_d * kLog2e, inv_r = 1.f / (float)a.R;
@@ -580,7 +580,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_rows2(ScoreArgs a)
             mx = fmaxf(mx, wred[2][k]);
             s2 += wred[3][k];
         }
-        float *pp = a.part2 + ((int64_t)u * a.nch2 + blockIdx.x) * 4;
+        float *pp = a.part2 + ((int64_t)u * a.nch2 + sb.x) * 4;
         pp[0] = s;
         pp[1] = mn;
         pp[2] = mx;
@@ -607,9 +607,9 @@ static void launch_mt(int pass, const ScoreArgs &a, dim3 grid, hipStream_t st)
 
 int sweep_rows_max_keys(bool bf16) { return bf16 ? rows::Geo<true, 64>::kMaxKeys : rows::Geo<false, 64>::kMaxKeys; }
 
-void sweep_rows_launch(int pass, const ScoreArgs &a, int blocks, hipStream_t st)
+void sweep_rows_launch(int pass, const ScoreArgs &a, unsigned blocks, hipStream_t st)
 {
-    const dim3 grid(blocks, a.L * a.Hkv * a.B);
+    const dim3 grid(blocks);
     if (!a.kbf16) {
         if (a.D == 128) rows::launch_mt<false, 128>(pass, a, grid, st);
         else rows::launch_mt<false, 64>(pass, a, grid, st);
