@@ -11,14 +11,24 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
+// Unit u with its sequence's place.
+__device__ __forceinline__ Unit score_unit(const ScoreArgs &a, int u)
+{
+    Unit un = unit_of(u, a.Hkv, a.B);
+    const SeqSpan q = seq_span(a.seq, a.B, un.s);
+    un.c0 = q.c0;
+    un.T = q.T;
+    return un;
+}
+
 __device__ __forceinline__ int64_t unit_out_base(const ScoreArgs &a, const Unit &un)
 {
-    return ((int64_t)un.l * a.Hkv + un.h) * a.Ptot + (a.seq.cu[un.s] - un.s * a.w);
+    return ((int64_t)un.l * a.Hkv + un.h) * a.Ptot + (un.c0 - un.s * a.w);
 }
 
 __device__ __forceinline__ int64_t unit_row0(const ScoreArgs &a, const Unit &un)
 {
-    return ((int64_t)un.l * a.Hkv + un.h) * a.Ttot + a.seq.cu[un.s];
+    return ((int64_t)un.l * a.Hkv + un.h) * a.Ttot + un.c0;
 }
 
 // Global row index of window row r = (g, j) of unit `un` in Q_win.
@@ -40,18 +50,26 @@ struct SweepBlock {
 __device__ __forceinline__ SweepBlock sweep_block(const ScoreArgs &a)
 {
     SweepBlock b;
-    const int per = a.bl[a.B], lh = blockIdx.x / per, r = blockIdx.x - lh * per;
-    int s = 0;
-    for (int n = a.B; n > 1;) {  // the last s with bl[s] <= r
-        const int half = n >> 1;
-        if (a.bl[s + half] <= r) s += half;
-        n -= half;
+    int lh, s = 0, r;
+    if (a.B == 1) {
+        lh = blockIdx.x / a.bl[1];
+        r = blockIdx.x - lh * a.bl[1];
+        b.x = r;
+    } else {
+        const int per = a.bl[a.B];
+        lh = blockIdx.x / per;
+        r = blockIdx.x - lh * per;
+        for (int n = a.B; n > 1;) {  // the last s with bl[s] <= r
+            const int half = n >> 1;
+            if (a.bl[s + half] <= r) s += half;
+            n -= half;
+        }
+        b.x = r - a.bl[s];
     }
-    b.un.s = s;
-    b.un.l = lh / a.Hkv;
-    b.un.h = lh - b.un.l * a.Hkv;
-    b.u = lh * a.B + s;
-    b.x = r - a.bl[s];
+    const SeqSpan q = seq_span(a.seq, a.B, s);
+    const int l = lh / a.Hkv;
+    b.un = Unit{l, lh - l * a.Hkv, q.s, q.c0, q.T};
+    b.u = lh * a.B + q.s;
     return b;
 }
 

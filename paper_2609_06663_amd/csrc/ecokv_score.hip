@@ -63,7 +63,8 @@ __device__ __forceinline__ void load_query_operands(const ScoreArgs &a, const Un
 // key stream and, within a few per cent of it, by the per-key arithmetic at
 // two waves per SIMD.
 constexpr int kS2Waves = 4;
-constexpr int kS2KeysMin = 256;     // keys per block at least
+constexpr int kS2KeysMin = 512;     // keys per block at least (one layer of 4 x 32768: 256 is no faster in either
+                                    // sweep and doubles the partials, reduce1 4.8 -> 6.4 us)
 constexpr int kS2KeysMax = 2048;    // and at most
 constexpr int kS2KeysCache = 512;   // of the sweep that writes the cache
 
@@ -92,7 +93,7 @@ __global__ __launch_bounds__(256, 2) void k_fs2s(ScoreArgs a)
     const SweepBlock sb = sweep_block(a);
     const int u = sb.u;
     const Unit un = sb.un;
-    const int T = a.seq.cu[un.s + 1] - a.seq.cu[un.s];
+    const int T = un.T;
     const int P = T - a.w;
     const int row_base = sb.x * a.rpb2;
     const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, kl = lane & 31;
@@ -316,7 +317,7 @@ __global__ __launch_bounds__(256, 2) void k_fs1s(ScoreArgs a)
     const SweepBlock sb = sweep_block(a);
     const int u = sb.u;
     const Unit un = sb.un;
-    const int T = a.seq.cu[un.s + 1] - a.seq.cu[un.s];
+    const int T = un.T;
     const int P = T - a.w;
     const int row_base = sb.x * a.rpb1;
     const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, kl = lane & 31;
@@ -332,7 +333,7 @@ __global__ __launch_bounds__(256, 2) void k_fs1s(ScoreArgs a)
     const __amdgpu_buffer_rsrc_t rs =
         CACHE ? __builtin_amdgcn_make_buffer_rsrc(
                     const_cast<uint16_t *>(uniform_ptr(static_cast<const uint16_t *>(a.Ksrc) +
-                                                       (((int64_t)un.l * a.Ttot + a.seq.cu[un.s] + wbase) * a.Hkv +
+                                                       (((int64_t)un.l * a.Ttot + un.c0 + wbase) * a.Hkv +
                                                         un.h) * kD)),
                     (short)0, wkeys * src_row_bytes, 0x00020000)
               : key_rows_rsrc(krow0 + (int64_t)wbase * kD, wkeys);
@@ -517,8 +518,8 @@ __device__ __forceinline__ float lane_group_reduce(float x, Op op)
 template <int LANES, bool PRE>
 __device__ __forceinline__ void reduce1_columns(const ScoreArgs &a, int u, int cg, int ncg)
 {
-    const Unit un = unit_of(u, a.Hkv, a.B);
-    const int T = a.seq.cu[un.s + 1] - a.seq.cu[un.s];
+    const Unit un = score_unit(a, u);
+    const int T = un.T;
     const int nb = (T + a.rpb1 - 1) / a.rpb1;
     const int stride = 2 * a.D + 2 * a.R;
     const float *p = a.part1 + (int64_t)u * a.nch1 * stride;
@@ -775,8 +776,8 @@ __global__ __launch_bounds__(kEpiThreads) void k_epi1(ScoreArgs a)
 {
     __shared__ Red4 lds[kEpiThreads / kWave];
     const int u = blockIdx.y;
-    const Unit un = unit_of(u, a.Hkv, a.B);
-    const int T = a.seq.cu[un.s + 1] - a.seq.cu[un.s];
+    const Unit un = score_unit(a, u);
+    const int T = un.T;
     const int P = T - a.w;
     const int i0 = blockIdx.x * kEpiKeys;
     if (i0 >= P) return;
@@ -817,8 +818,8 @@ __global__ __launch_bounds__(kEpiThreads) void k_epi2(ScoreArgs a)
 {
     __shared__ Red4 lds[kEpiThreads / kWave];
     const int u = blockIdx.y;
-    const Unit un = unit_of(u, a.Hkv, a.B);
-    const int T = a.seq.cu[un.s + 1] - a.seq.cu[un.s];
+    const Unit un = score_unit(a, u);
+    const int T = un.T;
     const int P = T - a.w;
     const int i0 = blockIdx.x * kEpiKeys;
     if (i0 >= P) return;
@@ -965,8 +966,8 @@ __global__ __launch_bounds__(kUThreads) void k_epi_unit(ScoreArgs a)
     __shared__ f32x4 svl[kVec][kUThreads];  // S_div of every thread's keys
     __shared__ f32x4 edge[kUW][2];          // per wave: its first and last four attention values
     const int u = blockIdx.x / SPLIT, part = blockIdx.x % SPLIT;
-    const Unit un = unit_of(u, a.Hkv, a.B);
-    const int T = a.seq.cu[un.s + 1] - a.seq.cu[un.s];
+    const Unit un = score_unit(a, u);
+    const int T = un.T;
     const int P = T - a.w;
     const int64_t ob = unit_out_base(a, un);
 
@@ -1240,8 +1241,8 @@ __global__ __launch_bounds__(kVnThreads) void k_vnorm(ScoreArgs a)
     __shared__ float n2s[kVnThreads];
     constexpr int kRowBytes = SEGS * 16;
     const int u = blockIdx.y;
-    const Unit un = unit_of(u, a.Hkv, a.B);
-    const int T = a.seq.cu[un.s + 1] - a.seq.cu[un.s];
+    const Unit un = score_unit(a, u);
+    const int T = un.T;
     const int P = T - a.w;
     const int row0 = blockIdx.x * kVnThreads;
     if (row0 >= P) return;

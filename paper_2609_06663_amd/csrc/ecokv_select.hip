@@ -22,36 +22,39 @@ constexpr int kMaxFlatHeads = 256;
 // s, min(budget, T_s) entries per head, first entry at out_base.
 struct SelGroup {
     int l, h0, s, nh, beff;
+    int c0, T;  // the sequence's first token and its tokens
     int64_t out_base;
 };
 __device__ __forceinline__ SelGroup sel_group(const SelectArgs &a, int gi)
 {
     SelGroup g;
+    const int j = a.B == 1 ? gi : gi / a.B;
+    const SeqSpan q = seq_span(a.seq, a.B, gi - j * a.B);
+    g.s = q.s;
+    g.c0 = q.c0;
+    g.T = q.T;
     if (a.heads) {
         // one unit per group, (layer, head) pair lh0 + j of the launch's table
-        const int j = gi / a.B;
-        g.s = gi - j * a.B;
         const int lh = a.lht.lh0 + j;
         g.l = lh / a.Hkv;
         g.h0 = lh - g.l * a.Hkv;
         g.nh = 1;
-        g.beff = min(a.lht.b[j], a.seq.cu[g.s + 1] - a.seq.cu[g.s]);
+        g.beff = min(a.lht.b[j], g.T);
         g.out_base = a.lht.start[j] + lh_seq_offset(a.lht, a.seq, j, g.s);
-    } else if (a.flat) {
-        g.l = gi / a.B;
-        g.s = gi % a.B;
+        return g;
+    }
+    const int boff = a.B == 1 ? 0 : a.seq.boff[g.s];
+    g.beff = a.B == 1 ? a.seq.beff[0] : a.seq.beff[g.s];
+    if (a.flat) {
+        g.l = j;
         g.h0 = 0;
         g.nh = a.Hkv;
-        g.beff = a.seq.beff[g.s];
-        g.out_base = (int64_t)g.l * a.Hkv * a.per_lh + (int64_t)a.Hkv * a.seq.boff[g.s];
+        g.out_base = (int64_t)j * a.Hkv * a.per_lh + (int64_t)a.Hkv * boff;
     } else {
-        const Unit un = unit_of(gi, a.Hkv, a.B);
-        g.l = un.l;
-        g.s = un.s;
-        g.h0 = un.h;
+        g.l = j / a.Hkv;
+        g.h0 = j - g.l * a.Hkv;
         g.nh = 1;
-        g.beff = a.seq.beff[g.s];
-        g.out_base = ((int64_t)g.l * a.Hkv + g.h0) * a.per_lh + a.seq.boff[g.s];
+        g.out_base = (int64_t)j * a.per_lh + boff;
     }
     return g;
 }
@@ -258,8 +261,8 @@ __device__ __forceinline__ void pick_digit(uint32_t *h, int rem, uint32_t *slot)
 // Bound by the vector instructions per key of one compute unit: hence no look
 // at n in any pass, one mask for the emission where all of a class is taken,
 // and lists without counting first.  (us, 8-bit first digit, gathered list and
-// n looked at for every key -> now: 4 groups of 32764 keys 23.9 -> 17.3, 112
-// of them 30.1 -> 21.3, 4 of 8184 11.7 -> 8.7; the two stages of 32 groups of
+// n looked at for every key -> now: 4 groups of 32764 keys 23.9 -> 15.5, 112
+// of them 30.1 -> 20.1, 4 of 8184 11.7 -> 8.7; the two stages of 32 groups of
 // 65528, 2040 kept, 15.1 and 17.2 -> 12.6 and 13.6; MAD quantiles of 48 units
 // of up to 29997 35.1 -> 25.1.)
 constexpr int kTakeAll = 0x7fffffff;
@@ -685,7 +688,7 @@ __global__ __launch_bounds__(kSelThreads) void k_select_reg(SelectArgs a)
 
     const SelGroup grp = sel_group(a, blockIdx.x);
     const int l = grp.l, h0 = grp.h0, s = grp.s, nh = grp.nh;
-    const int T = a.seq.cu[s + 1] - a.seq.cu[s];
+    const int T = grp.T;
     const int P = T - a.w;
     const int beff = grp.beff;
     const int64_t out_base = grp.out_base;
@@ -703,7 +706,7 @@ __global__ __launch_bounds__(kSelThreads) void k_select_reg(SelectArgs a)
     }
 
     GroupView g;
-    g.base = a.scores + ((int64_t)l * a.Hkv + h0) * a.Ptot + (a.seq.cu[s] - s * a.w);
+    g.base = a.scores + ((int64_t)l * a.Hkv + h0) * a.Ptot + (grp.c0 - s * a.w);
     g.hstride = a.Ptot;
     g.P = P;
     g.nh = nh;
@@ -730,10 +733,19 @@ __global__ __launch_bounds__(kSelThreads) void k_select_reg(SelectArgs a)
         for (int q = 0; q < KPT / 4; ++q) {
             const int left = n - (q * kSelThreads + tid) * 4;  // keys from this piece on
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                x[q][e] = score_key(__uint_as_float(x[q][e]));
-                lmin = e < left ? min(lmin, x[q][e]) : lmin;
-                lmax = e < left ? max(lmax, x[q][e]) : lmax;
+            for (int e = 0; e < 4; ++e) x[q][e] = score_key(__uint_as_float(x[q][e]));
+            if (left >= 4) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    lmin = min(lmin, x[q][e]);
+                    lmax = max(lmax, x[q][e]);
+                }
+            } else {
+#pragma unroll
+                for (int e = 0; e < 3; ++e) {
+                    lmin = e < left ? min(lmin, x[q][e]) : lmin;
+                    lmax = e < left ? max(lmax, x[q][e]) : lmax;
+                }
             }
             stg[q * kSelThreads + (tid ^ ((tid >> 3) & 7))] = x[q];
         }
@@ -861,7 +873,7 @@ constexpr int kCandSlice = kCandKPT * kSelThreads;  // 8192 keys
 // The scores of single-head group grp.
 __device__ __forceinline__ const float *head_scores(const SelectArgs &a, const SelGroup &grp)
 {
-    return a.scores + ((int64_t)grp.l * a.Hkv + grp.h0) * a.Ptot + (a.seq.cu[grp.s] - grp.s * a.w);
+    return a.scores + ((int64_t)grp.l * a.Hkv + grp.h0) * a.Ptot + (grp.c0 - grp.s * a.w);
 }
 
 __global__ __launch_bounds__(kSelThreads) void k_sel_cand(SelectArgs a)
@@ -874,7 +886,7 @@ __global__ __launch_bounds__(kSelThreads) void k_sel_cand(SelectArgs a)
     __shared__ u32x4_t stg[kCandSlice / 4];  // the radix scratch
     const int gi = blockIdx.x / a.c_slices, j = blockIdx.x - gi * a.c_slices;
     const SelGroup grp = sel_group(a, gi);
-    const int T = a.seq.cu[grp.s + 1] - a.seq.cu[grp.s];
+    const int T = grp.T;
     const int P = T - a.w;
     const int k = grp.beff - a.w;
     const int s0 = j * kCandSlice;
@@ -923,7 +935,7 @@ __global__ __launch_bounds__(kSelThreads) void k_sel_final(SelectArgs a)
     __shared__ u32x4_t stg[KPT * kSelThreads / 4];  // the radix scratch
     const int gi = blockIdx.x;
     const SelGroup grp = sel_group(a, gi);
-    const int T = a.seq.cu[grp.s + 1] - a.seq.cu[grp.s];
+    const int T = grp.T;
     const int P = T - a.w;
     int32_t *out = a.idx + grp.out_base;
     const int tid = threadIdx.x;
@@ -1011,11 +1023,11 @@ __device__ __forceinline__ MbGroup mb_group(const SelectArgs &a, int gi)
 {
     MbGroup g;
     g.sg = sel_group(a, gi);
-    g.T = a.seq.cu[g.sg.s + 1] - a.seq.cu[g.sg.s];
+    g.T = g.sg.T;
     g.P = g.T - a.w;
     g.n = (int64_t)g.sg.nh * g.P;
     g.k = (int64_t)g.sg.nh * (g.sg.beff - a.w);
-    g.base = a.scores + ((int64_t)g.sg.l * a.Hkv + g.sg.h0) * a.Ptot + (a.seq.cu[g.sg.s] - g.sg.s * a.w);
+    g.base = a.scores + ((int64_t)g.sg.l * a.Hkv + g.sg.h0) * a.Ptot + (g.sg.c0 - g.sg.s * a.w);
     g.hstride = a.Ptot;
     // bytes from base to the end of the last head's scores (< 2^31, checked on the host)
     const int bytes = (int)(((int64_t)(g.sg.nh - 1) * g.hstride + g.P) * 4);
@@ -1031,7 +1043,8 @@ typedef float f32x4s __attribute__((ext_vector_type(4)));
 template <int KPT>
 __device__ __forceinline__ void mb_load(const MbGroup &g, int64_t r0, uint32_t (&kk)[KPT], int &h0, int &i0)
 {
-    int h = g.sg.nh == 1 ? 0 : (int)(r0 / g.P);
+    // (in 32 bits: a group's scores span less than 2^31 bytes, checked on the host)
+    int h = g.sg.nh == 1 ? 0 : (int)((uint32_t)r0 / (uint32_t)g.P);
     int i = (int)(r0 - (int64_t)h * g.P);
     h0 = h;
     i0 = i;
@@ -1437,8 +1450,8 @@ hipError_t select_launch(SelectArgs a, char *ws, hipStream_t st)
     }
     if (maxn <= 32 * kSelThreads) {
         // one block per group: for groups this small, one launch beats five
-        // short ones (28-layer stack, 112 groups of 32764 keys: 21 against 46 us;
-        // one layer, 4 groups: 17 against 33 us).  Keys per thread by group
+        // short ones (28-layer stack, 112 groups of 32764 keys: 20 against 46 us;
+        // one layer, 4 groups: 15.5 against 33 us).  Keys per thread by group
         // size, so that a small group's per-key work spreads over every wave
         if (maxn <= 8 * kSelThreads)
             ECOKV_TIMED("select", st, hipLaunchKernelGGL(k_select_reg<8>, dim3((unsigned)groups), dim3(kSelThreads),

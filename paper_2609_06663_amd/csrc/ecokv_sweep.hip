@@ -288,7 +288,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_rows1(ScoreArgs a)
     const SweepBlock sb = sweep_block(a);
     const int u = sb.u;
     const Unit un = sb.un;
-    const int T = a.seq.cu[un.s + 1] - a.seq.cu[un.s];
+    const int T = un.T;
     const int P = T - a.w;
     const int row_base = sb.x * a.rpb1;
     const int lane = threadIdx.x & 63, wv = uniform_i32(threadIdx.x >> 6);
@@ -451,7 +451,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_rows2(ScoreArgs a)
     const SweepBlock sb = sweep_block(a);
     const int u = sb.u;
     const Unit un = sb.un;
-    const int T = a.seq.cu[un.s + 1] - a.seq.cu[un.s];
+    const int T = un.T;
     const int P = T - a.w;
     const int row_base = sb.x * a.rpb2;
     const int tid = threadIdx.x, lane = tid & 63, g4 = lane >> 4, wv = uniform_i32(tid >> 6);

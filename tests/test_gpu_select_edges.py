@@ -25,8 +25,10 @@ def _need_gpu():
 def scores(kind, n, rng):
     if kind == "octave":  # one exponent: the first digit spreads it
         return (1.0 + rng.random(n)).astype(np.float32)
-    if kind == "wide":  # both signs, many octaves, infinities
+    if kind == "wide":  # both signs, many octaves, subnormal numbers, infinities
         s = (np.exp(rng.uniform(-60, 60, n)) * rng.choice([-1.0, 1.0], n)).astype(np.float32)
+        i = rng.integers(0, n, max(1, n // 3))
+        s[i] = (rng.integers(-9, 10, i.size) * 1e-42).astype(np.float32)
         s[rng.integers(0, n, max(1, n // 50))] = np.inf
         s[rng.integers(0, n, max(1, n // 50))] = -np.inf
         return s

@@ -23,7 +23,7 @@ def _need_gpu():
 
 
 @pytest.mark.parametrize("L,Hkv,lens", [
-    (1, 4, [40001]),             # about 313 keys for each of 512 blocks
+    (1, 4, [40001]),             # about 313 keys for each of 512 blocks: 512-key blocks
     (1, 4, [61003, 33]),         # 480
     (1, 8, [39999, 257, 4097]),  # 695
     (2, 8, [36001, 5]),          # 1126
