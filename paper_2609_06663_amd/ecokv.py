@@ -156,7 +156,7 @@ def _ptr(t: Optional[torch.Tensor]):
         return None
     if not t.is_contiguous():
         raise ValueError("tensors passed to libecokv must be contiguous")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 _ELEM = {torch.bfloat16: "bf16", torch.float32: "float32", torch.int32: "int32", torch.uint8: "uint8"}
@@ -171,6 +171,10 @@ def _arg(t: Optional[torch.Tensor], name: str, dtypes, numel: int, device, optio
         if optional:
             return None
         raise ValueError(f"{name} is required")
+    # (one test for a call in order; what is wrong with another is told apart below)
+    if (isinstance(t, torch.Tensor) and t.is_cuda and t.dtype in dtypes and t.numel() >= numel and t.is_contiguous()
+            and (device is None or t.device == device)):
+        return t.data_ptr()
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{name} must be a torch tensor")
     if not t.is_cuda:
@@ -210,15 +214,21 @@ def _dtype_code(t: torch.Tensor) -> int:
     raise TypeError(f"unsupported element type {t.dtype} (bf16 or fp32)")
 
 
-def _stream(stream) -> ctypes.c_void_p:
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+def _stream(stream) -> int:
+    if stream is not None:
+        return stream.cuda_stream
+    if torch.cuda.is_initialized():
+        # the current stream's handle alone: the Stream object of
+        # torch.cuda.current_stream() costs a quarter of a short call's host work
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return torch.cuda.current_stream().cuda_stream
 
 
 def _flat_ints(x) -> list:
     if hasattr(x, "reshape"):  # numpy array or tensor
         x = x.reshape(-1).tolist()
+    if isinstance(x, (list, tuple)) and all(type(v) is int for v in x):
+        return list(x)
     out = []
     for v in x:
         if isinstance(v, (list, tuple)):
@@ -387,9 +397,12 @@ def ecokv_index_count(shape: Shape, budget: Sequence[int]) -> int:
 
 
 def ecokv_index_count_mode(shape: Shape, mode: int, budget) -> int:
+    return _index_count(shape, mode, _budget(shape, budget, mode))
+
+
+def _index_count(shape: Shape, mode: int, bud) -> int:
     n = ctypes.c_int64(0)
-    _check(lib.ecokv_index_count_mode(ctypes.byref(shape.c), int(mode), _budget(shape, budget, mode),
-                                      ctypes.byref(n)))
+    _check(lib.ecokv_index_count_mode(ctypes.byref(shape.c), int(mode), bud, ctypes.byref(n)))
     return n.value
 
 
@@ -416,7 +429,7 @@ def ecokv_select(scores: torch.Tensor, shape: Shape, mode: int, budget, idx: tor
                                 _ptr(offsets), _ptr(workspace), 0 if workspace is None else workspace.numel(),
                                 _stream(stream)))
         return
-    n = ecokv_index_count_mode(shape, mode, budget)
+    n = _index_count(shape, mode, bud)
     dev = scores.device if isinstance(scores, torch.Tensor) else None
     flat = int(mode) == LAYER_FLAT
     sp_ = _arg(scores, "scores", _F32, shape.score_numel(), dev)
@@ -439,7 +452,7 @@ def ecokv_compact(K: torch.Tensor, V: torch.Tensor, shape: Shape, mode: int, bud
         _check(lib.ecokv_compact(_ptr(K), _ptr(V), _dtype_code(K), ctypes.byref(shape.c), int(mode), bud,
                                  _ptr(idx), _ptr(counts), _ptr(offsets), _ptr(Kc), _ptr(Vc), _stream(stream)))
         return
-    n = ecokv_index_count_mode(shape, mode, budget)
+    n = _index_count(shape, mode, bud)
     dev = K.device
     flat = int(mode) == LAYER_FLAT
     D = shape.c.head_dim
