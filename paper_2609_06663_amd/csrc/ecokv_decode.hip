@@ -248,8 +248,7 @@ __global__ __launch_bounds__(kDecThreads, BF ? 3 : 2) void k_decode(DecodeArgs a
             x[r] = b0 + 4 * kg + r < nrows ? cc[r] * a.qscale : -INFINITY;
             mb = fmaxf(mb, x[r]);
         }
-        mb = fmaxf(mb, __shfl_xor(mb, 16, kWave));
-        mb = fmaxf(mb, __shfl_xor(mb, 32, kWave));  // finite: row b0 is valid
+        mb = across32(across16(mb, OpMax{}), OpMax{});  // finite: row b0 is valid
         const bool move = mb > m + kDecRebase;      // (always in the first tile: m = -inf)
         if (__builtin_amdgcn_ballot_w64(move)) {
             const float nm = move ? mb : m;
@@ -302,21 +301,29 @@ __global__ __launch_bounds__(kDecThreads, BF ? 3 : 2) void k_decode(DecodeArgs a
         tile(kb, vb, b0 + BR);
     }
 
-    // P.V: add the row groups of the V layout; sums: add the four lane groups
+    // P.V: add the row groups of the V layout (64 / S of them), each fold
+    // leaving half of the elements in either half of the lanes, so that all
+    // lanes end with EW elements of their segment; sums: add the four lane groups
+    constexpr int EW = S <= 16 ? EL / 4 : EL / 2;
+    const int e0 = (lane >= 32 ? EL / 2 : 0) + (S <= 16 && (lane & 16) ? EL / 4 : 0);
 #pragma unroll
-    for (int g = 0; g < QG; ++g)
+    for (int g = 0; g < QG; ++g) {
+        if constexpr (S == 8) {
 #pragma unroll
-        for (int msk = S; msk < kWave; msk <<= 1)
+            for (int e = 0; e < EL; ++e) acc[g][e] += dpp_row<0x128>(acc[g][e]);  // row_ror:8, lane ^ 8
+        }
 #pragma unroll
-            for (int e = 0; e < EL; ++e) acc[g][e] += __shfl_xor(acc[g][e], msk, kWave);
-    ls += __shfl_xor(ls, 16, kWave);
-    ls += __shfl_xor(ls, 32, kWave);
-    if (lane < S) {
+        for (int e = 0; e < EL / 2; ++e) acc[g][e] = fold32(acc[g][e], acc[g][e + EL / 2]);
+        if constexpr (S <= 16) {
 #pragma unroll
-        for (int g = 0; g < QG; ++g)
+            for (int e = 0; e < EL / 4; ++e) acc[g][e] = fold16(acc[g][e], acc[g][e + EL / 4]);
+        }
+        if (S > 8 || !(lane & 8)) {
 #pragma unroll
-            for (int e = 0; e < EL; ++e) cacc[wv][g][seg * EL + e] = acc[g][e];
+            for (int e = 0; e < EW; ++e) cacc[wv][g][seg * EL + e0 + e] = acc[g][e];
+        }
     }
+    ls = across32(across16(ls, OpAdd{}), OpAdd{});
     if (lane < QG) {
         cm[wv][lane] = m;
         cl[wv][lane] = ls;

@@ -201,9 +201,9 @@ __global__ __launch_bounds__(256, 2) void k_fs2s(ScoreArgs a)
 #pragma unroll
         for (int r = 0; r < 16; ++r) att += fast_exp2(fmaf(acc[r], sc, -rsh[r]));
         float kmu = h ? acc[14] + acc[15] : 0.f;
-        n2 += __shfl_xor(n2, 32, kWave);
-        att += __shfl_xor(att, 32, kWave);
-        kmu += __shfl_xor(kmu, 32, kWave);
+        n2 = across32(n2, OpAdd{});
+        att = across32(att, OpAdd{});
+        kmu = across32(kmu, OpAdd{});
         const float dE = __builtin_amdgcn_sqrtf(wd[kl]);
         const float cm = kmu * __builtin_amdgcn_rsqf(fmaxf(n2, 1e-24f));
         const int gi = key0 + kl;
@@ -380,7 +380,7 @@ __global__ __launch_bounds__(256, 2) void k_fs1s(ScoreArgs a)
             n2 = dot2sq(b[st][0], dot2sq(b[st][1], dot2sq(b[st][2], dot2sq(b[st][3], n2))));
             acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, b[st]), aq[0][st], acc, 0, 0, 0);
         }
-        n2 += __shfl_xor(n2, 32, kWave);
+        n2 = across32(n2, OpAdd{});
         const float inv = __builtin_amdgcn_rsqf(fmaxf(n2, 1e-24f));
         if (h == 0) {
             const unsigned hi = bf16_rne(inv);
@@ -982,6 +982,7 @@ __global__ __launch_bounds__(kUThreads) void k_epi_unit(ScoreArgs a)
     // d_E, khat.mu and attention of the thread's keys (zero past P), and the
     // attention just outside the block's range (a negative offset wraps past
     // the range and reads zero)
+    const unsigned tag = SPLIT > 1 ? *a.tagw : 0u;  // this call's (bumped by the second sweep)
     Red4 v{0.f, 0.f, INFINITY, -INFINITY};
     float dq2 = 0.f;  // this thread's partial sum of d_E^2
     const int nb2 = (T + a.rpb2 - 1) / a.rpb2;
@@ -1074,43 +1075,38 @@ __global__ __launch_bounds__(kUThreads) void k_epi_unit(ScoreArgs a)
     }
     Red4 sd = block_red4_lds(w, lds);
     if (SPLIT > 1) {
-        // exchange with the other parts of the unit: publish, then wait for each (bounded)
-        if (threadIdx.x == 0) {
-            const unsigned tag = *a.tagw;  // this call's (bumped by the second sweep)
-            unsigned long long *mine = a.epiT + ((int64_t)u * SPLIT + part) * 4;
-            epi_tag_store(mine + 0, sd.s0, tag);
-            epi_tag_store(mine + 1, sd.s1, tag);
-            epi_tag_store(mine + 2, sd.mn, tag);
-            epi_tag_store(mine + 3, sd.mx, tag);
-            Red4 c{0.f, 0.f, INFINITY, -INFINITY};
-            bool all_ok = true;
-            for (int pp = 0; pp < SPLIT; ++pp) {  // in part order, so every part adds in the same order
-                Red4 r = sd;
-                if (pp != part) {
-                    const unsigned long long *other = a.epiT + ((int64_t)u * SPLIT + pp) * 4;
-                    unsigned long long o[4] = {0ull, 0ull, 0ull, 0ull};
-                    bool ok = false;
-                    // a spin limit <= 0 (set by the host to exercise this path) gives up at once
-                    for (int tries = 0; tries < a.spin_limit && !ok; ++tries) {
-                        ok = true;
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            o[q] = __hip_atomic_load(other + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                            ok = ok && (unsigned)(o[q] >> 32) == tag;
-                        }
-                        if (!ok) __builtin_amdgcn_s_sleep(2);
-                    }
-                    all_ok = all_ok && ok;
-                    r = Red4{__uint_as_float((unsigned)o[0]), __uint_as_float((unsigned)o[1]),
-                             __uint_as_float((unsigned)o[2]), __uint_as_float((unsigned)o[3])};
+        // exchange with the other parts of the unit: publish, then wait for all
+        // (bounded), lane 4 p + q of wave 0 polling word q of part p, so that the
+        // parts cost one round trip and not one each
+        if (wv == 0) {
+            unsigned long long *words = a.epiT + (int64_t)u * SPLIT * 4;
+            const float mine = (lane & 3) == 0 ? sd.s0 : (lane & 3) == 1 ? sd.s1 : (lane & 3) == 2 ? sd.mn : sd.mx;
+            const bool own = lane >> 2 == part;
+            if (own) epi_tag_store(words + lane, mine, tag);
+            float got = mine;
+            bool ok = own || lane >= 4 * SPLIT;
+            // a spin limit <= 0 (set by the host to exercise this path) gives up at once
+            for (int tries = 0; tries < a.spin_limit && __builtin_amdgcn_ballot_w64(!ok); ++tries) {
+                if (!ok) {
+                    const unsigned long long o =
+                        __hip_atomic_load(words + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    ok = (unsigned)(o >> 32) == tag;
+                    got = __uint_as_float((unsigned)o);
                 }
-                c = pp == 0 ? r : Red4{c.s0 + r.s0, c.s1 + r.s1, fminf(c.mn, r.mn), fmaxf(c.mx, r.mx)};
+                if (__builtin_amdgcn_ballot_w64(!ok)) __builtin_amdgcn_s_sleep(2);
             }
-            if (!all_ok) {
-                __hip_atomic_store(a.status, tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                c.s0 = NAN;
+            auto value = [&](int l) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(got), l)); };
+            Red4 c{value(0), value(1), value(2), value(3)};
+#pragma unroll
+            for (int p = 1; p < SPLIT; ++p)  // in part order, so every part adds in the same order
+                c = Red4{c.s0 + value(4 * p), c.s1 + value(4 * p + 1), fminf(c.mn, value(4 * p + 2)),
+                         fmaxf(c.mx, value(4 * p + 3))};
+            const bool lost = __builtin_amdgcn_ballot_w64(!ok) != 0;
+            if (lost) c.s0 = NAN;
+            if (lane == 0) {
+                if (lost) __hip_atomic_store(a.status, tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                lds[kUW] = c;
             }
-            lds[kUW] = c;
         }
         lds_barrier();
         sd = lds[kUW];

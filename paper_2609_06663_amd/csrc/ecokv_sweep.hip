@@ -254,20 +254,12 @@ __device__ __forceinline__ void tile_operand(const u32x4 *wst, int nt, int lane,
 // three swaps and three additions instead of eight lane moves and eight.
 __device__ __forceinline__ float groups_sum4(float a, float b, float c, float d)
 {
-    // lanes 32..63 of the first with lanes 0..31 of the second
-    const auto ac = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(c), false, false);
-    const auto bd = __builtin_amdgcn_permlane32_swap(__float_as_uint(b), __float_as_uint(d), false, false);
-    const float x = __uint_as_float(ac[0]) + __uint_as_float(ac[1]);
-    const float y = __uint_as_float(bd[0]) + __uint_as_float(bd[1]);
-    // the odd 16-lane rows of the first with the even rows of the second
-    const auto xy = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
-    return __uint_as_float(xy[0]) + __uint_as_float(xy[1]);
+    return fold16(fold32(a, c), fold32(b, d));
 }
 
 __device__ __forceinline__ float groups_sum(float x)
 {
-    x += __shfl_xor(x, 16, kWave);
-    return x + __shfl_xor(x, 32, kWave);
+    return across32(across16(x, OpAdd{}), OpAdd{});
 }
 
 // Sweep 1, per block of a.rpb1 keys: column sums of k and k / |k|, and per
