@@ -105,15 +105,21 @@ __device__ __forceinline__ float centroid_component(const ScoreArgs &a, const Un
 // rows' base-2 references and sums): from the workspace after the first sweep,
 // or converted from the sums a prefill handed over (ecokv_score_pre: plain
 // sums over the T keys, references in natural units).
-__device__ __forceinline__ float anchor_value(const ScoreArgs &a, const Unit &un, int u, int T, int c)
+__device__ __forceinline__ float anchor_load(const ScoreArgs &a, int u, int c)
 {
-    const int64_t at = (int64_t)u * (2 * a.D + 2 * a.R) + c;
-    if (!a.pre) return a.anchors[at];
-    const float v = a.pre[at];
+    return (a.pre ? a.pre : a.anchors)[(int64_t)u * (2 * a.D + 2 * a.R) + c];
+}
+__device__ __forceinline__ float anchor_convert(const ScoreArgs &a, const Unit &un, int T, int c, float v)
+{
+    if (!a.pre) return v;
     if (c < a.D) return centroid_component(a, un, T, c, v);
     if (c < 2 * a.D) return v / (float)T;
     if (c < 2 * a.D + a.R) return v * kLog2e;
     return v;
+}
+__device__ __forceinline__ float anchor_value(const ScoreArgs &a, const Unit &un, int u, int T, int c)
+{
+    return anchor_convert(a, un, T, c, anchor_load(a, u, c));
 }
 
 // The unit's anchors for a sweep-2 block: the workspace row after the first
@@ -206,35 +212,6 @@ __device__ __forceinline__ void group_store(const u32x4 (&b)[8], __amdgpu_buffer
     for (int i = 0; i < 8; ++i)
         __builtin_amdgcn_raw_buffer_store_b128(b[i], rs, (key0 + 4 * i + (lane >> 4)) * (kD * 2) + (lane & 15) * 16, 0,
                                                2);
-}
-
-// Lane layout of a 32-key B operand of v_mfma_f32_32x32x16_bf16 (and of the
-// window-row A operands): lane l holds, for k-step s = 0..7, the 16-byte chunk
-// 2s + l/32 of its row, i.e. dimensions 8(2s + h) .. +7 with h = l/32.
-
-// MFMA operand row `which` (0: bf16 high part, 1: bf16 remainder) of the
-// fp32 vector v [kD] in that layout.
-__device__ __forceinline__ void mu_operand(const float *v, int which, int h, bf16x8 (&op)[8])
-{
-#pragma unroll
-    for (int s = 0; s < 8; ++s) {
-        const float4 *src = reinterpret_cast<const float4 *>(v + 8 * (2 * s + h));
-        const float4 x = src[0], y = src[1];
-        const float f8[8] = {x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
-        u32x4 q;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            unsigned half2[2];
-#pragma unroll
-            for (int z = 0; z < 2; ++z) {
-                const float f = f8[2 * e + z];
-                const unsigned hb = bf16_rne(f);
-                half2[z] = which ? bf16_rne(f - __uint_as_float(hb << 16)) : hb;
-            }
-            q[e] = half2[0] | (half2[1] << 16);
-        }
-        op[s] = __builtin_bit_cast(bf16x8, q);
-    }
 }
 
 }  // namespace fast

@@ -31,24 +31,24 @@ namespace ecokv {
 // ---------------------------------------------------------------------------
 namespace fast {
 
-// Window rows 32t + (lane & 31) as MFMA A operands (zero beyond R): for k-step
-// s the lane holds elements 8*(2s + lane/32) .. +7.
-template <int MT>
-__device__ __forceinline__ void load_query_operands(const ScoreArgs &a, const Unit &un, int lane, bf16x8 (&aq)[MT][8])
+// Window row lane & 31 as an MFMA operand (zero beyond R): for k-step s the
+// lane holds elements 8*(2s + lane/32) .. +7.  The loads alone, and the rows
+// beyond R cleared where they are first used, so that other loads go out
+// between the two.
+__device__ __forceinline__ void load_query_rows(const ScoreArgs &a, const Unit &un, int lane, u32x4 (&q)[8])
 {
+    const int r = lane & 31;
+    const uint16_t *qp = static_cast<const uint16_t *>(a.Q) + window_row(a, un, r < a.R ? r : 0) * kD;
 #pragma unroll
-    for (int t = 0; t < MT; ++t) {
-        const int r = 32 * t + (lane & 31);
-        const bool ok = r < a.R;
-        const uint16_t *qp = static_cast<const uint16_t *>(a.Q) + window_row(a, un, ok ? r : 0) * kD;
-        u32x4 q[8];
+    for (int s = 0; s < 8; ++s) q[s] = *reinterpret_cast<const u32x4 *>(qp + 8 * (2 * s + (lane >> 5)));
+}
+__device__ __forceinline__ void query_operands(const ScoreArgs &a, int lane, const u32x4 (&q)[8], bf16x8 (&aq)[1][8])
+{
+    const bool ok = (lane & 31) < a.R;
 #pragma unroll
-        for (int s = 0; s < 8; ++s) q[s] = *reinterpret_cast<const u32x4 *>(qp + 8 * (2 * s + (lane >> 5)));
-#pragma unroll
-        for (int s = 0; s < 8; ++s) {
-            const u32x4 z = {0u, 0u, 0u, 0u};
-            aq[t][s] = __builtin_bit_cast(bf16x8, ok ? q[s] : z);
-        }
+    for (int s = 0; s < 8; ++s) {
+        const u32x4 z = {0u, 0u, 0u, 0u};
+        aq[0][s] = __builtin_bit_cast(bf16x8, ok ? q[s] : z);
     }
 }
 
@@ -117,43 +117,54 @@ __global__ __launch_bounds__(256, 2) void k_fs2s(ScoreArgs a)
                                  (int)(((unsigned)(sb.x * kS2Waves + wv) * 2654435761u + u * 40503u) % (unsigned)ng))
                            : 0;
     auto goff = [&](int g) { return g < ng ? 32 * (g + rot < ng ? g + rot : g + rot - ng) : 32 * ng; };
+    // The set-up's loads go out first and the first three groups behind them:
+    // loads return in order, so the set-up works while the groups are in flight.
+    u32x4 q[8];
+    load_query_rows(a, un, lane, q);
+    // thread c < D: components c of kbar and mu; thread D + m: window row m's reference and sum
+    const int am = min(max(tid - kD, 0), a.R - 1);
+    const int ac0 = tid < kD ? tid : 2 * kD + am, ac1 = tid < kD ? kD + tid : 2 * kD + a.R + am;
+    const float ld0 = anchor_load(a, u, ac0), ld1 = anchor_load(a, u, ac1);
+    __builtin_amdgcn_sched_barrier(0);
     u32x4 b0[8], b1[8], b2[8], b3[8];
     group_load(b0, rs, goff(0), lane);
     group_load(b1, rs, goff(1), lane);
     group_load(b2, rs, goff(2), lane);
-    __shared__ __attribute__((aligned(16))) float sanc[2 * kD + 2 * ECOKV_MAX_ROWS];
-    const float *anc = unit_anchors(a, un, u, T, sanc);
+    __builtin_amdgcn_sched_barrier(0);
+    // The anchors through LDS, each converted once in the block: kbar, mu as two
+    // bf16 rows (high part and remainder), and the row shifts M'_m.
+    __shared__ __attribute__((aligned(16))) float kbs[kD];
+    __shared__ __attribute__((aligned(16))) uint16_t mus[2][kD];
+    __shared__ __attribute__((aligned(16))) float shs[32];
+    const float av0 = anchor_convert(a, un, T, ac0, ld0), av1 = anchor_convert(a, un, T, ac1, ld1);
+    if (tid < kD) {
+        kbs[tid] = av0;
+        const unsigned hi = bf16_rne(av1);
+        mus[0][tid] = (uint16_t)hi;
+        mus[1][tid] = (uint16_t)bf16_rne(av1 - __uint_as_float(hi << 16));
+    } else if (tid < kD + 32) {
+        shs[tid - kD] = tid - kD < a.R ? av0 + __log2f(av1) : INFINITY;
+    }
     const float sc = a.inv_sqrt_d * kLog2e;
     constexpr int kAnc = 32 - 2;
 
     // A operand: window rows (zero beyond R), rows 30, 31 mu high / remainder
     bf16x8 aq[1][8];
-    load_query_operands<1>(a, un, lane, aq);
-    if (kl >= kAnc) mu_operand(anc + kD, kl - kAnc, h, aq[0]);
+    query_operands(a, lane, q, aq);
+    lds_barrier();
+    if (kl >= kAnc) {
+#pragma unroll
+        for (int s = 0; s < 8; ++s)
+            aq[0][s] = *reinterpret_cast<const bf16x8 *>(&mus[kl - kAnc][8 * (2 * s + h)]);
+    }
     // kbar at the 8 dimensions of chunk lane % 16, the chunk this lane loads
     float kbc[8];
-    {
-        const float4 *src = reinterpret_cast<const float4 *>(anc + 8 * (lane & 15));
-        const float4 x = src[0], y = src[1];
-        kbc[0] = x.x; kbc[1] = x.y; kbc[2] = x.z; kbc[3] = x.w;
-        kbc[4] = y.x; kbc[5] = y.y; kbc[6] = y.z; kbc[7] = y.w;
-    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) kbc[e] = kbs[8 * (lane & 15) + e];
     // per-lane row shifts M'_m for the rows m = 8(r/4) + 4h + r%4 of accumulator r
     float rsh[16];
-    {
-        float mv[16], sv[16];
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int m = min(8 * (r >> 2) + 4 * h + (r & 3), a.R - 1);
-            mv[r] = anc[2 * kD + m];
-            sv[r] = anc[2 * kD + a.R + m];
-        }
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int m = 8 * (r >> 2) + 4 * h + (r & 3);
-            rsh[r] = m < a.R ? mv[r] + __log2f(sv[r]) : INFINITY;
-        }
-    }
+    for (int r = 0; r < 16; ++r) rsh[r] = shs[8 * (r >> 2) + 4 * h + (r & 3)];
 
     float dsum = 0.f, dsq = 0.f, dmn = INFINITY, dmx = -INFINITY;
     const float inv_r = 1.f / (float)a.R;
@@ -344,12 +355,16 @@ __global__ __launch_bounds__(256, 2) void k_fs1s(ScoreArgs a)
                                  (int)(((unsigned)(sb.x * kS2Waves + wv) * 2654435761u + u * 40503u) % (unsigned)ng))
                            : 0;
     auto goff = [&](int g) { return g < ng ? 32 * (g + rot < ng ? g + rot : g + rot - ng) : 32 * ng; };
+    u32x4 q[8];
+    load_query_rows(a, un, lane, q);
+    __builtin_amdgcn_sched_barrier(0);  // (ahead of the groups, as in sweep 2)
     u32x4 b0[8], b1[8], b2[8];
     group_load_rows(b0, rs, goff(0), lane, src_row_bytes);
     group_load_rows(b1, rs, goff(1), lane, src_row_bytes);
 
+    __builtin_amdgcn_sched_barrier(0);
     bf16x8 aq[1][8];
-    load_query_operands<1>(a, un, lane, aq);
+    query_operands(a, lane, q, aq);
     if (lane < 32) {
         wts[wv][0][lane] = 0x3f80;
         wts[wv][3][lane] = 0;
