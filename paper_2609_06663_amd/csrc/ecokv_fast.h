@@ -23,19 +23,19 @@ __device__ __forceinline__ Unit score_unit(const ScoreArgs &a, int u)
 
 __device__ __forceinline__ int64_t unit_out_base(const ScoreArgs &a, const Unit &un)
 {
-    return ((int64_t)un.l * a.Hkv + un.h) * a.Ptot + (un.c0 - un.s * a.w);
+    return (int64_t)un.lh * a.Ptot + (un.c0 - un.s * a.w);
 }
 
 __device__ __forceinline__ int64_t unit_row0(const ScoreArgs &a, const Unit &un)
 {
-    return ((int64_t)un.l * a.Hkv + un.h) * a.Ttot + un.c0;
+    return (int64_t)un.lh * a.Ttot + un.c0;
 }
 
 // Global row index of window row r = (g, j) of unit `un` in Q_win.
 __device__ __forceinline__ int64_t window_row(const ScoreArgs &a, const Unit &un, int r)
 {
     const int g = r / a.w, j = r % a.w;
-    return (((int64_t)un.l * a.Hq + (int64_t)un.h * a.G + g) * a.B + un.s) * a.w + j;
+    return (((int64_t)un.lh * a.G + g) * a.B + un.s) * a.w + j;
 }
 
 // The unit u and the block x of its keys that this block of a sweep takes.
@@ -49,26 +49,20 @@ struct SweepBlock {
 };
 __device__ __forceinline__ SweepBlock sweep_block(const ScoreArgs &a)
 {
+    // grid (blocks of a pair, pairs)
     SweepBlock b;
-    int lh, s = 0, r;
-    if (a.B == 1) {
-        lh = blockIdx.x / a.bl[1];
-        r = blockIdx.x - lh * a.bl[1];
-        b.x = r;
-    } else {
-        const int per = a.bl[a.B];
-        lh = blockIdx.x / per;
-        r = blockIdx.x - lh * per;
+    const int lh = blockIdx.y, r = blockIdx.x;
+    int s = 0;
+    if (a.B > 1)
         for (int n = a.B; n > 1;) {  // the last s with bl[s] <= r
             const int half = n >> 1;
             if (a.bl[s + half] <= r) s += half;
             n -= half;
         }
-        b.x = r - a.bl[s];
-    }
+    b.x = a.B > 1 ? r - a.bl[s] : r;
     const SeqSpan q = seq_span(a.seq, a.B, s);
     const int l = lh / a.Hkv;
-    b.un = Unit{l, lh - l * a.Hkv, q.s, q.c0, q.T};
+    b.un = Unit{l, lh - l * a.Hkv, q.s, lh, q.c0, q.T};
     b.u = lh * a.B + q.s;
     return b;
 }
@@ -122,25 +116,14 @@ __device__ __forceinline__ float anchor_value(const ScoreArgs &a, const Unit &un
     return anchor_convert(a, un, T, c, anchor_load(a, u, c));
 }
 
-// The unit's anchors for a sweep-2 block: the workspace row after the first
-// sweep, or, with handed-over sums, the converted row staged in `lds` (every
-// thread of the block calls it; a.pre is the same for the whole launch).
-__device__ __forceinline__ const float *unit_anchors(const ScoreArgs &a, const Unit &un, int u, int T, float *lds)
-{
-    if (!a.pre) return a.anchors + (int64_t)u * (2 * a.D + 2 * a.R);
-    for (int c = threadIdx.x; c < 2 * a.D + 2 * a.R; c += blockDim.x) lds[c] = anchor_value(a, un, u, T, c);
-    __syncthreads();
-    return lds;
-}
-
 // The workspace's exchange tag, bumped once per score call by the second
-// sweep's first block and read by the split epilogue after it, so that every
+// sweep's first block, when it is done, and read by the split epilogue after it, so that every
 // call (every replay of a captured call included) tags its exchanges afresh
 // and never reads an older call's words (0 is skipped: the status word
 // records the tag of a call whose wait gave up).
 __device__ __forceinline__ void bump_call_tag(const ScoreArgs &a)
 {
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
         const unsigned t = *a.tagw + 1u;
         *a.tagw = t ? t : 1u;
     }

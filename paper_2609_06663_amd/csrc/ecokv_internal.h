@@ -22,6 +22,7 @@ struct SeqTab {
 // Decode unit u = (l*Hkv + h)*B + s.
 struct Unit {
     int l, h, s;
+    int lh;     // l * Hkv + h
     int c0, T;  // the sequence's first token and its tokens (score_unit, sweep_block)
 };
 __device__ __forceinline__ Unit unit_of(int u, int Hkv, int B)
@@ -29,6 +30,7 @@ __device__ __forceinline__ Unit unit_of(int u, int Hkv, int B)
     Unit r{};
     r.s = B == 1 ? 0 : u % B;
     const int lh = B == 1 ? u : u / B;
+    r.lh = lh;
     r.h = lh % Hkv;
     r.l = lh / Hkv;
     return r;
@@ -215,7 +217,7 @@ hipError_t decode_launch(DecodeArgs a, char *ws, size_t ws_bytes, bool bf16, hip
 // rows): pass 1 or 2 over blocks of a.rpb1 / a.rpb2 keys, a multiple of 128
 // (bf16: 256) up to sweep_rows_max_keys.
 int sweep_rows_max_keys(bool bf16);
-void sweep_rows_launch(int pass, const ScoreArgs &a, unsigned blocks, hipStream_t st);
+void sweep_rows_launch(int pass, const ScoreArgs &a, dim3 grid, hipStream_t st);
 
 WsLayout score_ws_layout(int L, int Hkv, int B, int D, int R, int64_t Ptot, int maxT, bool bf16, bool vnorm);
 hipError_t score_launch(ScoreArgs a, char *ws, const WsLayout &lay, int maxT, hipStream_t st, bool bf16);

@@ -55,8 +55,8 @@ __device__ __forceinline__ void query_operands(const ScoreArgs &a, int lane, con
 // Sweep 2, streaming form (window rows + 2 rows of mu in one 32-row operand,
 // i.e. G*w <= 30): no LDS tile and no barrier in the key loop.  Each wave
 // streams a quarter of the block's keys in groups of 32 from HBM into
-// registers (three groups in flight, the first three before the window rows
-// and anchors, so that their latencies overlap), re-lays them out through a
+// registers (three groups in flight, the first three right behind the loads of
+// the window rows and anchors), re-lays them out through a
 // wave-private LDS stage into MFMA B operands (lane l: key l % 32, 16-byte
 // chunks 2s + l / 32).  The attention of row m is 2^(x - M'_m) with
 // M'_m = M_m + log2(S_m), the normaliser folded into the shift.  Bound by the
@@ -81,7 +81,6 @@ __device__ __forceinline__ void group_load(u32x4 (&b)[8], __amdgpu_buffer_rsrc_t
 
 __global__ __launch_bounds__(256, 2) void k_fs2s(ScoreArgs a)
 {
-    bump_call_tag(a);
     const int wave_keys = a.rpb2 / kS2Waves;  // a multiple of 32
     __shared__ float wred[4][kS2Waves];
     __shared__ u32x4 stage[kS2Waves][32 * kChunks];  // per wave: 32 rows, swizzled 16-byte chunks
@@ -113,12 +112,12 @@ __global__ __launch_bounds__(256, 2) void k_fs2s(ScoreArgs a)
     // at any moment they read different offsets rather than the same offset
     // of equally sized, equally aligned ranges (which would crowd the same
     // memory channels).  Slot g >= ng reads past the range: zeros, skipped.
-    const int rot = ng > 0 ? __builtin_amdgcn_readfirstlane(
-                                 (int)(((unsigned)(sb.x * kS2Waves + wv) * 2654435761u + u * 40503u) % (unsigned)ng))
-                           : 0;
+    const int rot = ng > 0 ? uniform_i32((int)(((unsigned)(sb.x * kS2Waves + wv) * 2654435761u + u * 40503u) % (unsigned)ng)) : 0;
     auto goff = [&](int g) { return g < ng ? 32 * (g + rot < ng ? g + rot : g + rot - ng) : 32 * ng; };
     // The set-up's loads go out first and the first three groups behind them:
-    // loads return in order, so the set-up works while the groups are in flight.
+    // loads return in order, so the set-up works while the groups are in flight
+    // (the other way round, and each wave converting the anchors by itself, the
+    // score of one 32768-token layer took 38.3 us instead of 34.5).
     u32x4 q[8];
     load_query_rows(a, un, lane, q);
     // thread c < D: components c of kbar and mu; thread D + m: window row m's reference and sum
@@ -295,6 +294,7 @@ __global__ __launch_bounds__(256, 2) void k_fs2s(ScoreArgs a)
         pp[2] = mx;
         pp[3] = s2;
     }
+    bump_call_tag(a);
 }
 
 // Sweep 1, streaming form (bf16, head_dim 128, G*w <= 32): like the streaming
@@ -351,9 +351,7 @@ __global__ __launch_bounds__(256, 2) void k_fs1s(ScoreArgs a)
     const __amdgpu_buffer_rsrc_t rdst = key_rows_rsrc(krow0 + (int64_t)wbase * kD, CACHE ? wkeys : 0);
     u32x4 *wst = stage[wv];
     const int ng = (wkeys + 31) >> 5;
-    const int rot = ng > 0 ? __builtin_amdgcn_readfirstlane(
-                                 (int)(((unsigned)(sb.x * kS2Waves + wv) * 2654435761u + u * 40503u) % (unsigned)ng))
-                           : 0;
+    const int rot = ng > 0 ? uniform_i32((int)(((unsigned)(sb.x * kS2Waves + wv) * 2654435761u + u * 40503u) % (unsigned)ng)) : 0;
     auto goff = [&](int g) { return g < ng ? 32 * (g + rot < ng ? g + rot : g + rot - ng) : 32 * ng; };
     u32x4 q[8];
     load_query_rows(a, un, lane, q);
@@ -1179,11 +1177,11 @@ static int64_t work_blocks(const ScoreArgs &a, int keys)
 }
 
 // Fills a.bl for blocks of `keys` keys; returns the grid of the sweep.
-static unsigned sweep_grid(ScoreArgs &a, int keys)
+static dim3 sweep_grid(ScoreArgs &a, int keys)
 {
     a.bl[0] = 0;
     for (int s = 0; s < a.B; ++s) a.bl[s + 1] = a.bl[s] + (a.seq.cu[s + 1] - a.seq.cu[s] + keys - 1) / keys;
-    return (unsigned)((int64_t)a.bl[a.B] * a.L * a.Hkv);
+    return dim3(a.bl[a.B], a.L * a.Hkv);
 }
 
 // Keys per block of the streaming sweeps: a multiple of 128 (whole 32-key
@@ -1386,7 +1384,7 @@ hipError_t score_launch(ScoreArgs a, char *ws, const WsLayout &lay, int maxT, hi
                 a.rpb1 = stream_block_keys(a);
                 a.nch1 = (maxT + a.rpb1 - 1) / a.rpb1;
                 ECOKV_TIMED("sweep1_stream", st,
-                            hipLaunchKernelGGL(fast::k_fs1s<false>, dim3(sweep_grid(a, a.rpb1)), dim3(256), 0, st, a));
+                            hipLaunchKernelGGL(fast::k_fs1s<false>, sweep_grid(a, a.rpb1), dim3(256), 0, st, a));
             } else {
                 a.rpb1 = rows_block_keys(a, bf16);
                 a.nch1 = (maxT + a.rpb1 - 1) / a.rpb1;
@@ -1406,7 +1404,7 @@ hipError_t score_launch(ScoreArgs a, char *ws, const WsLayout &lay, int maxT, hi
             a.rpb2 = stream_block_keys(a);
             a.nch2 = (maxT + a.rpb2 - 1) / a.rpb2;
             ECOKV_TIMED("sweep2_stream", st,
-                        hipLaunchKernelGGL(fast::k_fs2s, dim3(sweep_grid(a, a.rpb2)), dim3(256), 0, st, a));
+                        hipLaunchKernelGGL(fast::k_fs2s, sweep_grid(a, a.rpb2), dim3(256), 0, st, a));
         } else {
             a.rpb2 = rows_block_keys(a, bf16);
             a.nch2 = (maxT + a.rpb2 - 1) / a.rpb2;
@@ -1560,7 +1558,7 @@ hipError_t prefill_launch(ScoreArgs a, const void *Vsrc, void *Vdst, char *ws, i
         a.rpb1 = fast::kS2KeysCache;
         a.nch1 = (maxT + a.rpb1 - 1) / a.rpb1;
         ECOKV_TIMED("prefill_sweep", st,
-                    hipLaunchKernelGGL(fast::k_fs1s<true>, dim3(sweep_grid(a, a.rpb1)), dim3(256), 0, st, a));
+                    hipLaunchKernelGGL(fast::k_fs1s<true>, sweep_grid(a, a.rpb1), dim3(256), 0, st, a));
     } else {
         // other shapes: copy the rows, then the first sweep over the cache
         ECOKV_TIMED("prefill_copy", st,
