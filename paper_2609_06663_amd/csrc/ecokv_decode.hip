@@ -10,6 +10,7 @@
 // softmax is kept in base 2.  A block merges its waves in LDS and writes one
 // (max, sum, acc[D]) per query to the workspace; k_decode_merge combines a
 // query row's chunks.
+#include "ecokv_decode_plan.h"
 #include "ecokv_internal.h"
 
 namespace ecokv {
@@ -18,26 +19,19 @@ typedef unsigned int u32x4d __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8d __attribute__((ext_vector_type(8)));
 
 constexpr int kDecThreads = 256;
-constexpr int kDecWaves = kDecThreads / kWave;
-constexpr int kWaveRows = 192;    // rows per wave at most (256 measured no faster)
-constexpr int kMinWaveRows = 32;  // and at least: a wave's second tile loads while its first is used
-constexpr int kDecChunk = kDecWaves * kWaveRows;
-constexpr int kDecQG = 8;         // query heads per block at most
-constexpr int kOneRound = 256;    // chunks that give every compute unit one
-constexpr int kOneRows = 128;     // rows per wave up to which one round is enough
-constexpr int kPlanPer = 4;       // units per lane of a balanced plan
-constexpr int kPlanUnits = kPlanPer * kWave;  // and at most
+static_assert(kDecWaves == kDecThreads / kWave && kPlanUnits == kPlanPer * kWave, "the plan's block");
 
 // Which chunk a block takes.
-//  * Fixed (a.plan == 0): every unit in a.np chunks (or fewer, of at least
-//    kMinWaveRows rows per wave), block b chunk b / U of unit b % U, so that
-//    the blocks past the shorter units, which end at once, come last.
+//  * Fixed (a.plan == 0, and past two rounds): every unit in a.np chunks (or
+//    fewer, of at least kMinWaveRows rows per wave), block b chunk b / U of
+//    unit b % U, so that the blocks past the shorter units, which end at once,
+//    come last.
 //  * Balanced: the counts are on the device, so every wave reads them all,
 //    gives every chunk of the call the same number of rows and finds its
 //    block's chunk by a prefix sum.  Chunks of a fixed length leave compute
 //    units idle when there are few rows, and with each unit split into the
 //    same number of chunks the long ones of ragged units finish last.  About
-//    one chunk per compute unit while its waves then take at most kOneRows
+//    one block per compute unit while its waves then take at most kOneRows
 //    rows each, else two; past two rounds of kWaveRows rows the fixed chunks.
 //    (us, fixed 768-row chunks -> now: one layer's 4 units of 6553 rows 16 ->
 //    8.2; 16 sequences with budgets shared over 4 heads 36 -> 25; 8 packed
@@ -46,13 +40,6 @@ constexpr int kPlanUnits = kPlanPer * kWave;  // and at most
 struct DecodePlan {
     int u, c, n, off, wave_rows;  // unit, chunk, the unit's rows and offset, rows per wave
 };
-
-// Rows per wave of a unit of n rows in np fixed chunks.
-__device__ __forceinline__ int fixed_wave_rows(int n, int np)
-{
-    const int r = (n + kDecWaves * np - 1) / (kDecWaves * np);
-    return min(max((r + 15) & ~15, kMinWaveRows), kWaveRows);
-}
 
 __device__ __forceinline__ bool decode_plan(const DecodeArgs &a, int b, DecodePlan &p)
 {
@@ -72,17 +59,12 @@ __device__ __forceinline__ bool decode_plan(const DecodeArgs &a, int b, DecodePl
             n[q] = max(0, min(n[q], a.max_count));  // more rows than max_count: the merge writes NaN
             sum += (float)n[q];  // (a float: only the rows per wave come from it, alike in every wave)
         }
-        // rows per wave in one and in two rounds (a unit's last chunk is half empty on average)
-        const float total = wave_sum(sum) / (float)(kDecWaves * a.plan), lost = 0.5f * (float)U;
-        const float one = total / (kOneRound - lost), two = total / (2 * kOneRound - lost);
-        if (two <= 2.f * (float)kWaveRows) {
-            const int want = (int)ceilf(one <= (float)kOneRows ? one : two);
-            p.wave_rows = uniform_i32(min(max((want + 15) & ~15, kMinWaveRows), kWaveRows));
-            const int chunk = kDecWaves * p.wave_rows;
+        p.wave_rows = uniform_i32(plan_wave_rows(wave_sum(sum), U, a.plan));
+        if (p.wave_rows > 0) {
             int parts[kPlanPer], mine = 0;
 #pragma unroll
             for (int q = 0; q < kPlanPer; ++q) {
-                parts[q] = (n[q] + chunk - 1) / chunk;
+                parts[q] = unit_chunks(n[q], p.wave_rows);
                 mine += parts[q];
             }
             const int end = (int)wave_incl_scan((uint32_t)mine);
@@ -370,8 +352,7 @@ __global__ __launch_bounds__(kMergeThreads) void k_decode_merge(DecodeArgs a)
     const int2 e = a.plan ? a.tab[u] : make_int2(0, 0);  // (not written for a unit without rows)
     const int n = a.counts[u], nn = max(0, min(n, a.max_count));
     int64_t first = u, step = (int64_t)a.L * a.Hkv * a.B;
-    const int chunk = kDecWaves * fixed_wave_rows(nn, a.np);
-    int used = (nn + chunk - 1) / chunk;
+    int used = unit_chunks(nn, fixed_wave_rows(nn, a.np));
     if (nn > 0 && e.y > 0) {
         first = e.x;
         used = e.y;
@@ -428,10 +409,6 @@ __global__ __launch_bounds__(kMergeThreads) void k_decode_merge(DecodeArgs a)
         a.lse[qrow] = bad ? NAN : (M == -INFINITY ? -INFINITY : (M + log2f(L)) * 0.69314718055994531f);
 }
 
-// Query heads per block: all of G up to 8 (so that Kc / Vc are read once),
-// rounded up to 1, 2, 4 or 8; larger G takes several blocks of 8.
-static int decode_qg(int G) { return G > 4 ? kDecQG : G > 2 ? 4 : G; }
-
 template <bool BF, int D>
 static void launch_dec(const DecodeArgs &a, dim3 grid, hipStream_t st)
 {
@@ -440,39 +417,6 @@ static void launch_dec(const DecodeArgs &a, dim3 grid, hipStream_t st)
     else if (qg == 4) hipLaunchKernelGGL((k_decode<BF, D, 4>), grid, dim3(kDecThreads), 0, st, a);
     else if (qg == 2) hipLaunchKernelGGL((k_decode<BF, D, 2>), grid, dim3(kDecThreads), 0, st, a);
     else hipLaunchKernelGGL((k_decode<BF, D, 1>), grid, dim3(kDecThreads), 0, st, a);
-}
-
-// Chunks, blocks (per group of query heads) and workspace of a call.
-//  * `least`, what any call can do with: one chunk for every kDecChunk rows of
-//    max_count.  All that calls of at most two such chunks ask for: their
-//    callers hold workspaces of exactly that size.
-//  * chunks of kMinWaveRows rows per wave where max_count rows in every unit
-//    make at most one round of them;
-//  * else a balanced plan: at most one chunk per unit more than its rows
-//    divided by the chunk, and room in its grid for fixed chunks.
-struct DecodeGrid {
-    int plan, np;
-    int64_t blocks;
-    size_t bytes;
-};
-
-static DecodeGrid decode_grid(int64_t units, int G, int D, int max_count, bool least)
-{
-    DecodeGrid g{};
-    const size_t part = sizeof(float) * (size_t)G * (size_t)(D + 2);
-    const int qg = decode_qg(G), zg = (G + qg - 1) / qg;
-    constexpr int kSmall = kDecWaves * kMinWaveRows;
-    const int coarse = (max_count + kDecChunk - 1) / kDecChunk, fine = (max_count + kSmall - 1) / kSmall;
-    const bool few = units * fine * zg <= kOneRound;
-    least = least || coarse <= 2;
-    g.np = !least && few ? fine : coarse;
-    g.blocks = units * g.np;
-    g.bytes = part * (size_t)g.blocks;
-    if (least || few || units > kPlanUnits) return g;
-    g.plan = zg;
-    g.blocks = units + max((int64_t)(2 * kOneRound), (units * max_count + kDecChunk - 1) / kDecChunk);
-    g.bytes = part * (size_t)g.blocks + sizeof(int2) * (size_t)units;
-    return g;
 }
 
 size_t decode_ws_bytes(int64_t units, int G, int D, int max_count, bool least)
@@ -484,8 +428,6 @@ hipError_t decode_launch(DecodeArgs a, char *ws, size_t ws_bytes, bool bf16, hip
 {
     const int64_t U = (int64_t)a.L * a.Hkv * a.B;
     if (U == 0) return hipSuccess;
-    const int qg = decode_qg(a.G);
-    const int zg = (a.G + qg - 1) / qg;
     DecodeGrid g = decode_grid(U, a.G, a.D, a.max_count, false);
     if (ws_bytes < g.bytes) g = decode_grid(U, a.G, a.D, a.max_count, true);
     if (g.blocks > INT32_MAX) return hipErrorInvalidConfiguration;
@@ -493,7 +435,7 @@ hipError_t decode_launch(DecodeArgs a, char *ws, size_t ws_bytes, bool bf16, hip
     a.np = g.np;
     a.part = reinterpret_cast<float *>(ws);
     a.tab = g.plan ? reinterpret_cast<int2 *>(ws + g.bytes - sizeof(int2) * (size_t)U) : nullptr;
-    const dim3 grid((unsigned)g.blocks, zg);
+    const dim3 grid((unsigned)g.blocks, decode_head_groups(a.G));
     if (bf16 && a.D == 128) ECOKV_TIMED("decode", st, (launch_dec<true, 128>(a, grid, st)));
     else if (bf16) ECOKV_TIMED("decode", st, (launch_dec<true, 64>(a, grid, st)));
     else if (a.D == 128) ECOKV_TIMED("decode", st, (launch_dec<false, 128>(a, grid, st)));

@@ -1,0 +1,96 @@
+// How ecokv_decode splits the rows of a call over blocks: the arithmetic that
+// the workspace size, the grid and the kernels share.  Values only, no device
+// state, so that it can be evaluated on the host for any shape.
+#pragma once
+
+#include <math.h>
+#include <stddef.h>
+#include <stdint.h>
+
+namespace ecokv {
+
+constexpr int kDecWaves = 4;      // waves per block
+constexpr int kWaveRows = 192;    // rows per wave at most (256 measured no faster)
+constexpr int kMinWaveRows = 32;  // and at least: a wave's second tile loads while its first is used
+constexpr int kDecChunk = kDecWaves * kWaveRows;
+constexpr int kDecQG = 8;         // query heads per block at most
+constexpr int kOneRound = 256;    // blocks that give every compute unit one
+constexpr int kOneRows = 128;     // rows per wave up to which one round is enough
+constexpr int kPlanPer = 4;       // units per lane of a balanced plan
+constexpr int kPlanUnits = kPlanPer * 64;  // and at most
+
+// Query heads per block: all of G up to 8 (so that Kc / Vc are read once),
+// rounded up to 1, 2, 4 or 8; larger G takes several blocks of 8 per chunk.
+__host__ __device__ inline int decode_qg(int G) { return G > 4 ? kDecQG : G > 2 ? 4 : G; }
+__host__ __device__ inline int decode_head_groups(int G) { return (G + decode_qg(G) - 1) / decode_qg(G); }
+
+__host__ __device__ inline int clamp_wave_rows(int rows)
+{
+    const int r = (rows + 15) & ~15;  // whole 16-row tiles
+    return r < kMinWaveRows ? kMinWaveRows : r > kWaveRows ? kWaveRows : r;
+}
+
+// Rows per wave of a unit of n rows in np fixed chunks.
+__host__ __device__ inline int fixed_wave_rows(int n, int np)
+{
+    return clamp_wave_rows((n + kDecWaves * np - 1) / (kDecWaves * np));
+}
+
+// Rows per wave of a balanced plan over `units` units of `rows` rows in all,
+// each chunk read by zg blocks (one per group of query heads), so that a round
+// of blocks holds 1 / zg as many chunks; 0 where the call takes fixed chunks.
+// The chunks of a plan, sum of ceil(n / chunk) <= units + rows / chunk, always
+// fit decode_grid's blocks: with `one` or `two` rows per wave
+// rows / chunk <= (2 kOneRound - units / 2) / zg, and the half unit left over
+// is more than the rounding of `rows`; at kWaveRows the chunk is kDecChunk.
+__host__ __device__ inline int plan_wave_rows(float rows, int units, int zg)
+{
+    // rows per wave in one and in two rounds (a unit's last chunk is half empty on average)
+    const float total = rows * (float)zg / (float)kDecWaves, lost = 0.5f * (float)units;
+    const float one = total / (kOneRound - lost), two = total / (2 * kOneRound - lost);
+    if (two > 2.f * (float)kWaveRows) return 0;
+    return clamp_wave_rows((int)ceilf(one <= (float)kOneRows ? one : two));
+}
+
+// Chunks of a unit of n rows.
+__host__ __device__ inline int unit_chunks(int n, int wave_rows)
+{
+    return (n + kDecWaves * wave_rows - 1) / (kDecWaves * wave_rows);
+}
+
+// Chunks, blocks (per group of query heads) and workspace of a call.
+//  * `least`, what any call can do with: one chunk for every kDecChunk rows of
+//    max_count.  All that calls of at most two such chunks ask for: their
+//    callers hold workspaces of exactly that size.
+//  * chunks of kMinWaveRows rows per wave where max_count rows in every unit
+//    make at most one round of them;
+//  * else a balanced plan: at most one chunk per unit more than its rows
+//    divided by the chunk, and room in its grid for fixed chunks.
+struct DecodeGrid {
+    int plan;  // groups of query heads of a balanced plan, 0: fixed chunks
+    int np;    // fixed chunks per unit at most
+    int64_t blocks;
+    size_t bytes;
+};
+
+inline DecodeGrid decode_grid(int64_t units, int G, int D, int max_count, bool least)
+{
+    DecodeGrid g{};
+    const size_t part = sizeof(float) * (size_t)G * (size_t)(D + 2);
+    const int zg = decode_head_groups(G);
+    constexpr int kSmall = kDecWaves * kMinWaveRows;
+    const int coarse = (max_count + kDecChunk - 1) / kDecChunk, fine = (max_count + kSmall - 1) / kSmall;
+    const bool few = units * fine * zg <= kOneRound;
+    least = least || coarse <= 2;
+    g.np = !least && few ? fine : coarse;
+    g.blocks = units * g.np;
+    g.bytes = part * (size_t)g.blocks;
+    if (least || few || units > kPlanUnits) return g;
+    const int64_t fixed = (units * max_count + kDecChunk - 1) / kDecChunk;
+    g.plan = zg;
+    g.blocks = units + (fixed > 2 * kOneRound ? fixed : 2 * kOneRound);
+    g.bytes = part * (size_t)g.blocks + 2 * sizeof(int) * (size_t)units;  // and the units' (first block, blocks)
+    return g;
+}
+
+}  // namespace ecokv

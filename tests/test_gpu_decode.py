@@ -137,19 +137,30 @@ def test_decode_many_units_ragged():
     check(c, O, lse, L, Hq, Hkv, B, D, "bf16")
 
 
-@pytest.mark.parametrize("dtype,D,Hq,Hkv,B,counts,max_count", [
+# The last entry is the split that the call takes with its full workspace: fixed
+# chunks, or a balanced plan of so many rows per wave (test_decode_plan.py
+# checks these).
+PLAN_CASES = [
     # fixed chunks of 32 rows per wave (few units), their edges and one row past
-    ("bf16", 128, 28, 4, 1, [128, 129, 6553, 2049], 6553),
-    ("f32", 128, 14, 2, 1, [1, 4097], 4097),
+    ("bf16", 128, 28, 4, 1, [128, 129, 6553, 2049], 6553, "fixed"),
+    ("f32", 128, 14, 2, 1, [1, 4097], 4097, "fixed"),
     # the balanced plan: one round, two rounds, past two (fixed chunks again); units without rows
-    ("bf16", 128, 28, 4, 4, [4000, 1, 0, 9000, 127, 128, 129, 2500, 16, 17, 640, 1536, 768, 769, 3000, 5], 9000),
-    ("f32", 64, 32, 16, 4, list(range(60, 60 + 64 * 113, 113)), 9001),
-    ("bf16", 64, 8, 8, 8, [6144 + 31 * i for i in range(64)], 12000),
-    ("bf16", 64, 8, 8, 8, [12000 - i for i in range(64)], 12000),
+    ("bf16", 128, 28, 4, 4, [4000, 1, 0, 9000, 127, 128, 129, 2500, 16, 17, 640, 1536, 768, 769, 3000, 5], 9000, "balanced 32"),
+    ("f32", 64, 32, 16, 4, list(range(60, 60 + 64 * 113, 113)), 9001, "balanced 128"),
+    ("bf16", 64, 8, 8, 8, [6144 + 31 * i for i in range(64)], 12000, "balanced 192"),
+    ("bf16", 64, 8, 8, 8, [12000 - i for i in range(64)], 12000, "fixed"),
     # two groups of query heads; one unit more than a plan takes
-    ("bf16", 64, 48, 4, 1, [3000, 20, 900, 1700], 3000),
-    ("f32", 64, 257, 257, 1, [1600 + i % 7 for i in range(257)], 1606),
-])
+    ("bf16", 64, 48, 4, 1, [3000, 20, 900, 1700], 3000, "fixed"),
+    ("f32", 64, 257, 257, 1, [1600 + i % 7 for i in range(257)], 1606, "fixed"),
+    # balanced plans whose chunks take two, three and eight groups of query heads
+    ("f32", 64, 32, 2, 2, [6553, 1, 7000, 6000], 7000, "balanced 48"),
+    ("bf16", 64, 64, 4, 4, [19660 - 7 * i for i in range(16)], 19660, "balanced 192"),
+    ("bf16", 128, 96, 4, 1, [19660, 19001, 19659, 3], 19660, "balanced 96"),
+    ("bf16", 64, 64, 1, 1, [60000], 60000, "balanced 192"),
+]
+
+
+@pytest.mark.parametrize("dtype,D,Hq,Hkv,B,counts,max_count", [c[:7] for c in PLAN_CASES])
 def test_decode_plans(dtype, D, Hq, Hkv, B, counts, max_count):
     """The same outputs however the rows are split: with the workspace that the
     call asks for and with the least it takes.  Both are sums of the same
