@@ -93,7 +93,7 @@ __device__ __forceinline__ bool decode_plan(const DecodeArgs &a, int b, DecodePl
     p.off = uniform_i32(a.offsets[p.u]);
     if (a.plan && p.c == 0 && threadIdx.x == 0) a.tab[p.u] = make_int2(0, 0);  // (fixed chunks)
     p.wave_rows = fixed_wave_rows(p.n, a.np);
-    return p.c * (kDecWaves * p.wave_rows) < p.n;
+    return (int64_t)p.c * (kDecWaves * p.wave_rows) < p.n;
 }
 
 template <bool BF16>
@@ -146,7 +146,8 @@ __global__ __launch_bounds__(kDecThreads, BF ? 3 : 2) void k_decode(DecodeArgs a
     __shared__ __attribute__((aligned(16))) float pt[kDecWaves][BR][QP];
     const int z = blockIdx.y;
     DecodePlan pl;
-    if (!decode_plan(a, blockIdx.x, pl)) return;  // (the whole block)
+    const int block = blockIdx.z * kGridX + blockIdx.x;
+    if (!decode_plan(a, block, pl)) return;  // (the whole block; those past the last too)
     const Unit un = unit_of(pl.u, a.Hkv, a.B);
     const int lane = threadIdx.x & 63, wv = uniform_i32(threadIdx.x >> 6);
     const int r16 = lane & 15, kg = lane >> 4, seg = lane % S, rg = lane / S;
@@ -322,7 +323,7 @@ __global__ __launch_bounds__(kDecThreads, BF ? 3 : 2) void k_decode(DecodeArgs a
                 L += cl[w2][g] * wt;
                 A += cacc[w2][g][d] * wt;
             }
-        float *pp = a.part + ((int64_t)blockIdx.x * a.G + z * QG + g) * (D + 2);
+        float *pp = a.part + ((int64_t)block * a.G + z * QG + g) * (D + 2);
         pp[2 + d] = A;
         if (d == 0) {
             pp[0] = M;
@@ -344,7 +345,8 @@ template <int kMergeRegs>
 __global__ __launch_bounds__(kMergeThreads) void k_decode_merge(DecodeArgs a)
 {
     __shared__ float wt[kMergeThreads], red[2][kMergeThreads / kWave], osum[kMergeThreads];
-    const int64_t qrow = blockIdx.x;
+    const int64_t qrow = (int64_t)blockIdx.y * kGridX + blockIdx.x;
+    if (blockIdx.y > 0 && qrow >= (int64_t)a.L * a.Hq * a.B) return;
     const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
     const int s = (int)(qrow % a.B), q = (int)((qrow / a.B) % a.Hq), l = (int)(qrow / ((int64_t)a.B * a.Hq));
     const int64_t u = ((int64_t)l * a.Hkv + q / a.G) * a.B + s;
@@ -430,23 +432,26 @@ hipError_t decode_launch(DecodeArgs a, char *ws, size_t ws_bytes, bool bf16, hip
     if (U == 0) return hipSuccess;
     DecodeGrid g = decode_grid(U, a.G, a.D, a.max_count, false);
     if (ws_bytes < g.bytes) g = decode_grid(U, a.G, a.D, a.max_count, true);
-    if (g.blocks > INT32_MAX) return hipErrorInvalidConfiguration;
+    if (g.blocks > INT32_MAX - kGridX) return hipErrorInvalidConfiguration;
     a.plan = g.plan;
     a.np = g.np;
     a.part = reinterpret_cast<float *>(ws);
     a.tab = g.plan ? reinterpret_cast<int2 *>(ws + g.bytes - sizeof(int2) * (size_t)U) : nullptr;
-    const dim3 grid((unsigned)g.blocks, decode_head_groups(a.G));
+    auto along_x = [](int64_t n) { return (unsigned)(n < kGridX ? n : kGridX); };
+    auto rest = [](int64_t n) { return (unsigned)((n + kGridX - 1) / kGridX); };
+    const dim3 grid(along_x(g.blocks), decode_head_groups(a.G), rest(g.blocks));
     if (bf16 && a.D == 128) ECOKV_TIMED("decode", st, (launch_dec<true, 128>(a, grid, st)));
     else if (bf16) ECOKV_TIMED("decode", st, (launch_dec<true, 64>(a, grid, st)));
     else if (a.D == 128) ECOKV_TIMED("decode", st, (launch_dec<false, 128>(a, grid, st)));
     else ECOKV_TIMED("decode", st, (launch_dec<false, 64>(a, grid, st)));
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const unsigned rows = (unsigned)((int64_t)a.L * a.Hq * a.B);
+    const int64_t rows = (int64_t)a.L * a.Hq * a.B;
+    const dim3 merge(along_x(rows), rest(rows));
     if (rows >= 512)
-        ECOKV_TIMED("decode_merge", st, hipLaunchKernelGGL(k_decode_merge<8>, dim3(rows), dim3(kMergeThreads), 0, st, a));
+        ECOKV_TIMED("decode_merge", st, hipLaunchKernelGGL(k_decode_merge<8>, merge, dim3(kMergeThreads), 0, st, a));
     else
-        ECOKV_TIMED("decode_merge", st, hipLaunchKernelGGL(k_decode_merge<16>, dim3(rows), dim3(kMergeThreads), 0, st, a));
+        ECOKV_TIMED("decode_merge", st, hipLaunchKernelGGL(k_decode_merge<16>, merge, dim3(kMergeThreads), 0, st, a));
     return hipGetLastError();
 }
 

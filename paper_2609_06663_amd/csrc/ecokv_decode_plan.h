@@ -16,6 +16,7 @@ constexpr int kDecChunk = kDecWaves * kWaveRows;
 constexpr int kDecQG = 8;         // query heads per block at most
 constexpr int kOneRound = 256;    // blocks that give every compute unit one
 constexpr int kOneRows = 128;     // rows per wave up to which one round is enough
+constexpr int kGridX = 1 << 20;   // blocks along x at most: a dimension's threads past 2^32 would wrap round
 constexpr int kPlanPer = 4;       // units per lane of a balanced plan
 constexpr int kPlanUnits = kPlanPer * 64;  // and at most
 

@@ -198,3 +198,34 @@ def test_decode_plans(dtype, D, Hq, Hkv, B, counts, max_count):
     np.testing.assert_allclose(outs[0][1][0][keep], outs[1][1][0][keep], atol=1e-5, rtol=1e-6)
     if not empty.any():
         check(c, *outs[0], 1, Hq, Hkv, B, D, dtype)
+
+
+@pytest.mark.parametrize("units", [256, 257])
+def test_decode_loose_max_count_of_many_blocks(units):
+    # a bound of 50 million rows: 65 600 chunks per unit, more blocks in all
+    # (16.8 million) than one grid dimension of 2^32 threads holds.  One long
+    # unit, whose fixed chunks reach past the blocks that such a dimension
+    # wraps round to (256 units would take a balanced plan for fewer rows)
+    L, D, max_count = 1, 64, 768 * 65600
+    counts = [1 + i % 9 for i in range(units)]
+    counts[units // 2] = 600_000
+    c = make_cache(21, L, units, units, 1, D, counts, "bf16")
+    say(f"{units} units, max_count {max_count}")
+    O, lse = run(c, L, units, units, 1, D, "bf16", max_count=max_count)
+    check(c, O, lse, L, units, units, 1, D, "bf16")
+
+
+def test_decode_many_query_rows():
+    # 16.8 million query rows: more blocks of the merge than one grid dimension
+    # holds.  Every unit reads the same row, whose V is then every output
+    import paper_2609_06663_amd as P
+    L, Hq, Hkv, B, D = 4097, 64, 1, 64, 64
+    say(f"{L * Hq * B} query rows")
+    shape = P.Shape(L, Hq, Hkv, D, 1, [2 * s for s in range(B + 1)])
+    Q = torch.zeros(L, Hq, B, D, dtype=torch.bfloat16, device="cuda")
+    Kc, Vc = (torch.arange(D, dtype=torch.bfloat16, device="cuda").view(1, D) + x for x in (1, 2))
+    n = torch.ones(shape.units, dtype=torch.int32, device="cuda")
+    O = torch.full((L, Hq, B, D), -7.0, device="cuda")
+    lse = torch.full((L, Hq, B), -7.0, device="cuda")
+    P.ecokv_decode(Q, Kc, Vc, shape, n, torch.zeros_like(n), 1, O, lse)
+    assert bool((O == Vc[0].float()).all()) and bool((lse == 0).all())
