@@ -477,7 +477,9 @@ def ecokv_decode(Q_dec: torch.Tensor, Kc: torch.Tensor, Vc: torch.Tensor, shape:
     """Enqueue ecokv_decode (attention of one query per head over the compressed cache).
     The rows each unit reads (offsets[u] .. + counts[u]) are device values the
     binding cannot see; the caller guarantees they lie inside Kc and Vc, as
-    ecokv_select writes them for a cache that ecokv_compact filled."""
+    ecokv_select writes them for a cache that ecokv_compact filled.
+    `workspace`: ecokv_decode_workspace_size bytes, or fewer down to one chunk
+    of rows for every 768 of max_count."""
     if Kc.dtype != Q_dec.dtype or Vc.dtype != Q_dec.dtype:
         raise TypeError("Q_dec, Kc and Vc must share one element type")
     c = shape.c
@@ -489,6 +491,8 @@ def ecokv_decode(Q_dec: torch.Tensor, Kc: torch.Tensor, Vc: torch.Tensor, shape:
     nq = c.num_layers * c.num_q_heads * c.num_seqs
     if Kc.numel() % D or Vc.numel() != Kc.numel():
         raise ValueError("Kc and Vc must hold the same whole number of rows of head_dim elements")
+    if workspace is not None:  # what the call can do with (a size held for another shape, say)
+        need = 4 * nq * -(-int(max_count) // 768) * (D + 2)
     workspace = _workspace(workspace, need, dev, stream)
     _check(lib.ecokv_decode(_arg(Q_dec, "Q_dec", _KV_TYPES, nq * D, dev), _arg(Kc, "Kc", _KV_TYPES, D, dev),
                             _arg(Vc, "Vc", _KV_TYPES, D, dev), _dtype_code(Q_dec), ctypes.byref(shape.c),

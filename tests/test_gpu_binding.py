@@ -55,6 +55,36 @@ def test_wrong_types_and_sizes_are_refused():
     torch.cuda.synchronize()
 
 
+@pytest.mark.parametrize("held_units,units,max_count", [(6, 6, 2400), (257, 256, 2304)])
+def test_decode_with_a_workspace_of_its_least_size(held_units, units, max_count):
+    # the header's least: one chunk for every 768 rows of max_count.  A caller
+    # may hold such a workspace, or one sized for a shape with more units (256
+    # units ask for more than 257 do); one byte less is refused
+    import paper_2609_06663_amd as P
+    D, G = 64, 2
+    say(f"decode of {units} units, max_count {max_count}, in a workspace for {held_units}")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    rows = 900
+    Kc, Vc = (torch.randn(rows, D, generator=g, device="cuda", dtype=torch.float32) for _ in range(2))
+    Q = torch.randn(1, G * units, 1, D, generator=g, device="cuda", dtype=torch.float32)
+    n = torch.full((units,), rows, dtype=torch.int32, device="cuda")  # every unit the same rows
+    off = torch.zeros(units, dtype=torch.int32, device="cuda")
+    shape = P.Shape(1, G * units, units, D, 1, [0, 2])
+    held = P.Shape(1, G * held_units, held_units, D, 1, [0, 2])
+    least = 4 * G * units * ((max_count + 767) // 768) * (D + 2)
+    size = least if held_units == units else P.ecokv_decode_workspace_size(held, max_count)
+    assert least <= size < P.ecokv_decode_workspace_size(shape, max_count)
+    O = torch.full((1, G * units, 1, D), -7.0, device="cuda")
+    P.ecokv_decode(Q, Kc, Vc, shape, n, off, max_count, O, workspace=torch.zeros(size, dtype=torch.uint8, device="cuda"))
+    ref = torch.softmax(Q[0, :, 0].double() @ Kc.double().t() / 8.0, 1) @ Vc.double()
+    assert (O[0, :, 0] - ref).abs().max() <= 1e-4 * Vc.abs().max()
+    with pytest.raises(ValueError, match="workspace has"):
+        P.ecokv_decode(Q, Kc, Vc, shape, n, off, max_count, O,
+                       workspace=torch.zeros(least - 1, dtype=torch.uint8, device="cuda"))
+    torch.cuda.synchronize()
+
+
 def test_forced_wait_timeout_is_reported(monkeypatch):
     import paper_2609_06663_amd as P
     from paper_2609_06663_amd.pipeline import EvictionPass
