@@ -268,6 +268,14 @@ __device__ __forceinline__ float groups_sum4(float a, float b, float c, float d)
     return fold16(fold32(a, c), fold32(b, d));
 }
 
+// 2^x down to the least subnormal; v_exp_f32 gives zero below kExpLeast.
+constexpr float kExpLeast = -126.f;
+__device__ __forceinline__ float exp2_subnormal(float x)
+{
+    const bool low = x < kExpLeast;  // (x + 64 is exact there)
+    return fast::fast_exp2(low ? x + 64.f : x) * (low ? 0x1p-64f : 1.f);
+}
+
 __device__ __forceinline__ float groups_sum(float x)
 {
     return across32(across16(x, OpAdd{}), OpAdd{});
@@ -537,11 +545,28 @@ __global__ __launch_bounds__(kThreads, 2) void k_rows2(ScoreArgs a)
                 }
             }
             if constexpr (MT == 4) load_rows();
+            // Keys whose attention falls below the least normal float still rank by
+            // it: rare enough that a wave does them over.  (Not with 128-wide bf16
+            // keys: the streaming kernels of that shape have zero there, and with four
+            // tiles it would spill 31 registers.)
+            constexpr bool kSubnormal = !(BF && D == 128);
+            float least = 0.f;
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    att = fmaf(fast::fast_exp2(fmaf(acc[mt][nt][r], sc, -rm[mt][r])), rs[mt][r], att);
+                for (int r = 0; r < 4; ++r) {
+                    const float x = fmaf(acc[mt][nt][r], sc, -rm[mt][r]);
+                    least = fminf(least, x);
+                    att = fmaf(fast::fast_exp2(x), rs[mt][r], att);
+                }
+            if (kSubnormal && __builtin_amdgcn_ballot_w64(least < kExpLeast)) {
+                att = 0.f;
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        att = fmaf(exp2_subnormal(fmaf(acc[mt][nt][r], sc, -rm[mt][r])), rs[mt][r], att);
+            }
             // totals over the four lane groups, one per group: |k - kbar|^2, k.mu,
             // |k|^2 and the attention of key lane % 16
             const float t4 = groups_sum4((d2p[0] + d2p[1]) + (d2p[2] + d2p[3]), (kmp[0] + kmp[1]) + (kmp[2] + kmp[3]),

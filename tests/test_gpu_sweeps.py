@@ -122,3 +122,28 @@ def test_keys_at_any_element(D):
     shape = P.Shape(2, 8, 2, D, 4, cu)
     for a, b in zip(scores(shape, K, Q), scores(shape, K1, Q1)):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("dtype,D", [("f32", 64), ("f32", 128), ("bf16", 64)])
+def test_attention_below_the_least_normal(dtype, D):
+    # keys whose attention falls by half from one to the next, past 2^-126 (the
+    # least normal float) to 2^-149 (the least of all).  With lambda 0 and no
+    # pooling the score is the attention itself.  The base-2 logits, up to 150,
+    # round by 2^-24 of themselves a few times (1e-4 of the weight at most); a
+    # subnormal weight rounds to multiples of 2^-149 a few times on its way
+    import paper_2609_06663_amd as P
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    T, step = 240, 0.69921875
+    say(f"{dtype} D={D}: subnormal attention")
+    t = -torch.arange(T, dtype=torch.float64)
+    K = torch.zeros(1, 1, T, D, dtype=torch.float64)
+    K[..., 0], K[..., 1] = t, 1.0
+    Q = torch.zeros(1, 1, 1, 1, D, dtype=torch.float64)
+    Q[..., 0] = step * math.sqrt(D)  # (bf16, 64 dimensions: 5.59375, exact)
+    shape = P.Shape(1, 1, 1, D, 1, [0, T])
+    S = torch.full((T - 1,), math.nan, device="cuda")
+    P.ecokv_score(K.to(tdt).cuda(), Q.to(tdt).cuda(), shape, P.Params(lambda_override=0.0, pool_kernel=1), S)
+    x = step * t
+    ref = (x - x.logsumexp(0)).exp()[:T - 1].numpy()
+    err = abs(S.cpu().numpy().astype("f8") - ref)
+    assert (err <= 1e-4 * ref + 4 * 2.0 ** -149).all(), int((err / (1e-4 * ref + 4 * 2.0 ** -149)).argmax())
