@@ -231,8 +231,8 @@ __global__ __launch_bounds__(kDecThreads, BF ? 3 : 2) void k_decode(DecodeArgs a
             x[r] = b0 + 4 * kg + r < nrows ? cc[r] * a.qscale : -INFINITY;
             mb = fmaxf(mb, x[r]);
         }
-        mb = across32(across16(mb, OpMax{}), OpMax{});  // finite: row b0 is valid
-        const bool move = mb > m + kDecRebase;      // (always in the first tile: m = -inf)
+        mb = across32(across16(mb, OpMax{}), OpMax{});
+        const bool move = mb > m + kDecRebase;      // (from m = -inf: with the first finite logit)
         if (__builtin_amdgcn_ballot_w64(move)) {
             const float nm = move ? mb : m;
             const float sc = __builtin_amdgcn_exp2f(m - nm);  // 0 while m = -inf
@@ -245,9 +245,10 @@ __global__ __launch_bounds__(kDecThreads, BF ? 3 : 2) void k_decode(DecodeArgs a
                 for (int e = 0; e < EL; ++e) acc[g][e] *= sg;
             }
         }
+        const float ref = m == -INFINITY ? 0.f : m;  // (weight 0 for logits of -inf, also before any other)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const float p = __builtin_amdgcn_exp2f(x[r] - m);
+            const float p = __builtin_amdgcn_exp2f(x[r] - ref);
             ls += p;
             if (r16 < QG) ptw[(4 * kg + r) * QP + r16] = p;
         }

@@ -229,3 +229,41 @@ def test_decode_many_query_rows():
     lse = torch.full((L, Hq, B), -7.0, device="cuda")
     P.ecokv_decode(Q, Kc, Vc, shape, n, torch.zeros_like(n), 1, O, lse)
     assert bool((O == Vc[0].float()).all()) and bool((lse == 0).all())
+
+
+@pytest.mark.parametrize("dtype,D", [("bf16", 128), ("bf16", 64), ("f32", 128), ("f32", 64)])
+@pytest.mark.parametrize("where", ["one tile", "everywhere"])
+def test_decode_rows_of_weight_zero(dtype, D, where):
+    # rows whose logit is -inf, wherever a wave or a chunk may begin: whole tiles,
+    # the first rows of every 32, whole chunks; the others' attention as if they
+    # were not there
+    import paper_2609_06663_amd as P
+    Hq, Hkv = 28, 4
+    counts = [6553, 40, 1700, 3000]
+    c = make_cache(23, 1, Hq, Hkv, 1, D, counts, dtype)
+    Q, Kc, Vc = dev(c["Q"], dtype), dev(c["Kc"], dtype), dev(c["Vc"], dtype)
+    off = c["offsets"].reshape(-1)
+    dead = torch.zeros(len(Kc), dtype=torch.bool, device="cuda")
+    dead[off[0] + 32:off[0] + 48] = True
+    if where == "everywhere":
+        dead[off[0] + 200:off[0] + 1100] = True
+        dead[off[1] + 16:off[1] + 32] = True
+        j = torch.arange(counts[2], device="cuda")
+        dead[off[2]:off[2] + counts[2]] = (j % 32 < 16) & (j >= 32)
+        dead[off[3] + 2900:off[3] + 3000] = True
+    Q[..., 0] = 1.0
+    Kc[dead, 0] = -float("inf")
+    say(f"{dtype} D={D}, {where}: {int(dead.sum())} of {len(Kc)} rows with logit -inf")
+    shape = P.Shape(1, Hq, Hkv, D, 1, [0, 2])
+    n, o = (torch.from_numpy(c[k].reshape(-1)).cuda() for k in ("counts", "offsets"))
+    O = torch.full((1, Hq, 1, D), -7.0, device="cuda")
+    lse = torch.full((1, Hq, 1), -7.0, device="cuda")
+    P.ecokv_decode(Q, Kc, Vc, shape, n, o, 6553, O, lse)
+    for q in range(Hq):
+        u = q // (Hq // Hkv)
+        rows = slice(off[u], off[u] + counts[u])
+        x = (Kc[rows].double().masked_fill(dead[rows, None], 0.0) @ Q[0, q, 0].double()) / D ** 0.5
+        x.masked_fill_(dead[rows], -float("inf"))
+        ref = x.softmax(0) @ Vc[rows].double()
+        assert (O[0, q, 0] - ref).abs().max() <= 1e-4 * Vc[rows].abs().max(), (u, q)
+        assert (lse[0, q, 0] - x.logsumexp(0)).abs() <= 1e-4 * max(1.0, float(x.logsumexp(0).abs())), (u, q)
