@@ -318,12 +318,13 @@ __global__ __launch_bounds__(kDecThreads, BF ? 3 : 2) void k_decode(DecodeArgs a
         float M = cm[0][g];
         for (int w2 = 1; w2 < kDecWaves; ++w2) M = fmaxf(M, cm[w2][g]);
         float L = 0.f, A = 0.f;
-        if (M != -INFINITY)
-            for (int w2 = 0; w2 < kDecWaves; ++w2) {
-                const float wt = exp2f(cm[w2][g] - M);
-                L += cl[w2][g] * wt;
-                A += cacc[w2][g][d] * wt;
-            }
+        // (waves without a finite logit add 0, or their NaN, also where all are such)
+        const float ref = M == -INFINITY ? 0.f : M;
+        for (int w2 = 0; w2 < kDecWaves; ++w2) {
+            const float wt = exp2f(cm[w2][g] - ref);
+            L += cl[w2][g] * wt;
+            A += cacc[w2][g][d] * wt;
+        }
         float *pp = a.part + ((int64_t)block * a.G + z * QG + g) * (D + 2);
         pp[2 + d] = A;
         if (d == 0) {
@@ -404,12 +405,13 @@ __global__ __launch_bounds__(kMergeThreads) void k_decode_merge(DecodeArgs a)
     osum[t] = o;
     __syncthreads();
     const bool bad = n > a.max_count || n < 0;
+    // (L is 0 without rows and where every logit is -inf, NaN where one is)
     if (t < a.D) {
         for (int g2 = 1; g2 < ngrp; ++g2) o += osum[g2 * a.D + t];
-        a.O[qrow * a.D + t] = bad ? NAN : (M == -INFINITY ? 0.f : o / L);
+        a.O[qrow * a.D + t] = bad ? NAN : (L == 0.f ? 0.f : o / L);
     }
     if (t == 0 && a.lse)
-        a.lse[qrow] = bad ? NAN : (M == -INFINITY ? -INFINITY : (M + log2f(L)) * 0.69314718055994531f);
+        a.lse[qrow] = bad ? NAN : (L == 0.f ? -INFINITY : (M + log2f(L)) * 0.69314718055994531f);
 }
 
 template <bool BF, int D>

@@ -267,3 +267,25 @@ def test_decode_rows_of_weight_zero(dtype, D, where):
         ref = x.softmax(0) @ Vc[rows].double()
         assert (O[0, q, 0] - ref).abs().max() <= 1e-4 * Vc[rows].abs().max(), (u, q)
         assert (lse[0, q, 0] - x.logsumexp(0)).abs() <= 1e-4 * max(1.0, float(x.logsumexp(0).abs())), (u, q)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("rows", [(0, 128), (40, 41), (0, 6553)])
+def test_decode_nan_rows_reach_the_output(dtype, rows):
+    # NaN keys in one unit, down to a whole chunk of them: its outputs are NaN
+    # however the rows are split, the other units' finite
+    import paper_2609_06663_amd as P
+    Hq, Hkv, D = 28, 4, 128
+    c = make_cache(24, 1, Hq, Hkv, 1, D, [2000, 6553, 40, 3000], dtype)
+    Kc = dev(c["Kc"], dtype)
+    Kc[2000 + rows[0]:2000 + rows[1], 5] = float("nan")
+    say(f"{dtype}: NaN in rows {rows} of unit 1")
+    shape = P.Shape(1, Hq, Hkv, D, 1, [0, 2])
+    n, o = (torch.from_numpy(c[k].reshape(-1)).cuda() for k in ("counts", "offsets"))
+    O = torch.full((1, Hq, 1, D), -7.0, device="cuda")
+    lse = torch.full((1, Hq, 1), -7.0, device="cuda")
+    P.ecokv_decode(dev(c["Q"], dtype), Kc, dev(c["Vc"], dtype), shape, n, o, 6553, O, lse)
+    bad = torch.zeros(Hq, dtype=torch.bool, device="cuda")
+    bad[7:14] = True
+    assert bool(O[0, bad].isnan().all()) and bool(lse[0, bad].isnan().all())
+    assert bool(O[0, ~bad].isfinite().all()) and bool(lse[0, ~bad].isfinite().all())
