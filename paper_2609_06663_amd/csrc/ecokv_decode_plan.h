@@ -61,8 +61,10 @@ __host__ __device__ inline int unit_chunks(int n, int wave_rows)
 
 // Chunks, blocks (per group of query heads) and workspace of a call.
 //  * `least`, what any call can do with: one chunk for every kDecChunk rows of
-//    max_count.  All that calls of at most two such chunks ask for: their
-//    callers hold workspaces of exactly that size.
+//    max_count.  Calls of at most two such chunks (max_count up to 1536) ask
+//    for no more: the size returned for them is part of the interface (the ABI
+//    tests hold it), so they are split no finer, however idle the device: 4
+//    units of 1536 rows are 8 blocks, 4 of 1537 rows 52.
 //  * chunks of kMinWaveRows rows per wave where max_count rows in every unit
 //    make at most one round of them;
 //  * else a balanced plan: at most one chunk per unit more than its rows

@@ -67,10 +67,10 @@ struct ScoreArgs {
     float *bufB;     // [L][Hkv][Ptot]      khat.mu
     float *bufC;     // [L][Hkv][Ptot]      window-mean attention a
     float *bufV;     // [L][Hkv][Ptot]      pool(a) * |v| (vnorm only)
-    // values the two blocks of a unit's split epilogue exchange, each a 64-bit
-    // word (launch tag << 32 | float bits) so that a reader can tell a value of
-    // this launch from anything older without ordering fences
-    unsigned long long *epiT;   // [U][4][4]           per-part S_div / S_imp sums and extrema
+    // values the SPLIT (2, 4 or 8) blocks of a unit's split epilogue exchange,
+    // each a 64-bit word (call tag << 32 | float bits) so that a reader can tell
+    // a value of this call from anything older without ordering fences
+    unsigned long long *epiT;   // [U][SPLIT][4]       per-part S_div / S_imp sums and extrema
     unsigned *status;           // workspace status word: set to the call's tag if a wait ran out of time
     unsigned *tagw;             // workspace word: the call's tag (bumped by the second sweep, never 0)
     int spin_limit;             // polls of a bounded wait before it gives up (<= 0: give up at once)
@@ -221,9 +221,6 @@ void sweep_rows_launch(int pass, const ScoreArgs &a, dim3 grid, hipStream_t st);
 
 WsLayout score_ws_layout(int L, int Hkv, int B, int D, int R, int64_t Ptot, int maxT, bool bf16, bool vnorm);
 hipError_t score_launch(ScoreArgs a, char *ws, const WsLayout &lay, int maxT, hipStream_t st, bool bf16);
-
-// A launch tag (never 0), distinct for every launch of the process: values a
-// launch publishes between its blocks carry it.
 
 // ecokv_prefill_write: workspace bytes, and the launches (a.K = the cache,
 // a.Ksrc = the new rows, a.pre_out = pre; Vsrc / Vdst may be null).

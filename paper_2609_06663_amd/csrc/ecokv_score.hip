@@ -309,13 +309,11 @@ __global__ __launch_bounds__(256, 2) void k_fs2s(ScoreArgs a)
 //    block with rows (1, 1/|k| high, remainder, 0...) over the wave's 32 keys
 //    as A, and the keys transposed out of the stage with ds_read_b64_tr_b16
 //    as B.
-constexpr float kRebase1 = 16.f;  // log2 headroom of the lazily moved row reference
-
-//
 // With CACHE (the KV-cache write of ecokv_prefill_write), each key row is read
 // from the token-major new rows a.Ksrc and the loaded registers are written to
 // the head-major cache a.K on arrival, before the group is used: one read and
 // one write of K, and the sweep rides on them.
+constexpr float kRebase1 = 16.f;  // log2 headroom of the lazily moved row reference
 template <bool CACHE>
 __global__ __launch_bounds__(256, 2) void k_fs1s(ScoreArgs a)
 {
@@ -512,9 +510,6 @@ __global__ __launch_bounds__(256, 2) void k_fs1s(ScoreArgs a)
 constexpr int kReduceThreads = 1024;
 inline int reduce1_lanes(int nch1) { return nch1 > 16 ? 16 : 4; }
 
-// With PRE (ecokv_prefill_write) the unit's sums are written to a.pre_out in
-// the layout ecokv_score_pre takes: plain sums, and the row maxima in natural
-// units (max q.k / sqrt(D)).
 // op over an aligned group of 4 or 16 lanes (a quad, a DPP row), every lane
 // getting the result.
 template <int LANES, class Op>
@@ -528,6 +523,9 @@ __device__ __forceinline__ float lane_group_reduce(float x, Op op)
 
 // Columns cg, cg + ncg, ... (in groups of blockDim.x / LANES) of unit u's
 // partials, LANES lanes per column; the calling block's threads all take part.
+// With PRE (ecokv_prefill_write) the unit's sums are written to a.pre_out in
+// the layout ecokv_score_pre takes: plain sums, and the window rows'
+// references in natural units (of q.k / sqrt(D)).
 template <int LANES, bool PRE>
 __device__ __forceinline__ void reduce1_columns(const ScoreArgs &a, int u, int cg, int ncg)
 {
@@ -1400,7 +1398,7 @@ hipError_t score_launch(ScoreArgs a, char *ws, const WsLayout &lay, int maxT, hi
         }
         if ((e = hipGetLastError()) != hipSuccess) return e;
         if (score_fast_path(a.D, bf16) && a.R <= kStreamMaxRows) {
-            // streaming sweep 2: window rows and the four anchor rows in one operand
+            // streaming sweep 2: window rows and the two rows of mu in one operand
             a.rpb2 = stream_block_keys(a);
             a.nch2 = (maxT + a.rpb2 - 1) / a.rpb2;
             ECOKV_TIMED("sweep2_stream", st,

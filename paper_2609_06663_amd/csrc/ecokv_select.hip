@@ -600,7 +600,6 @@ __device__ __forceinline__ void block_exscan2(uint32_t x0, uint32_t x1, uint32_t
 }
 
 // Scores of one selection group: head h's non-window scores at base + h * hstride
-
 // (a single head in per-head mode: no division on that path; a group has at
 // most kMaxFlatHeads * 2^31 keys, so the head index fits 32 bits).
 struct GroupView {
@@ -615,9 +614,6 @@ struct GroupView {
         return base[(int64_t)h * hstride + (v - (int64_t)h * P)];
     }
 };
-
-
-// The selection group of this block: layer l, heads h0 .. h0+nh-1 of
 
 
 // Ordered emission of one head's chosen keys from the registers (thread t
@@ -667,23 +663,22 @@ __device__ __forceinline__ void emit_ordered(const uint32_t (&kk)[KPT], int v0, 
 // One block per group, for groups of up to 32 Ki keys (each a handful of
 // launches' worth of work for the multi-block form below): thread t owns the
 // contiguous run [t*KPT, t*KPT + KPT) of the group's keys in registers
-// (16-byte loads in per-head mode), the radix passes histogram them into one
-// LDS copy per wave, and the ordered emission walks the registers.
+// (16-byte loads in per-head mode), the radix select counts and lists them in
+// LDS, and the ordered emission walks the registers.
 // ---------------------------------------------------------------------------
 
 template <int KPT>
 __global__ __launch_bounds__(kSelThreads) void k_select_reg(SelectArgs a)
 {
-    // the radix histograms and the listed keys live in stg
     __shared__ uint32_t h1[256];
     __shared__ uint32_t bc[2][3];
     __shared__ uint32_t wsum[2 * kSelWaves + 2];
     __shared__ uint32_t mm[2][kSelWaves];
     __shared__ int64_t through[kMaxFlatHeads];
     typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
-    // With KPT == 32 the stage of the coalesced score load, then of
-    // the radix histograms and listed keys, then of the output (the barriers
-    // of the extremes and of the radix passes separate the three uses)
+    // the radix histograms and the listed keys; with KPT == 32 before them the
+    // stage of the coalesced score load, after them that of the output (the
+    // barriers after the load and of the radix passes separate the three uses)
     __shared__ u32x4_t stg[KPT * kSelThreads / 4];
 
     const SelGroup grp = sel_group(a, blockIdx.x);

@@ -56,7 +56,7 @@ def test_alternative_bf16_d128(name):
 
 @pytest.mark.parametrize("name", ["winsor5", "mad", "rstd", "prefix"])
 def test_alternative_f32_d64(name):
-    # the block sweeps (fp32 keys, head_dim 64) carry the same partials
+    # the row sweeps (fp32 keys, head_dim 64) carry the same partials
     wl = W.custom(82, L=1, Hq=4, Hkv=2, D=64, w=8, seqlens=[900, 131], dtype="f32", budget=[200, 40], group=32)
     say(f"{name}: fp32 head_dim 64")
     p = opts(name)

@@ -76,14 +76,15 @@ def check(c, O, lse, L, Hq, Hkv, B, D, dtype):
 @pytest.mark.parametrize("dtype,D,Hq,Hkv", [("bf16", 128, 28, 4), ("bf16", 64, 8, 8), ("f32", 128, 8, 4),
                                             ("f32", 64, 12, 4), ("bf16", 128, 32, 2), ("bf16", 128, 24, 2)])
 def test_decode_ragged(dtype, D, Hq, Hkv):
-    # G = 7, 1, 2, 3, 16 (two blocks of 8 query heads), 12 (8 + 4)
+    # G = 7, 1, 2, 3, 16 (two blocks of 8 query heads), 12 (8 + 4); counts from
+    # one row to a few chunks
     L, B = 2, 3
     r = np.random.default_rng(100 + Hq)
     counts = r.integers(1, 2600, size=(L, Hkv, B))
     counts.reshape(-1)[0] = 1                     # one row
-    counts.reshape(-1)[-1] = 1024                 # exactly one chunk
+    counts.reshape(-1)[-1] = 1024                 # whole tiles
     if counts.size > 2:
-        counts.reshape(-1)[1] = 257               # one row past a wave's share
+        counts.reshape(-1)[1] = 257               # one row past whole tiles
     c = make_cache(7, L, Hq, Hkv, B, D, counts, dtype, kscale=2.0)
     say(f"{dtype} D={D} Hq={Hq} Hkv={Hkv}: ragged counts up to {int(counts.max())}")
     O, lse = run(c, L, Hq, Hkv, B, D, dtype)
@@ -149,7 +150,7 @@ PLAN_CASES = [
     ("f32", 64, 32, 16, 4, list(range(60, 60 + 64 * 113, 113)), 9001, "balanced 128"),
     ("bf16", 64, 8, 8, 8, [6144 + 31 * i for i in range(64)], 12000, "balanced 192"),
     ("bf16", 64, 8, 8, 8, [12000 - i for i in range(64)], 12000, "fixed"),
-    # two groups of query heads; one unit more than a plan takes
+    # two groups of query heads in fixed chunks; one unit more than a plan takes
     ("bf16", 64, 48, 4, 1, [3000, 20, 900, 1700], 3000, "fixed"),
     ("f32", 64, 257, 257, 1, [1600 + i % 7 for i in range(257)], 1606, "fixed"),
     # balanced plans whose chunks take two, three and eight groups of query heads

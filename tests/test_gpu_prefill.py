@@ -101,7 +101,7 @@ def check_cache(wl, Kc, Vc, with_v=True):
 @pytest.mark.parametrize("dtype,D,Hq,Hkv,w,seqlens", [
     ("bf16", 128, 28, 4, 4, [3000, 517, 1200]),   # streaming sweep with the cache write (512-key blocks)
     ("bf16", 128, 8, 8, 8, [4100]),               # one query head per KV head, R = 8
-    ("bf16", 128, 32, 4, 8, [2100, 700]),         # R = 64: copy, then the block sweep
+    ("bf16", 128, 32, 4, 8, [2100, 700]),         # R = 64: copy, then the row sweep
     ("f32", 64, 4, 2, 8, [1500, 333, 70]),        # fp32 keys
     ("bf16", 64, 8, 2, 4, [2000, 9]),             # head_dim 64; a sequence just past the window
 ])
