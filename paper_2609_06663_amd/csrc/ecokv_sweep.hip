@@ -259,6 +259,29 @@ __device__ __forceinline__ void tile_operand(const u32x4 *wst, int nt, int lane,
     for (int st = 0; st < G::NCH; ++st) kx[st] = wst[G::pos(16 * nt + (lane & 15), 4 * st + (lane >> 4))];
 }
 
+// v_sqrt_f32 errs by up to 0.9 of a last place and by 0.16 downwards on
+// average, v_rsq_f32 by 0.1: the same way for all keys of about the same
+// length, so that sums over keys keep it.  A Newton step each leaves a rounding
+// of either sign (4096 lengths: d_E within 0.5 of a last place; 1 / |k| off by
+// 0.005 x 2^-24 on average instead of 0.10) for 1 % of a call of 64-wide keys
+// (12 layers of 4 heads x 16384: 64.9 -> 65.5 us).  128-wide bf16 keys keep the
+// plain instructions, as in the streaming kernels.
+template <bool BF, int D>
+constexpr bool kRefine = !(BF && D == 128);
+
+// 1 / sqrt(x), 1e-37 <= x < infinity.
+__device__ __forceinline__ float rsq_refined(float x)
+{
+    const float r = __builtin_amdgcn_rsqf(x);
+    return fmaf(0.5f * r, fmaf(-(x * r), r, 1.f), r);
+}
+// sqrt(x) from r = 1 / sqrt(x).
+__device__ __forceinline__ float sqrt_refined(float x, float r)
+{
+    const float s = x * r;
+    return fmaf(0.5f * r, fmaf(-s, s, x), s);
+}
+
 // Sums over the four 16-lane groups of four values at once: group 0 gets the
 // total of a over the lanes of its column, group 1 of b, group 2 of c and
 // group 3 of d.  Each swap gives both halves of two values to one addition:
@@ -379,7 +402,9 @@ __global__ __launch_bounds__(kThreads, 2) void k_rows1(ScoreArgs a)
             tile_operand<BF, D>(wst, nt, lane, q);
 #pragma unroll
             for (int st = 0; st < G::NCH; ++st) n2 = sq_chunk<BF>(q[st], n2);
-            const float inv = __builtin_amdgcn_rsqf(fmaxf(groups_sum(n2), 1e-24f));
+            const float len2 = groups_sum(n2);
+            const float inv = kRefine<BF, D> ? rsq_refined(__builtin_amdgcn_fmed3f(len2, 1e-24f, 3e38f))
+                                             : __builtin_amdgcn_rsqf(fmaxf(len2, 1e-24f));
 #pragma unroll
             for (int st = 0; st < G::NCH; ++st) {
                 float v[G::EL];
@@ -571,8 +596,18 @@ __global__ __launch_bounds__(kThreads, 2) void k_rows2(ScoreArgs a)
             // |k|^2 and the attention of key lane % 16
             const float t4 = groups_sum4((d2p[0] + d2p[1]) + (d2p[2] + d2p[3]), (kmp[0] + kmp[1]) + (kmp[2] + kmp[3]),
                                          (n2p[0] + n2p[1]) + (n2p[2] + n2p[3]), att);
-            const float root = BF ? __builtin_amdgcn_sqrtf(t4) : sqrtf(t4);  // group 0: d_E; group 2: |k|
-            const float len = BF ? __builtin_amdgcn_rsqf(fmaxf(t4, 1e-24f)) : fmaxf(root, 1e-12f);
+            float root, len;  // group 0: d_E; group 2: 1 / |k| (bf16), |k|
+            if constexpr (!BF) {
+                root = sqrtf(t4);
+                len = fmaxf(root, 1e-12f);
+            } else if constexpr (kRefine<BF, D>) {
+                const float r = rsq_refined(__builtin_amdgcn_fmed3f(t4, 1e-37f, 3e38f));
+                root = sqrt_refined(t4, r);
+                len = fminf(r, 1e12f);
+            } else {
+                root = __builtin_amdgcn_sqrtf(t4);
+                len = __builtin_amdgcn_rsqf(fmaxf(t4, 1e-24f));
+            }
             const float klen = __shfl(len, 32 + (lane & 15), kWave);
             const float val = g4 == 0 ? root : g4 == 1 ? (BF ? t4 * klen : t4 / klen) : t4 * inv_r;
             const int gi = key0 + 16 * t + (lane & 15);

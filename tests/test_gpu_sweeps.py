@@ -147,3 +147,44 @@ def test_attention_below_the_least_normal(dtype, D):
     ref = (x - x.logsumexp(0)).exp()[:T - 1].numpy()
     err = abs(S.cpu().numpy().astype("f8") - ref)
     assert (err <= 1e-4 * ref + 4 * 2.0 ** -149).all(), int((err / (1e-4 * ref + 4 * 2.0 ** -149)).argmax())
+
+
+@pytest.mark.parametrize("dtype,D", [("f32", 64), ("f32", 128), ("bf16", 64)])
+def test_lengths_are_rounded_not_approximated(dtype, D):
+    # Keys of components 1, a, b, whose squared length is exact in fp32.
+    #  * Two equal keys: their sum of k / |k| at the component 1 is 2 / |k|.  Its
+    #    error is that of a square root and a quotient (2^-24 of the value each at
+    #    most) and evens out over the lengths: 4096 errors of 0.5 x 2^-24 leave a
+    #    mean of 0.008, 0.05 is six times that.
+    #  * k, -k and a window key of 0: their centroid is 0 and d_E = |k|, the
+    #    rounded square root (a last Newton step may miss it by a hair).
+    import numpy as np
+    import paper_2609_06663_amd as P
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    L, Hkv, G, B = 4, 16, 4, 64
+    U = L * Hkv * B
+    rng = np.random.default_rng(5)
+    ab = rng.integers(1, 256, size=(U, 2)) / 128.0
+    length = np.sqrt(1.0 + (ab ** 2).sum(1))
+    k = np.zeros((U, D))
+    k[:, 7], k[:, 20], k[:, D - 1] = 1.0, ab[:, 0], ab[:, 1]
+    Q = torch.zeros(L, Hkv * G, B, 1, D, dtype=tdt, device="cuda")
+    say(f"{dtype} D={D}: 1 / |k| and |k|")
+
+    def keys(*rows):
+        return torch.from_numpy(np.ascontiguousarray(np.stack(rows, 1).reshape(L, Hkv, len(rows) * B, D))).to(tdt).cuda()
+
+    K = keys(k, k)
+    shape = P.Shape(L, Hkv * G, Hkv, D, 1, [2 * s for s in range(B + 1)])
+    pre = torch.full((U, 2 * D + 2 * G), math.nan, device="cuda")
+    P.ecokv_prefill_write(K.transpose(1, 2).contiguous(), None, Q, shape, P.Params(), torch.zeros_like(K), None, pre)
+    err = (pre[:, D + 7].double().cpu().numpy() / 2 * length - 1) * 2.0 ** 24
+    assert abs(err).max() <= 2 and abs(err.mean()) <= 0.05, (abs(err).max(), err.mean())
+    shape = P.Shape(L, Hkv * G, Hkv, D, 1, [3 * s for s in range(B + 1)])
+    S = torch.full((shape.score_numel(),), math.nan, device="cuda")
+    st = torch.full((U, P.NSTATS), math.nan, device="cuda")
+    P.ecokv_score(keys(k, -k, 0 * k), Q, shape, P.Params(), S, None, st)
+    d = st[:, [P.STAT["dmin"], P.STAT["dmax"]]].double().cpu().numpy()
+    ulp = np.spacing(length.astype(np.float32)).astype(np.float64)
+    off = abs(d - length[:, None]) / ulp[:, None]
+    assert off.max() <= 0.501, off.max()
