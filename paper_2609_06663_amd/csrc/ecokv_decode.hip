@@ -144,9 +144,10 @@ __global__ __launch_bounds__(kDecThreads, BF ? 3 : 2) void k_decode(DecodeArgs a
     __shared__ float cm[kDecWaves][QG], cl[kDecWaves][QG];
     __shared__ float cacc[kDecWaves][QG][D];
     __shared__ __attribute__((aligned(16))) float pt[kDecWaves][BR][QP];
-    const int z = blockIdx.y;
+    const int index = blockIdx.z * kGridX + blockIdx.x;
+    const DecodePlace place = QG == kDecQG && a.zg > 1 ? decode_place(index, a.zg) : DecodePlace{index, 0};
+    const int block = place.block, z = place.z;
     DecodePlan pl;
-    const int block = blockIdx.z * kGridX + blockIdx.x;
     if (!decode_plan(a, block, pl)) return;  // (the whole block; those past the last too)
     const Unit un = unit_of(pl.u, a.Hkv, a.B);
     const int lane = threadIdx.x & 63, wv = uniform_i32(threadIdx.x >> 6);
@@ -435,14 +436,16 @@ hipError_t decode_launch(DecodeArgs a, char *ws, size_t ws_bytes, bool bf16, hip
     if (U == 0) return hipSuccess;
     DecodeGrid g = decode_grid(U, a.G, a.D, a.max_count, false);
     if (ws_bytes < g.bytes) g = decode_grid(U, a.G, a.D, a.max_count, true);
-    if (g.blocks > INT32_MAX - kGridX) return hipErrorInvalidConfiguration;
+    if (decode_places(g.blocks, decode_head_groups(a.G)) > INT32_MAX - kGridX) return hipErrorInvalidConfiguration;
     a.plan = g.plan;
     a.np = g.np;
     a.part = reinterpret_cast<float *>(ws);
     a.tab = g.plan ? reinterpret_cast<int2 *>(ws + g.bytes - sizeof(int2) * (size_t)U) : nullptr;
     auto along_x = [](int64_t n) { return (unsigned)(n < kGridX ? n : kGridX); };
     auto rest = [](int64_t n) { return (unsigned)((n + kGridX - 1) / kGridX); };
-    const dim3 grid(along_x(g.blocks), decode_head_groups(a.G), rest(g.blocks));
+    a.zg = decode_head_groups(a.G);
+    const int64_t n = decode_places(g.blocks, a.zg);
+    const dim3 grid(along_x(n), 1, rest(n));
     if (bf16 && a.D == 128) ECOKV_TIMED("decode", st, (launch_dec<true, 128>(a, grid, st)));
     else if (bf16) ECOKV_TIMED("decode", st, (launch_dec<true, 64>(a, grid, st)));
     else if (a.D == 128) ECOKV_TIMED("decode", st, (launch_dec<false, 128>(a, grid, st)));

@@ -204,7 +204,8 @@ struct DecodeArgs {
     int2 *tab;            // [U] first block and blocks of each unit (balanced plan)
     int L, Hq, Hkv, G, B, D;
     int max_count;
-    int plan;             // blocks per chunk of a balanced plan (groups of query heads), 0: fixed chunks
+    int zg;               // blocks per chunk (groups of query heads)
+    int plan;             // the same of a balanced plan, 0: fixed chunks
     int np;               // fixed chunks per unit at most
     float qscale;         // log2(e) / sqrt(D)
 };

@@ -19,6 +19,7 @@ CSRC = os.path.join(ROOT, "paper_2609_06663_amd", "csrc")
 SHIM = r"""
 #define __host__
 #define __device__
+#include <vector>
 #include "ecokv_decode_plan.h"
 using namespace ecokv;
 static int chunk_rows(int n, int c, int rows) {  // the rows of chunk c, as the kernel's waves take them
@@ -51,6 +52,21 @@ extern "C" int plan(long long units, int G, int D, int max_count, const int *cou
         out[2] += chunks;
     }
     if (wr > 0 && out[2] > g.blocks) return 5;                           // blocks 0 .. chunks - 1
+    // blocks that find no chunk cost a read of the counts each: with every group
+    // of query heads no more than two rounds past what the units and fixed chunks need
+    const long long zg = decode_head_groups(G), fixed = (units * max_count + kDecChunk - 1) / kDecChunk;
+    if (g.plan && g.blocks * zg > (units + fixed) * zg + 2 * kOneRound + zg) return 6;
+    if (zg > 1) {  // every (chunk, group of query heads) has one place of the launch
+        const long long places = decode_places(g.blocks, (int)zg);
+        if (places < g.blocks * zg || places >= (g.blocks + 8) * zg) return 7;
+        std::vector<char> seen((g.blocks + 8) * zg, 0);
+        for (int i = 0; i < places; ++i) {
+            const DecodePlace p = decode_place(i, (int)zg);
+            if (p.block < 0 || p.block >= g.blocks + 8 || p.z < 0 || p.z >= zg || seen[p.block * zg + p.z]++) return 8;
+        }
+        for (long long i = 0; i < g.blocks * zg; ++i)
+            if (!seen[i]) return 9;
+    }
     return 0;
 }
 """
