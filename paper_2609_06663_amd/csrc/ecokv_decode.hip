@@ -44,6 +44,9 @@ struct DecodePlan {
 __device__ __forceinline__ bool decode_plan(const DecodeArgs &a, int b, DecodePlan &p)
 {
     const int U = a.L * a.Hkv * a.B;
+    // the fixed chunk's, read beside the plan's so that falling back costs no round trip
+    const int fixed_u = b % U;
+    int fixed_n = a.counts[fixed_u], fixed_off = a.offsets[fixed_u];
     if (a.plan) {
         const int lane = threadIdx.x & 63;
         int n[kPlanPer], off[kPlanPer];
@@ -54,12 +57,13 @@ __device__ __forceinline__ bool decode_plan(const DecodeArgs &a, int b, DecodePl
             n[q] = u < U ? a.counts[u] : 0;
             off[q] = u < U ? a.offsets[u] : 0;
         }
+        asm volatile("" : "+s"(fixed_n), "+s"(fixed_off));
 #pragma unroll
         for (int q = 0; q < kPlanPer; ++q) {
             n[q] = max(0, min(n[q], a.max_count));  // more rows than max_count: the merge writes NaN
             sum += (float)n[q];  // (a float: only the rows per wave come from it, alike in every wave)
         }
-        p.wave_rows = uniform_i32(plan_wave_rows(wave_sum(sum), U, a.plan));
+        p.wave_rows = uniform_i32(plan_wave_rows(wave_sum(sum), U, a.plan, a.max_count));
         if (p.wave_rows > 0) {
             int parts[kPlanPer], mine = 0;
 #pragma unroll
@@ -87,10 +91,10 @@ __device__ __forceinline__ bool decode_plan(const DecodeArgs &a, int b, DecodePl
             return true;
         }
     }
-    p.u = b % U;
+    p.u = fixed_u;
     p.c = b / U;
-    p.n = uniform_i32(max(0, min(a.counts[p.u], a.max_count)));
-    p.off = uniform_i32(a.offsets[p.u]);
+    p.n = uniform_i32(max(0, min(fixed_n, a.max_count)));
+    p.off = uniform_i32(fixed_off);
     if (a.plan && p.c == 0 && threadIdx.x == 0) a.tab[p.u] = make_int2(0, 0);  // (fixed chunks)
     p.wave_rows = fixed_wave_rows(p.n, a.np);
     return (int64_t)p.c * (kDecWaves * p.wave_rows) < p.n;

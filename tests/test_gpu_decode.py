@@ -155,9 +155,12 @@ PLAN_CASES = [
     ("f32", 64, 257, 257, 1, [1600 + i % 7 for i in range(257)], 1606, "fixed"),
     # balanced plans whose chunks take two, three and eight groups of query heads
     ("f32", 64, 32, 2, 2, [6553, 1, 7000, 6000], 7000, "balanced 48"),
-    ("bf16", 64, 64, 4, 4, [19660 - 7 * i for i in range(16)], 19660, "balanced 192"),
+    ("bf16", 64, 64, 4, 4, [19660 - 700 * i for i in range(16)], 19660, "balanced 192"),
     ("bf16", 128, 96, 4, 1, [19660, 19001, 19659, 3], 19660, "balanced 96"),
-    ("bf16", 64, 64, 1, 1, [60000], 60000, "balanced 192"),
+    ("bf16", 64, 64, 1, 1, [60000], 90000, "balanced 192"),
+    # the same rows in units nearly all full: fixed chunks
+    ("bf16", 64, 64, 4, 4, [15000 - 7 * i for i in range(16)], 15000, "fixed"),
+    ("f32", 128, 64, 64, 4, [1600 - i % 5 for i in range(256)], 1600, "fixed"),
 ]
 
 
