@@ -130,24 +130,37 @@ __device__ __forceinline__ void unpack(const u32x4d &x, float (&f)[BF16 ? 8 : 4]
 //    fp32 P.V accumulators are rescaled rarely (one wave-uniform branch).
 //  * P goes through a wave-private LDS tile into the V layout (lane l: row
 //    RPI i + l / S, bytes 16 (l % S)) and P.V accumulates there.
+// fp32 rows for one or two query heads (kVector) take q.k on the vector ALUs
+// instead: the rows in the V layout, four products per lane and the S lanes of
+// a row added by butterflies.  The 32 (16) serial fp32 matrix instructions of a
+// tile cost more than that for so few heads, and without them the loads are
+// whole lines and four waves share a SIMD (the call, us, 128-wide rows and one
+// query head, matrix -> vector: 4 units of 1500 rows 19.8 -> 12.3, 32 of 2048
+// 17.1 -> 14.5, 112 of 6553 122 -> 117; two heads 20.0 -> 17.1, 17.3 -> 14.8,
+// 123 -> 119.  Four heads have the matrix form: 112 of 6553 129 against 138).
 constexpr float kDecRebase = 8.f;
+
+template <bool BF, int QG>
+constexpr bool kVector = !BF && QG <= 2;
 
 // The register budget: with bf16 rows 168, so that three waves share a SIMD.
 template <bool BF, int D, int QG>
-__global__ __launch_bounds__(kDecThreads, BF ? 3 : 2) void k_decode(DecodeArgs a)
+__global__ __launch_bounds__(kDecThreads, (kVector<BF, QG> ? 4 : BF ? 3 : 2)) void k_decode(DecodeArgs a)
 {
+    constexpr bool VEC = kVector<BF, QG>;
     constexpr int RB = D * (BF ? 2 : 4);  // row bytes
     constexpr int EL = BF ? 8 : 4;        // elements per 16 bytes
-    constexpr int KS = RB / 64;           // K load instructions per tile
     constexpr int S = RB / 16;            // lanes per row in the V layout
     constexpr int RPI = kWave / S;        // V rows per load instruction
-    constexpr int NV = 16 / RPI;          // V load instructions per tile
-    constexpr int BR = 16;                // rows per tile
+    constexpr int BR = VEC ? 4 * RPI : 16;  // rows per tile
+    constexpr int NV = BR / RPI;          // V load instructions per tile
+    constexpr int KS = VEC ? NV : RB / 64;  // K load instructions per tile
+    constexpr int MS = VEC ? QG : 1;      // softmax states per lane
     constexpr int QP = QG < 4 ? 4 : QG;   // floats per row of the P tile
     typedef float f32x4d __attribute__((ext_vector_type(4)));
     __shared__ float cm[kDecWaves][QG], cl[kDecWaves][QG];
     __shared__ float cacc[kDecWaves][QG][D];
-    __shared__ __attribute__((aligned(16))) float pt[kDecWaves][BR][QP];
+    __shared__ __attribute__((aligned(16))) float pt[VEC ? 1 : kDecWaves][BR][QP];
     const int index = blockIdx.z * kGridX + blockIdx.x;
     const DecodePlace place = QG == kDecQG && a.zg > 1 ? decode_place(index, a.zg) : DecodePlace{index, 0};
     const int block = place.block, z = place.z;
@@ -158,13 +171,21 @@ __global__ __launch_bounds__(kDecThreads, BF ? 3 : 2) void k_decode(DecodeArgs a
     const int r16 = lane & 15, kg = lane >> 4, seg = lane % S, rg = lane / S;
     const int64_t off = pl.off;
     const int nq = min(QG, a.G - z * QG);
-    u32x4d qb[KS];
+    // the query heads as operand B; vector form: this lane's 16 bytes of each head
+    u32x4d qb[VEC ? QG : KS];
     {
-        const int64_t qrow = ((int64_t)un.l * a.Hq + un.h * a.G + z * QG + min(r16, nq - 1)) * a.B + un.s;
-        const char *qp = static_cast<const char *>(a.Q) + qrow * RB + 16 * kg;
+        const int64_t q0 = (int64_t)un.l * a.Hq + un.h * a.G + z * QG;
+        if constexpr (VEC) {
 #pragma unroll
-        for (int st = 0; st < KS; ++st)
-            qb[st] = r16 < nq ? *reinterpret_cast<const u32x4d *>(qp + 64 * st) : (u32x4d){0u, 0u, 0u, 0u};
+            for (int g = 0; g < QG; ++g)
+                qb[g] = *reinterpret_cast<const u32x4d *>(static_cast<const char *>(a.Q) +
+                                                          ((q0 + min(g, nq - 1)) * a.B + un.s) * RB + 16 * seg);
+        } else {
+            const char *qp = static_cast<const char *>(a.Q) + ((q0 + min(r16, nq - 1)) * a.B + un.s) * RB + 16 * kg;
+#pragma unroll
+            for (int st = 0; st < KS; ++st)
+                qb[st] = r16 < nq ? *reinterpret_cast<const u32x4d *>(qp + 64 * st) : (u32x4d){0u, 0u, 0u, 0u};
+        }
     }
     const int row0 = (pl.c * kDecWaves + wv) * pl.wave_rows;
     const int nrows = max(0, min(pl.n - row0, pl.wave_rows));
@@ -177,103 +198,149 @@ __global__ __launch_bounds__(kDecThreads, BF ? 3 : 2) void k_decode(DecodeArgs a
         const_cast<char *>(uniform_ptr(static_cast<const char *>(a.Vc) + base)), (short)0, uniform_i32(nrows * RB),
         0x00020000);
 
-    // m, ls: head r16's reference maximum and this lane's part of its sum
-    float m = -INFINITY, ls = 0.f, acc[QG][EL];
+    // m, ls: head r16's (vector form: every head's) reference maximum and this
+    // lane's part of its sum
+    float m[MS], ls[MS], acc[QG][EL];
+#pragma unroll
+    for (int g = 0; g < MS; ++g) {
+        m[g] = -INFINITY;
+        ls[g] = 0.f;
+    }
 #pragma unroll
     for (int g = 0; g < QG; ++g)
 #pragma unroll
         for (int e = 0; e < EL; ++e) acc[g][e] = 0.f;
-    float *ptw = &pt[wv][0][0];
+    float *ptw = &pt[VEC ? 0 : wv][0][0];
 
     // every load is unconditional: rows past nrows read zero.  A Kc load
     // instruction covers 64 of a row's bytes, so two instructions share each
     // 128-byte line: those loads keep the default cache policy, and the
     // second finds the line the first brought in (nontemporal Kc loads took
-    // 68 us instead of 62 on the 28-layer cache); the Vc loads cover whole
-    // lines and stream nontemporally.
+    // 68 us instead of 62 on the 28-layer cache); the Vc loads, and the vector
+    // form's Kc loads, cover whole lines and stream nontemporally.
     auto load = [&](u32x4d (&kx)[KS], u32x4d (&vx)[NV], int b0) {
 #pragma unroll
         for (int st = 0; st < KS; ++st)
             kx[st] = __builtin_bit_cast(
-                u32x4d, __builtin_amdgcn_raw_buffer_load_b128(rk, (b0 + r16) * RB + 64 * st + 16 * kg, 0, 0));
+                u32x4d, VEC ? __builtin_amdgcn_raw_buffer_load_b128(rk, (b0 + RPI * st) * RB + lane * 16, 0, 2)
+                            : __builtin_amdgcn_raw_buffer_load_b128(rk, (b0 + r16) * RB + 64 * st + 16 * kg, 0, 0));
 #pragma unroll
         for (int i = 0; i < NV; ++i)
             vx[i] = __builtin_bit_cast(u32x4d,
                                        __builtin_amdgcn_raw_buffer_load_b128(rv, (b0 + RPI * i) * RB + lane * 16, 0, 2));
     };
     auto tile = [&](const u32x4d (&kx)[KS], const u32x4d (&vx)[NV], int b0) {
-        f32x4d cc = (f32x4d){0.f, 0.f, 0.f, 0.f};
-        if constexpr (BF) {
+        if constexpr (VEC) {
+            float x[NV][QG];
 #pragma unroll
-            for (int st = 0; st < KS; ++st)
-                cc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8d, kx[st]),
-                                                            __builtin_bit_cast(bf16x8d, qb[st]), cc, 0, 0, 0);
-        } else {
-            // eight runs of D / 8 products, the runs as a tree (one chain over
-            // all of them would round more often)
-            f32x4d t[4];
+            for (int i = 0; i < NV; ++i) {
+                const bool valid = b0 + RPI * i + rg < nrows;
 #pragma unroll
-            for (int run = 0; run < 8; ++run) {
-                constexpr int RE = D / 32;  // instructions per run (4 or 2 of the step's elements)
-                f32x4d x = (f32x4d){0.f, 0.f, 0.f, 0.f};
+                for (int g = 0; g < QG; ++g) {
+                    float pd = 0.f;
 #pragma unroll
-                for (int e = 0; e < RE; ++e) {
-                    const int st = run * RE / 4, el = (run * RE + e) % 4;
-                    x = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(kx[st][el]), __uint_as_float(qb[st][el]), x, 0,
-                                                            0, 0);
+                    for (int e = 0; e < 4; ++e) pd = fmaf(__uint_as_float(qb[g][e]), __uint_as_float(kx[i][e]), pd);
+                    pd = row_sum<S>(pd);  // (every lane takes part)
+                    x[i][g] = valid ? pd * a.qscale : -INFINITY;
                 }
-                int l = 0;
-#pragma unroll
-                for (; (run >> l) & 1; ++l) x = t[l] + x;
-                t[l] = x;
             }
-            cc = t[3];
-        }
-        float x[4];
-        float mb = -INFINITY;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            x[r] = b0 + 4 * kg + r < nrows ? cc[r] * a.qscale : -INFINITY;
-            mb = fmaxf(mb, x[r]);
-        }
-        mb = across32(across16(mb, OpMax{}), OpMax{});
-        const bool move = mb > m + kDecRebase;      // (from m = -inf: with the first finite logit)
-        if (__builtin_amdgcn_ballot_w64(move)) {
-            const float nm = move ? mb : m;
-            const float sc = __builtin_amdgcn_exp2f(m - nm);  // 0 while m = -inf
-            ls *= sc;
-            m = nm;
 #pragma unroll
             for (int g = 0; g < QG; ++g) {
-                const float sg = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(sc), g));
+                float mb = x[0][g];
 #pragma unroll
-                for (int e = 0; e < EL; ++e) acc[g][e] *= sg;
+                for (int i = 1; i < NV; ++i) mb = fmaxf(mb, x[i][g]);
+                if (S <= 16) mb = across16(mb, OpMax{});
+                mb = across32(mb, OpMax{});  // (the same in every lane)
+                if (__builtin_amdgcn_ballot_w64(mb > m[g] + kDecRebase)) {
+                    const float sc = __builtin_amdgcn_exp2f(m[g] - mb);  // 0 while m = -inf
+                    ls[g] *= sc;
+                    m[g] = mb;
+#pragma unroll
+                    for (int e = 0; e < EL; ++e) acc[g][e] *= sc;
+                }
+                const float ref = m[g] == -INFINITY ? 0.f : m[g];
+#pragma unroll
+                for (int i = 0; i < NV; ++i) {
+                    const float p = __builtin_amdgcn_exp2f(x[i][g] - ref);
+                    ls[g] += p;
+#pragma unroll
+                    for (int e = 0; e < EL; ++e) acc[g][e] = fmaf(p, __uint_as_float(vx[i][e]), acc[g][e]);
+                }
             }
-        }
-        const float ref = m == -INFINITY ? 0.f : m;  // (weight 0 for logits of -inf, also before any other)
+        } else {
+            f32x4d cc = (f32x4d){0.f, 0.f, 0.f, 0.f};
+            if constexpr (BF) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const float p = __builtin_amdgcn_exp2f(x[r] - ref);
-            ls += p;
-            if (r16 < QG) ptw[(4 * kg + r) * QP + r16] = p;
-        }
-        // (a wave's own LDS accesses are ordered)
+                for (int st = 0; st < KS; ++st)
+                    cc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8d, kx[st]),
+                                                                __builtin_bit_cast(bf16x8d, qb[st]), cc, 0, 0, 0);
+            } else {
+                // eight runs of D / 8 products, the runs as a tree (one chain over
+                // all of them would round more often)
+                f32x4d t[4];
 #pragma unroll
-        for (int i = 0; i < NV; ++i) {
-            const float *prow = ptw + (RPI * i + rg) * QP;
-            float pv[QP];
+                for (int run = 0; run < 8; ++run) {
+                    constexpr int RE = D / 32;  // instructions per run (4 or 2 of the step's elements)
+                    f32x4d x = (f32x4d){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int q4 = 0; q4 < QP / 4; ++q4) {
-                const f32x4d y = *reinterpret_cast<const f32x4d *>(prow + 4 * q4);
+                    for (int e = 0; e < RE; ++e) {
+                        const int st = run * RE / 4, el = (run * RE + e) % 4;
+                        x = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(kx[st][el]), __uint_as_float(qb[st][el]), x, 0,
+                                                                0, 0);
+                    }
+                    int l = 0;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) pv[4 * q4 + e] = y[e];
+                    for (; (run >> l) & 1; ++l) x = t[l] + x;
+                    t[l] = x;
+                }
+                cc = t[3];
             }
-            float vf[EL];
-            unpack<BF>(vx[i], vf);
+            float x[4];
+            float mb = -INFINITY;
 #pragma unroll
-            for (int g = 0; g < QG; ++g)
+            for (int r = 0; r < 4; ++r) {
+                x[r] = b0 + 4 * kg + r < nrows ? cc[r] * a.qscale : -INFINITY;
+                mb = fmaxf(mb, x[r]);
+            }
+            mb = across32(across16(mb, OpMax{}), OpMax{});
+            const bool move = mb > m[0] + kDecRebase;      // (from m = -inf: with the first finite logit)
+            if (__builtin_amdgcn_ballot_w64(move)) {
+                const float nm = move ? mb : m[0];
+                const float sc = __builtin_amdgcn_exp2f(m[0] - nm);  // 0 while m = -inf
+                ls[0] *= sc;
+                m[0] = nm;
 #pragma unroll
-                for (int e = 0; e < EL; ++e) acc[g][e] = fmaf(pv[g], vf[e], acc[g][e]);
+                for (int g = 0; g < QG; ++g) {
+                    const float sg = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(sc), g));
+#pragma unroll
+                    for (int e = 0; e < EL; ++e) acc[g][e] *= sg;
+                }
+            }
+            const float ref = m[0] == -INFINITY ? 0.f : m[0];  // (weight 0 for logits of -inf, also before any other)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const float p = __builtin_amdgcn_exp2f(x[r] - ref);
+                ls[0] += p;
+                if (r16 < QG) ptw[(4 * kg + r) * QP + r16] = p;
+            }
+            // (a wave's own LDS accesses are ordered)
+#pragma unroll
+            for (int i = 0; i < NV; ++i) {
+                const float *prow = ptw + (RPI * i + rg) * QP;
+                float pv[QP];
+#pragma unroll
+                for (int q4 = 0; q4 < QP / 4; ++q4) {
+                    const f32x4d y = *reinterpret_cast<const f32x4d *>(prow + 4 * q4);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) pv[4 * q4 + e] = y[e];
+                }
+                float vf[EL];
+                unpack<BF>(vx[i], vf);
+#pragma unroll
+                for (int g = 0; g < QG; ++g)
+#pragma unroll
+                    for (int e = 0; e < EL; ++e) acc[g][e] = fmaf(pv[g], vf[e], acc[g][e]);
+            }
         }
     };
     // two register buffers: the next tile's rows load while this one is used
@@ -312,10 +379,17 @@ __global__ __launch_bounds__(kDecThreads, BF ? 3 : 2) void k_decode(DecodeArgs a
             for (int e = 0; e < EW; ++e) cacc[wv][g][seg * EL + e0 + e] = acc[g][e];
         }
     }
-    ls = across32(across16(ls, OpAdd{}), OpAdd{});
-    if (lane < QG) {
-        cm[wv][lane] = m;
-        cl[wv][lane] = ls;
+#pragma unroll
+    for (int g = 0; g < MS; ++g) {
+        if (!VEC || S <= 16) ls[g] = across16(ls[g], OpAdd{});
+        ls[g] = across32(ls[g], OpAdd{});
+    }
+    if (VEC ? lane == 0 : lane < QG) {
+#pragma unroll
+        for (int g = 0; g < MS; ++g) {
+            cm[wv][VEC ? g : lane] = m[g];
+            cl[wv][VEC ? g : lane] = ls[g];
+        }
     }
     __syncthreads();
     for (int t = threadIdx.x; t < nq * D; t += kDecThreads) {
