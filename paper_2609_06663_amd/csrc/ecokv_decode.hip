@@ -10,7 +10,6 @@
 // softmax is kept in base 2.  A block merges its waves in LDS and writes one
 // (max, sum, acc[D]) per query to the workspace; k_decode_merge combines a
 // query row's chunks.
-#include "ecokv_decode_plan.h"
 #include "ecokv_internal.h"
 
 namespace ecokv {
@@ -49,21 +48,23 @@ __device__ __forceinline__ bool decode_plan(const DecodeArgs &a, int b, DecodePl
     int fixed_n = a.counts[fixed_u], fixed_off = a.offsets[fixed_u];
     if (a.plan) {
         const int lane = threadIdx.x & 63;
-        int n[kPlanPer], off[kPlanPer];
+        // four units' counts and offsets per lane (zero past the last unit)
+        static_assert(kPlanPer == 4, "one 16-byte load");
+        const auto units4 = [&](const int32_t *p) {
+            const __amdgpu_buffer_rsrc_t r =
+                __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t *>(p), (short)0, U * 4, 0x00020000);
+            return __builtin_bit_cast(u32x4d, __builtin_amdgcn_raw_buffer_load_b128(r, lane * 16, 0, 0));
+        };
+        const u32x4d cnt = units4(a.counts), off = units4(a.offsets);
+        int n[kPlanPer];
         float sum = 0.f;
-#pragma unroll
-        for (int q = 0; q < kPlanPer; ++q) {
-            const int u = kPlanPer * lane + q;
-            n[q] = u < U ? a.counts[u] : 0;
-            off[q] = u < U ? a.offsets[u] : 0;
-        }
         asm volatile("" : "+s"(fixed_n), "+s"(fixed_off));
 #pragma unroll
         for (int q = 0; q < kPlanPer; ++q) {
-            n[q] = max(0, min(n[q], a.max_count));  // more rows than max_count: the merge writes NaN
+            n[q] = max(0, min((int)cnt[q], a.max_count));  // more rows than max_count: the merge writes NaN
             sum += (float)n[q];  // (a float: only the rows per wave come from it, alike in every wave)
         }
-        p.wave_rows = uniform_i32(plan_wave_rows(wave_sum(sum), U, a.plan, a.max_count));
+        p.wave_rows = uniform_i32(plan_wave_rows(wave_sum(sum), a.scale));
         if (p.wave_rows > 0) {
             int parts[kPlanPer], mine = 0;
 #pragma unroll
@@ -83,7 +84,7 @@ __device__ __forceinline__ bool decode_plan(const DecodeArgs &a, int b, DecodePl
                     p.u = kPlanPer * ol + q;
                     p.c = b - first;
                     p.n = __builtin_amdgcn_readlane(n[q], ol);
-                    p.off = __builtin_amdgcn_readlane(off[q], ol);
+                    p.off = __builtin_amdgcn_readlane((int)off[q], ol);
                     if (p.c == 0 && threadIdx.x == 0) a.tab[p.u] = make_int2(b, pq);
                 }
                 first += pq;
@@ -577,6 +578,7 @@ hipError_t decode_launch(DecodeArgs a, char *ws, size_t ws_bytes, bool bf16, hip
     if (ws_bytes < g.bytes) g = decode_grid(U, a.G, a.D, a.max_count, true);
     if (decode_places(g.blocks, decode_head_groups(a.G)) > INT32_MAX - kGridX) return hipErrorInvalidConfiguration;
     a.plan = g.plan;
+    if (g.plan) a.scale = plan_scale(U, g.plan, a.max_count);
     a.np = g.np;
     a.part = reinterpret_cast<float *>(ws);
     a.tab = g.plan ? reinterpret_cast<int2 *>(ws + g.bytes - sizeof(int2) * (size_t)U) : nullptr;

@@ -48,13 +48,20 @@ __host__ __device__ inline int fixed_wave_rows(int n, int np)
 // nearly all of max_count rows take fixed chunks too: those launch chunk by
 // chunk of every unit, so that the units' shorter last chunks end the call (256
 // units of 1600 fp32 rows of 128 dimensions 78 -> 65 us).
-__host__ __device__ inline int plan_wave_rows(float rows, int units, int zg, int max_count)
+struct PlanScale {
+    float one, two;  // rows per wave in one and in two rounds, per row of the call
+    float full;      // rows from which on units are nearly full
+};
+inline PlanScale plan_scale(int64_t units, int zg, int max_count)
 {
-    // rows per wave in one and in two rounds (a unit's last chunk is half empty on average)
-    const float total = rows * (float)zg / (float)kDecWaves, lost = 0.5f * (float)units;
-    const float one = total / (kOneRound - lost), two = total / (2 * kOneRound - lost);
-    if (two > 2.f * (float)kWaveRows) return 0;
-    if (two > (float)kWaveRows && rows > 0.75f * (float)units * (float)max_count) return 0;
+    const float lost = 0.5f * (float)units;  // a unit's last chunk is half empty on average
+    const float per = (float)zg / (float)kDecWaves;
+    return PlanScale{per / (kOneRound - lost), per / (2 * kOneRound - lost), 0.75f * (float)units * (float)max_count};
+}
+__host__ __device__ inline int plan_wave_rows(float rows, PlanScale p)
+{
+    const float one = rows * p.one, two = rows * p.two;
+    if (two > 2.f * (float)kWaveRows || (two > (float)kWaveRows && rows > p.full)) return 0;
     return clamp_wave_rows((int)ceilf(one <= (float)kOneRows ? one : two));
 }
 

@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include "ecokv.h"
+#include "ecokv_decode_plan.h"
 
 namespace ecokv {
 
@@ -206,6 +207,7 @@ struct DecodeArgs {
     int max_count;
     int zg;               // blocks per chunk (groups of query heads)
     int plan;             // the same of a balanced plan, 0: fixed chunks
+    PlanScale scale;      // of a balanced plan
     int np;               // fixed chunks per unit at most
     float qscale;         // log2(e) / sqrt(D)
 };

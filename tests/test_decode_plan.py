@@ -37,7 +37,7 @@ extern "C" int plan(long long units, int G, int D, int max_count, const int *cou
     if (g.bytes < part * g.blocks + (g.plan ? 2 * sizeof(int) * units : 0)) return 1;
     float rows = 0.f;
     for (long long u = 0; u < units; ++u) rows += (float)counts[u];
-    const int wr = g.plan ? plan_wave_rows(rows * rounding, (int)units, g.plan, max_count) : 0;
+    const int wr = g.plan ? plan_wave_rows(rows * rounding, plan_scale(units, g.plan, max_count)) : 0;
     out[0] = wr > 0;
     out[1] = wr;
     out[2] = 0;

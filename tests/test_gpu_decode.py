@@ -158,6 +158,9 @@ PLAN_CASES = [
     ("bf16", 64, 64, 4, 4, [19660 - 700 * i for i in range(16)], 19660, "balanced 192"),
     ("bf16", 128, 96, 4, 1, [19660, 19001, 19659, 3], 19660, "balanced 96"),
     ("bf16", 64, 64, 1, 1, [60000], 90000, "balanced 192"),
+    # units that do not fill the last lane's four
+    ("bf16", 64, 10, 5, 3, [4000 - 211 * i for i in range(15)], 4000, "balanced 48"),
+    ("f32", 64, 1, 1, 1, [40000], 40000, "balanced 48"),
     # the same rows in units nearly all full: fixed chunks
     ("bf16", 64, 64, 4, 4, [15000 - 7 * i for i in range(16)], 15000, "fixed"),
     ("f32", 128, 64, 64, 4, [1600 - i % 5 for i in range(256)], 1600, "fixed"),
@@ -176,8 +179,10 @@ def test_decode_plans(dtype, D, Hq, Hkv, B, counts, max_count):
     c = make_cache(14, 1, Hq, Hkv, B, D, counts, dtype, kscale=1.5)
     shape = P.Shape(1, Hq, Hkv, D, 1, [0] + list(np.cumsum([2] * B)))
     Q, Kc, Vc = dev(c["Q"], dtype), dev(c["Kc"], dtype), dev(c["Vc"], dtype)
-    n = torch.from_numpy(c["counts"].reshape(-1)).cuda()
-    off = torch.from_numpy(c["offsets"].reshape(-1)).cuda()
+    # (what follows the counts and offsets in memory is not read as theirs)
+    n, off = (torch.full((len(counts) + 8,), 9999, dtype=torch.int32, device="cuda")[:len(counts)] for _ in range(2))
+    n.copy_(torch.from_numpy(c["counts"].reshape(-1)))
+    off.copy_(torch.from_numpy(c["offsets"].reshape(-1)))
     full = P.ecokv_decode_workspace_size(shape, max_count)
     least = 4 * Hq * B * ((max_count + 767) // 768) * (D + 2)
     assert full >= least
