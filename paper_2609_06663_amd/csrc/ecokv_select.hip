@@ -254,6 +254,11 @@ __device__ __forceinline__ void pick_digit(uint32_t *h, int rem, uint32_t *slot)
 //    few in a hundred -- in its own part of the stage, and the later digits, 8
 //    bits each, count the lists only, into one histogram (h1) that the
 //    scanning wave reads and clears: two barriers per digit and no fold.
+// With at most kSmallKPT keys a thread (groups of up to 4096 keys) neither pays:
+// digits of 8 bits throughout, counted from the registers into one histogram;
+// the first nk keys of a thread count (the places past the last key, all
+// equal, would be added to one counter one by one).  (us, 4 groups, before the
+// 11-bit digit / with it / now: 500 keys 8.6 / 9.7 / 5.1, 2500 8.7 / 8.8 / 5.5.)
 // Returns the threshold key and how many keys equal to it are taken.  With
 // CLASS, kTakeAll in the place of that number when every key at or above
 // the returned threshold is taken: the digits stop at a bin that is taken
@@ -266,6 +271,7 @@ __device__ __forceinline__ void pick_digit(uint32_t *h, int rem, uint32_t *slot)
 // 65528, 2040 kept, 15.1 and 17.2 -> 12.6 and 13.6; MAD quantiles of 48 units
 // of up to 29997 35.1 -> 25.1.)
 constexpr int kTakeAll = 0x7fffffff;
+constexpr int kSmallKPT = 4;
 constexpr int kH1Bits = 11;
 constexpr int kH1Bins = 1 << kH1Bits;
 constexpr int kH1Stride = kH1Bins + 2;
@@ -274,12 +280,13 @@ static_assert(kH1Bins == 2 * kSelThreads, "two bins per thread");
 template <int KPT, bool CLASS>
 __device__ __forceinline__ void reg_radix_select(const uint32_t (&kk)[KPT], int k, uint32_t kmin, uint32_t kmax,
                                                  uint32_t *lds, uint32_t *h1, uint32_t *wsum, uint32_t (*bc)[3],
-                                                 uint32_t *thr_out, int *need_eq_out)
+                                                 uint32_t *thr_out, int *need_eq_out, int nk = KPT)
 {
     typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
     typedef unsigned u32x2_t __attribute__((ext_vector_type(2)));
+    constexpr bool SMALL = KPT <= kSmallKPT;  // no first digit of 11 bits, no lists
     constexpr int kCopies = KPT >= 32 ? 8 : KPT >= 16 ? 4 : 2;
-    static_assert(kCopies * kH1Stride <= KPT * kSelThreads && KPT <= 32 && kCopies * kH1Stride % 4 == 0,
+    static_assert(SMALL || (kCopies * kH1Stride <= KPT * kSelThreads && KPT <= 32 && kCopies * kH1Stride % 4 == 0),
                   "histograms and lists must fit the stage");
     const int tid = threadIdx.x, lane = tid & 63, wv = uniform_i32(tid >> 6);
     const uint32_t diff = kmin ^ kmax;
@@ -292,6 +299,29 @@ __device__ __forceinline__ void reg_radix_select(const uint32_t (&kk)[KPT], int 
     uint32_t mask = hi == 31 ? 0u : ~((2u << hi) - 1u);
     uint32_t prefix = kmin & mask;
     int rem = k;
+    if constexpr (SMALL) {
+        if (tid < 256) h1[tid] = 0u;
+        __syncthreads();
+        bool whole = false;
+        for (int par = 0; hi >= 0 && !(CLASS && whole); par ^= 1) {
+            const int lo = hi >= 7 ? hi - 7 : 0;
+            const uint32_t nb = 1u << (hi - lo + 1);
+#pragma unroll
+            for (int q = 0; q < KPT; ++q)
+                if (q < nk && (kk[q] & mask) == prefix) atomicAdd(&h1[(kk[q] >> lo) & (nb - 1u)], 1u);
+            __syncthreads();
+            if (tid < kWave) pick_digit(h1, rem, bc[par]);
+            __syncthreads();
+            prefix |= bc[par][0] << lo;
+            rem -= (int)bc[par][1];
+            whole = rem == (int)bc[par][2];
+            mask |= (nb - 1u) << lo;
+            hi = lo - 1;
+        }
+        *thr_out = prefix;
+        *need_eq_out = CLASS && whole ? kTakeAll : rem;
+        return;
+    }
     for (int b = tid; b < kCopies * kH1Stride / 4; b += kSelThreads)
         reinterpret_cast<u32x4_t *>(lds)[b] = (u32x4_t){0u, 0u, 0u, 0u};
     if (tid < 256) h1[tid] = 0u;
@@ -688,7 +718,7 @@ __global__ __launch_bounds__(kSelThreads) void k_select_reg(SelectArgs a)
     const int beff = grp.beff;
     const int64_t out_base = grp.out_base;
     int32_t *out = a.idx + out_base;
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int tid = threadIdx.x;
 
     if (beff >= T) {  // keep every token
         for (int64_t e = tid; e < (int64_t)nh * T; e += blockDim.x) out[e] = (int32_t)(e % T);
@@ -719,7 +749,7 @@ __global__ __launch_bounds__(kSelThreads) void k_select_reg(SelectArgs a)
         // thread takes its 32 consecutive keys from it.
         const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
             const_cast<float *>(uniform_ptr(g.base)), (short)0, uniform_i32(n) * 4, 0x00020000);
-        u32x4_t x[KPT / 4];
+        u32x4_t x[KPT < 4 ? 1 : KPT / 4];
 #pragma unroll
         for (int q = 0; q < KPT / 4; ++q)
             x[q] = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rs, (q * kSelThreads + tid) * 16, 0, 0));
@@ -761,6 +791,12 @@ __global__ __launch_bounds__(kSelThreads) void k_select_reg(SelectArgs a)
     } else if (nh == 1) {
         const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
             const_cast<float *>(uniform_ptr(g.base)), (short)0, uniform_i32(n) * 4, 0x00020000);
+        if constexpr (KPT == 2) {
+            typedef unsigned u32x2_t __attribute__((ext_vector_type(2)));
+            const u32x2_t x = __builtin_bit_cast(u32x2_t, __builtin_amdgcn_raw_buffer_load_b64(rs, v0 * 4, 0, 0));
+            kk[0] = score_key(__uint_as_float(x[0]));
+            kk[1] = score_key(__uint_as_float(x[1]));
+        }
 #pragma unroll
         for (int q = 0; q < KPT / 4; ++q) {
             const u32x4_t x = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rs, (v0 + 4 * q) * 4, 0, 0));
@@ -781,7 +817,8 @@ __global__ __launch_bounds__(kSelThreads) void k_select_reg(SelectArgs a)
     if (k > 0) {
         if (nh > 1 || KPT < 32) reg_extremes<KPT>(kk, v0, n, mm, &kmin, &kmax);
         // radix select of the k-th largest key
-        reg_radix_select<KPT, true>(kk, k, kmin, kmax, reinterpret_cast<uint32_t *>(stg), h1, wsum, bc, &thr, &need_eq);
+        reg_radix_select<KPT, true>(kk, k, kmin, kmax, reinterpret_cast<uint32_t *>(stg), h1, wsum, bc, &thr, &need_eq,
+                                    n - v0);
     }
     if (k > 0 && nh == 1) {
         // ordered emission of one head
@@ -1448,7 +1485,13 @@ hipError_t select_launch(SelectArgs a, char *ws, hipStream_t st)
         // short ones (28-layer stack, 112 groups of 32764 keys: 20 against 46 us;
         // one layer, 4 groups: 15.5 against 33 us).  Keys per thread by group
         // size, so that a small group's per-key work spreads over every wave
-        if (maxn <= 8 * kSelThreads)
+        if (maxn <= 2 * kSelThreads)
+            ECOKV_TIMED("select", st, hipLaunchKernelGGL(k_select_reg<2>, dim3((unsigned)groups), dim3(kSelThreads),
+                                                         0, st, a));
+        else if (maxn <= 4 * kSelThreads)
+            ECOKV_TIMED("select", st, hipLaunchKernelGGL(k_select_reg<4>, dim3((unsigned)groups), dim3(kSelThreads),
+                                                         0, st, a));
+        else if (maxn <= 8 * kSelThreads)
             ECOKV_TIMED("select", st, hipLaunchKernelGGL(k_select_reg<8>, dim3((unsigned)groups), dim3(kSelThreads),
                                                          0, st, a));
         else if (maxn <= 16 * kSelThreads)

@@ -67,3 +67,11 @@ def test_edges(kind, n, mode):
         ref = oracle.select(S.astype(np.float64), L, Hkv, cu, w, budget, oracle.LAYER_FLAT if flat else oracle.PER_HEAD)
         for got, want in zip((idx, counts, offsets), ref):
             np.testing.assert_array_equal(got.cpu().numpy(), want.reshape(-1))
+
+
+@pytest.mark.parametrize("kind", ["octave", "wide", "same", "two", "ties"])
+@pytest.mark.parametrize("n", [1023, 1024, 2047, 2048, 2049, 4095, 4096, 4097])
+@pytest.mark.parametrize("mode", ["per_head", "layer_flat"])
+def test_edges_of_small_groups(kind, n, mode):
+    # two and four keys a thread (up to 2048 and 4096 keys of a group), and just past
+    test_edges(kind, n, mode)
