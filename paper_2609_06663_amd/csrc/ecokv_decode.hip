@@ -276,25 +276,23 @@ __global__ __launch_bounds__(kDecThreads, (kVector<BF, QG> ? 4 : BF ? 3 : 2)) vo
                     cc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8d, kx[st]),
                                                                 __builtin_bit_cast(bf16x8d, qb[st]), cc, 0, 0, 0);
             } else {
-                // eight runs of D / 8 products, the runs as a tree (one chain over
-                // all of them would round more often)
-                f32x4d t[4];
+                // each instruction's four products a run of its own, the runs as a tree:
+                // as many roundings as a row's dimensions by fours on lanes added by
+                // butterflies (eight runs of D / 8: the logits of 128 dimensions 5.7e-7
+                // from float64 on average instead of 4.9e-7, 1 to 2 % less time)
+                constexpr int RUNS = D / 4, LEVELS = D == 128 ? 5 : 4;
+                f32x4d t[LEVELS + 1];
 #pragma unroll
-                for (int run = 0; run < 8; ++run) {
-                    constexpr int RE = D / 32;  // instructions per run (4 or 2 of the step's elements)
-                    f32x4d x = (f32x4d){0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                    for (int e = 0; e < RE; ++e) {
-                        const int st = run * RE / 4, el = (run * RE + e) % 4;
-                        x = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(kx[st][el]), __uint_as_float(qb[st][el]), x, 0,
-                                                                0, 0);
-                    }
+                for (int run = 0; run < RUNS; ++run) {
+                    f32x4d x = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(kx[run / 4][run % 4]),
+                                                                    __uint_as_float(qb[run / 4][run % 4]),
+                                                                    (f32x4d){0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
                     int l = 0;
 #pragma unroll
                     for (; (run >> l) & 1; ++l) x = t[l] + x;
                     t[l] = x;
                 }
-                cc = t[3];
+                cc = t[LEVELS];
             }
             float x[4];
             float mb = -INFINITY;
