@@ -67,20 +67,11 @@ __device__ __forceinline__ void unpack_chunk(u32x4 q, float (&v)[BF ? 8 : 4])
     }
 }
 
-// c += A B over one chunk of 16 rows (A) and 16 columns (B); fp32: elements
-// E0 .. E1 - 1 of each lane's four.
-template <bool BF, int E0 = 0, int E1 = 4>
+// c += A B over one chunk of 16 rows (A) and 16 columns (B).
 __device__ __forceinline__ f32x4v mfma_chunk(u32x4 x, u32x4 y, f32x4v c)
 {
-    if constexpr (BF) {
-        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, x), __builtin_bit_cast(bf16x8, y), c, 0,
-                                                      0, 0);
-    } else {
-#pragma unroll
-        for (int e = E0; e < E1; ++e)
-            c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(x[e]), __uint_as_float(y[e]), c, 0, 0, 0);
-        return c;
-    }
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, x), __builtin_bit_cast(bf16x8, y), c, 0, 0,
+                                                  0);
 }
 
 // |k|^2 over the lane's dimensions of a chunk.
@@ -150,37 +141,43 @@ __device__ __forceinline__ void logits(const u32x4 (&kx)[Geo<BF, D>::HT][Geo<BF,
                 for (int nt = 0; nt < G::HT; ++nt) {
                     // (64 dimensions are two instructions: their sums are added, not chained)
                     const f32x4v c0 = G::NCH > 2 ? acc[mt][nt] : (f32x4v){0.f, 0.f, 0.f, 0.f};
-                    const f32x4v c = KEYS_A ? mfma_chunk<BF>(kx[nt][st], q, c0) : mfma_chunk<BF>(q, kx[nt][st], c0);
+                    const f32x4v c = KEYS_A ? mfma_chunk(kx[nt][st], q, c0) : mfma_chunk(q, kx[nt][st], c0);
                     acc[mt][nt] = G::NCH > 2 || st == 0 ? c : acc[mt][nt] + c;
                 }
             }
         }
     } else {
-        // fp32 products are summed in eight runs of D / 8, the runs as a tree:
-        // one chain over all of them would round more often than a long row's
-        // logit can bear (scores 0.7e-6 from float64 instead of 0.5e-6)
+        // fp32 products are summed in 16 runs of D / 16, the runs as a tree, which
+        // rounds as often as 16 lanes' dot products added by butterflies (eight
+        // runs of D / 8: the logits of 128 dimensions 5.7e-7 from float64 instead of
+        // 5.1e-7, logits of 6; for 3 to 6 % of a score: 28 layers of 4 x 16384 x
+        // 128 with 28 window rows 437 -> 452 us, of 64 dimensions 262 -> 278)
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
             if (MT > 1) __builtin_amdgcn_sched_barrier(0);
-            f32x4v t[4][G::HT];  // sums of 1, 2, 4, 8 runs
+            f32x4v t[5][G::HT];  // sums of 1, 2, 4, 8, 16 runs
 #pragma unroll
-            for (int run = 0; run < 8; ++run) {
-                const int st = run * G::NCH / 8;
+            for (int run = 0; run < 16; ++run) {
+                constexpr int RE = D / 64;  // instructions per run (2 or 1 of the chunk's elements)
+                const int st = run * RE / 4, e0 = run * RE % 4;
                 const u32x4 q = qs[(mt * G::NCH + st) * 64 + lane];
 #pragma unroll
                 for (int nt = 0; nt < G::HT; ++nt) {
                     const u32x4 x = KEYS_A ? kx[nt][st] : q, y = KEYS_A ? q : kx[nt][st];
                     f32x4v c = (f32x4v){0.f, 0.f, 0.f, 0.f};
-                    if (G::NCH == 8) c = mfma_chunk<false>(x, y, c);
-                    else c = run % 2 ? mfma_chunk<false, 2, 4>(x, y, c) : mfma_chunk<false, 0, 2>(x, y, c);
+#pragma unroll
+                    for (int e = e0; e < e0 + RE; ++e)
+                        c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(x[e]), __uint_as_float(y[e]), c, 0, 0, 0);
                     int l = 0;
 #pragma unroll
                     for (; (run >> l) & 1; ++l) c = t[l][nt] + c;
+                    // (four runs in flight: all 16 at once would spill)
+                    if (D == 128 && run % 4 == 3) asm volatile("" : "+v"(c));
                     t[l][nt] = c;
                 }
             }
 #pragma unroll
-            for (int nt = 0; nt < G::HT; ++nt) acc[mt][nt] = t[3][nt];
+            for (int nt = 0; nt < G::HT; ++nt) acc[mt][nt] = t[4][nt];
         }
     }
 }

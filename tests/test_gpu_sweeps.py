@@ -188,3 +188,38 @@ def test_lengths_are_rounded_not_approximated(dtype, D):
     ulp = np.spacing(length.astype(np.float32)).astype(np.float64)
     off = abs(d - length[:, None]) / ulp[:, None]
     assert off.max() <= 0.501, off.max()
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("G", [7, 28, 56])
+def test_fp32_logits_round_no_oftener_than_a_tree(D, G):
+    # Keys k and -k: a window row's largest logit, the reference that the cache
+    # write hands over, is |q.k| / sqrt(D).  Its error against float64 beside that
+    # of 16 runs of D / 16 products added by a tree in numpy's float32, then the
+    # scale (base 2) and back: as large, but for the order of the dimensions
+    import numpy as np
+    import paper_2609_06663_amd as P
+    Hkv, B = 8, 64
+    f32 = lambda v: v.astype(np.float32).astype("f8")  # (a fused product and sum, rounded once)
+    rng = np.random.default_rng(G + D)
+    k = (6 * rng.standard_normal((Hkv, B, D))).astype(np.float32)
+    q = rng.standard_normal((Hkv, G, B, D)).astype(np.float32)
+    shape = P.Shape(1, Hkv * G, Hkv, D, 1, [2 * s for s in range(B + 1)])
+    K = torch.from_numpy(np.ascontiguousarray(np.stack([k, -k], 2).reshape(1, Hkv, 2 * B, D))).cuda()
+    pre = torch.full((Hkv, B, 2 * D + 2 * G), math.nan, device="cuda")
+    P.ecokv_prefill_write(K.transpose(1, 2).contiguous(), None, torch.from_numpy(q).cuda(), shape, P.Params(),
+                          torch.zeros_like(K), None, pre)
+    got = pre[..., 2 * D:2 * D + G].cpu().numpy().astype("f8").transpose(0, 2, 1).ravel()
+    p = k.astype("f8")[:, None] * q.astype("f8")
+    x = np.abs(p.sum(-1) / np.sqrt(D)).ravel()
+    t = p.reshape(-1, 16, D // 16)
+    s = f32(t[..., 0])
+    for j in range(1, D // 16):
+        s = f32(t[..., j] + s)
+    while s.shape[1] > 1:
+        s = f32(s[:, 0::2] + s[:, 1::2])
+    scale = np.float32(1 / np.sqrt(np.float32(D))) * np.float32(1.4426950408889634)
+    s = f32(f32(np.abs(s[:, 0]) * float(scale)) * float(np.float32(1 / np.float32(1.4426950408889634))))
+    rms, tree = (float(np.sqrt((e ** 2).mean())) for e in (got - x, s - x))
+    say(f"fp32 D={D} R={G}: logit error {rms:.3e}, tree {tree:.3e}")
+    assert rms <= (1 + 0.2 / np.sqrt(G)) * tree, (rms, tree)  # (512 G errors: 3 % / sqrt(G) each; four deviations)
