@@ -285,8 +285,10 @@ int ecokv_index_count_mode(const ecokv_shape *shape, int mode, const int32_t *bu
 
 /* Bytes of device workspace ecokv_select needs for this shape and mode (the
  * budgets do not change it).  Like the score workspace it must be zero-filled
- * before its first use; ecokv_select leaves it zero-filled, so one workspace
- * serves any number of calls of this or a smaller shape, one at a time. */
+ * before its first use; ecokv_select keeps the part that must be zero so, and
+ * one workspace, passed with the same workspace_bytes, serves any number of
+ * calls of this shape or smaller ones (no more selection groups, none longer),
+ * one at a time. */
 int ecokv_select_workspace_size(const ecokv_shape *shape, int mode, size_t *bytes);
 
 /* Select the kept positions (Sec. 3; AdaKV, PyramidKV and SparseMM budgets,
@@ -313,12 +315,12 @@ int ecokv_select_workspace_size(const ecokv_shape *shape, int mode, size_t *byte
  *           except in LAYER_FLAT)
  *   workspace, workspace_bytes: device scratch of at least
  *           ecokv_select_workspace_size bytes, 256-byte aligned, zero-filled
- *           before its first use (left so); not shared by calls that may
- *           overlap.  A selection group (a unit, or the heads of a (layer,
- *           sequence) in LAYER_FLAT) of more than 32768 keys is split over
- *           many blocks: its radix-select histograms and per-slice counts
- *           live there, or, for single-head groups whose budget is small,
- *           each 8192-key slice's own largest keys and their positions.
+ *           before its first use; not shared by calls that may overlap.  A
+ *           selection group (a unit, or the heads of a (layer, sequence) in
+ *           LAYER_FLAT) of more than 32768 keys is split over many blocks: its
+ *           radix-select histograms and per-slice counts live there, or, for
+ *           single-head groups whose budget is small, each 8192-key slice's
+ *           own largest keys and their positions.
  * NaN scores rank below every number; -0 ranks equal to +0.
  * ECOKV_EUNSUPPORTED: LAYER_FLAT with more than 256 KV heads, or with
  * H_kv * Ptot * 4 > 2^31 - 1 bytes of scores per layer; a sequence with

@@ -212,6 +212,7 @@ int select_workspace(const ShapeInfo &si, const ecokv_shape *shape, int mode, vo
         return fail(ECOKV_EWORKSPACE, "select workspace has %zu bytes, needs %zu", workspace_bytes, need);
     a->mb_groups = groups;
     a->mb_maxn = maxn;
+    a->ws_bytes = workspace_bytes;
     return ECOKV_OK;
 }
 

@@ -131,7 +131,7 @@ struct SelectArgs {
     int64_t per_lh;  // sum over s of min(b_s, T_s) (not ECOKV_HEAD_BUDGETS)
     int flat;
     int heads;       // ECOKV_HEAD_BUDGETS: budgets and starts from lht
-    // the caller's workspace (select_ws_layout(mb_groups, mb_maxn)), filled by select_launch
+    size_t ws_bytes;     // the caller's workspace (select_ws_layout(mb_groups, mb_maxn)), filled by select_launch
     uint4 *mb_state;     // [3][mb_groups]           selection state after each digit
     uint32_t *mb_hist;   // [mb_groups][5120]        global digit histograms
     uint32_t *mb_head;   // [mb_groups][256][2]      per-head keys above / equal to the threshold
@@ -148,9 +148,12 @@ struct SelectArgs {
     LhTab lht;
 };
 
-// Workspace of ecokv_select.
+// Workspace of ecokv_select: hist and head from its start, zero between calls,
+// and what a call leaves behind (state, cnt, cand; offsets from `total - left`
+// at the end of the workspace, so that a call of a smaller shape leaves nothing
+// where a larger one counts from zero, and the other way round).
 struct SelWsLayout {
-    size_t state, hist, head, cnt, cand, total;
+    size_t hist, head, state, cnt, cand, left, total;
 };
 // per_head: every group is a single head (ECOKV_PER_HEAD, ECOKV_HEAD_BUDGETS)
 SelWsLayout select_ws_layout(int64_t groups, int64_t maxn, bool per_head);

@@ -1029,7 +1029,7 @@ __global__ __launch_bounds__(kSelThreads) void k_sel_final(SelectArgs a)
 //               writes its taken positions in order; block 0 of the group
 //               writes the windows, counts and offsets.
 // A global histogram and the per-head counts are cleared by the launch after
-// their last reader, so the workspace ends as zero-filled as it started.
+// their last reader, so that part of the workspace ends as zero as it started.
 // When the chosen bin of a digit is taken whole, the later digits are
 // skipped and the key class under the prefix so far is the threshold class.
 // ---------------------------------------------------------------------------
@@ -1451,12 +1451,14 @@ SelWsLayout select_ws_layout(int64_t groups, int64_t maxn, bool per_head)
     const int64_t cand = per_head && maxn > 32 * kSelThreads ? (maxn + kCandSlice - 1) / kCandSlice * kCandSlice : 0;
     auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
     size_t o = 0;
-    w.state = o; o = al(o + sizeof(uint4) * 3 * groups);
     w.hist = o; o = al(o + sizeof(uint32_t) * kMbHistWords * groups);
     w.head = o; o = al(o + sizeof(uint32_t) * 2 * kMaxFlatHeads * groups);
-    w.cnt = o; o = al(o + sizeof(uint32_t) * 2 * slices * groups);
-    w.cand = o; o = al(o + (sizeof(int32_t) + sizeof(uint32_t)) * cand * groups);
-    w.total = o;
+    size_t e = 0;
+    w.state = e; e = al(e + sizeof(uint4) * 3 * groups);
+    w.cnt = e; e = al(e + sizeof(uint32_t) * 2 * slices * groups);
+    w.cand = e; e = al(e + (sizeof(int32_t) + sizeof(uint32_t)) * cand * groups);
+    w.left = e;
+    w.total = o + e;
     return w;
 }
 
@@ -1503,6 +1505,7 @@ hipError_t select_launch(SelectArgs a, char *ws, hipStream_t st)
         return hipGetLastError();
     }
     const SelWsLayout lay = select_ws_layout(a.mb_groups, a.mb_maxn, !a.flat);
+    char *const left = ws + ((a.ws_bytes & ~(size_t)255) - lay.left);
     if (!a.flat) {
         // single-head groups: two stages when every group's candidates (the
         // largest min(k, slice) keys of each slice) fit one block's registers
@@ -1522,8 +1525,8 @@ hipError_t select_launch(SelectArgs a, char *ws, hipStream_t st)
         if (ncmax <= 32 * kSelThreads) {
             a.c_slices = ns;
             const int64_t nslots = (a.mb_maxn + kCandSlice - 1) / kCandSlice * kCandSlice * a.mb_groups;
-            a.c_pos = reinterpret_cast<int32_t *>(ws + lay.cand);
-            a.c_key = reinterpret_cast<uint32_t *>(ws + lay.cand + sizeof(int32_t) * nslots);
+            a.c_pos = reinterpret_cast<int32_t *>(left + lay.cand);
+            a.c_key = reinterpret_cast<uint32_t *>(left + lay.cand + sizeof(int32_t) * nslots);
             ECOKV_TIMED("select", st, hipLaunchKernelGGL(k_sel_cand, dim3((unsigned)(groups * ns)), dim3(kSelThreads), 0,
                                                          st, a));
             if (ncmax <= 8 * kSelThreads)
@@ -1538,10 +1541,10 @@ hipError_t select_launch(SelectArgs a, char *ws, hipStream_t st)
             return hipGetLastError();
         }
     }
-    a.mb_state = reinterpret_cast<uint4 *>(ws + lay.state);
+    a.mb_state = reinterpret_cast<uint4 *>(left + lay.state);
     a.mb_hist = reinterpret_cast<uint32_t *>(ws + lay.hist);
     a.mb_head = reinterpret_cast<uint32_t *>(ws + lay.head);
-    a.mb_cnt = reinterpret_cast<uint32_t *>(ws + lay.cnt);
+    a.mb_cnt = reinterpret_cast<uint32_t *>(left + lay.cnt);
     const int kpt = mb_kpt(groups, maxn);
     a.mb_slices = (int)max((int64_t)1, (maxn + kMbThreads * kpt - 1) / (kMbThreads * kpt));
     const unsigned blocks = (unsigned)(groups * a.mb_slices);

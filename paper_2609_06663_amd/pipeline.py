@@ -33,7 +33,7 @@ class EvictionPass:
         else:
             # zero-filled: its first word is the status that ecokv_workspace_status reads
             self.workspace = torch.zeros(max(ws, 256), dtype=torch.uint8, device=device)
-        # zero-filled, as ecokv_select leaves it
+        # zero-filled before its first use
         self.sel_workspace = torch.zeros(max(E.ecokv_select_workspace_size(shape, mode), 256), dtype=torch.uint8,
                                          device=device)
         self.n_idx = E.ecokv_index_count_mode(shape, mode, self.budget)

@@ -75,3 +75,36 @@ def test_edges(kind, n, mode):
 def test_edges_of_small_groups(kind, n, mode):
     # two and four keys a thread (up to 2048 and 4096 keys of a group), and just past
     test_edges(kind, n, mode)
+
+
+def test_one_workspace_for_shapes_of_many_sizes():
+    # multi-block and two-stage selections of more and fewer groups, longer and
+    # shorter, in turn on one workspace sized for the largest
+    import paper_2609_06663_amd as P
+    rng = np.random.default_rng(77)
+    w = 4
+    for mode, shapes in ((P.PER_HEAD, [(6, 4, 41000), (1, 2, 33000), (6, 4, 40000), (2, 1, 36000), (3, 4, 41000)]),
+                         (P.LAYER_FLAT, [(30, 4, 12000), (1, 4, 9000), (30, 4, 11000), (2, 4, 12000), (7, 4, 8500)])):
+        make = lambda L, H, n: P.Shape(L, H, H, 128, w, [0, n + w])
+        ws = torch.zeros(max(P.ecokv_select_workspace_size(make(*s), mode) for s in shapes), dtype=torch.uint8,
+                         device="cuda")
+        for rnd, share in enumerate((0.6, 0.05, 0.6, 0.05)):
+            for L, H, n in shapes:
+                shape = make(L, H, n)
+                S = torch.from_numpy(rng.integers(0, 900, size=(L, H, n)).astype(np.float32)).cuda()
+                budget = [int(share * n) + w]
+                print(f"[gpu-select] mode {mode}, round {rnd}: {L} x {H} x {n}, {budget[0]} kept", file=sys.stderr, flush=True)
+                got = []
+                for work in (ws, torch.zeros_like(ws)):  # the shared one, a fresh one
+                    idx = torch.full((P.ecokv_index_count(shape, budget),), -7, dtype=torch.int32, device="cuda")
+                    counts = torch.full((L * H,), -7, dtype=torch.int32, device="cuda")
+                    offsets = torch.full_like(counts, -7)
+                    P.ecokv_select(S, shape, mode, budget, idx, counts, offsets, work)
+                    got.append((idx, counts, offsets))
+                torch.cuda.synchronize()
+                assert all(torch.equal(a, b) for a, b in zip(*got))
+                if L <= 2:
+                    ref = oracle.select(S.cpu().numpy().astype(np.float64), L, H, [0, n + w], w, budget,
+                                        oracle.LAYER_FLAT if mode == P.LAYER_FLAT else oracle.PER_HEAD)
+                    for a, b in zip(got[0], ref):
+                        np.testing.assert_array_equal(a.cpu().numpy(), b.reshape(-1))
