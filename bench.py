@@ -59,8 +59,8 @@ STAGE_KERNELS = {
     "sweep1_stream": ["k_fs1s"], "sweep1_rows": ["k_rows1"], "reduce1": ["k_reduce1"],
     "sweep2_stream": ["k_fs2s"], "sweep2_rows": ["k_rows2"], "epilogue": ["k_epi_unit"],
     "epilogue1": ["k_epi1"], "epilogue2": ["k_epi2"],
-    "select": ["k_select_reg", "k_select", "k_sel_digit", "k_sel_count", "k_sel_emit"], "compact": ["k_compact"], "vnorm": ["k_vnorm"],
-    "dquant": ["k_dquant", "k_dquant_reg"], "decode": ["k_decode"], "decode_merge": ["k_decode_merge"],
+    "select": ["k_select_reg", "k_sel_cand", "k_sel_final", "k_sel_digit", "k_sel_count", "k_sel_emit"], "compact": ["k_compact"], "vnorm": ["k_vnorm"],
+    "dquant": ["k_dquant", "k_dquant_reg"], "decode": ["k_decode"], "decode_merge": ["k_decode_merge", "k_decode_merge_few"],
     "prefill_sweep": [], "prefill_reduce": [], "prefill_copy": [],
 }
 BF16_MFMA_PEAK_TFLOPS = 2500.0  # MI355X dense bf16 matrix peak, vendor figure

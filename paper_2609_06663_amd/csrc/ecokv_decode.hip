@@ -4,12 +4,13 @@
 //
 // Split over rows (flash-decoding): every block takes a chunk of one unit's
 // rows (see DecodePlan) for query heads QG z .. QG z + QG - 1 of the unit's G;
-// each of its four waves takes a quarter of the chunk.  q.k runs on the matrix cores, 16 rows
-// per tile, P goes through LDS into the layout of the coalesced V loads, P.V
-// is fp32 FMAs, and the next tile's rows load while one is used.  The online
-// softmax is kept in base 2.  A block merges its waves in LDS and writes one
-// (max, sum, acc[D]) per query to the workspace; k_decode_merge combines a
-// query row's chunks.
+// each of its four waves takes a quarter of the chunk.  q.k runs on the matrix
+// cores, 16 rows per tile, P goes through LDS into the layout of the coalesced
+// V loads (one or two heads of fp32 rows: both on the vector ALUs, in that
+// layout), P.V is fp32 FMAs, and the next tile's rows load while one is used.
+// The online softmax is kept in base 2.  A block merges its waves in LDS and
+// writes one (max, sum, acc[D]) per query to the workspace; k_decode_merge or,
+// for few chunks, k_decode_merge_few combines a query row's chunks.
 #include "ecokv_internal.h"
 
 namespace ecokv {
@@ -35,7 +36,7 @@ static_assert(kDecWaves == kDecThreads / kWave && kPlanUnits == kPlanPer * kWave
 //    (us, fixed 768-row chunks -> now: one layer's 4 units of 6553 rows 16 ->
 //    8.2; 16 sequences with budgets shared over 4 heads 36 -> 25; 8 packed
 //    sequences 27 -> 14.5; 32 units of 2048 rows 15 -> 10.3; 4 layers of 4
-//    fp32 units of 6553 rows 54 -> 23, half of it from the matrix cores.)
+//    fp32 units of 6553 rows 54 -> 27, half of it from the matrix cores.)
 struct DecodePlan {
     int u, c, n, off, wave_rows;  // unit, chunk, the unit's rows and offset, rows per wave
 };
@@ -45,7 +46,7 @@ __device__ __forceinline__ bool decode_plan(const DecodeArgs &a, int b, DecodePl
     const int U = a.L * a.Hkv * a.B;
     // the fixed chunk's, read beside the plan's so that falling back costs no round trip
     const int fixed_u = b % U;
-    int fixed_n = a.counts[fixed_u], fixed_off = a.offsets[fixed_u];
+    int fixed_n = uniform_i32(a.counts[fixed_u]), fixed_off = uniform_i32(a.offsets[fixed_u]);
     if (a.plan) {
         const int lane = threadIdx.x & 63;
         // four units' counts and offsets per lane (zero past the last unit)
@@ -58,7 +59,6 @@ __device__ __forceinline__ bool decode_plan(const DecodeArgs &a, int b, DecodePl
         const u32x4d cnt = units4(a.counts), off = units4(a.offsets);
         int n[kPlanPer];
         float sum = 0.f;
-        asm volatile("" : "+s"(fixed_n), "+s"(fixed_off));
 #pragma unroll
         for (int q = 0; q < kPlanPer; ++q) {
             n[q] = max(0, min((int)cnt[q], a.max_count));  // more rows than max_count: the merge writes NaN
@@ -94,8 +94,8 @@ __device__ __forceinline__ bool decode_plan(const DecodeArgs &a, int b, DecodePl
     }
     p.u = fixed_u;
     p.c = b / U;
-    p.n = uniform_i32(max(0, min(fixed_n, a.max_count)));
-    p.off = uniform_i32(fixed_off);
+    p.n = max(0, min(fixed_n, a.max_count));
+    p.off = fixed_off;
     if (a.plan && p.c == 0 && threadIdx.x == 0) a.tab[p.u] = make_int2(0, 0);  // (fixed chunks)
     p.wave_rows = fixed_wave_rows(p.n, a.np);
     return (int64_t)p.c * (kDecWaves * p.wave_rows) < p.n;

@@ -17,7 +17,7 @@
 //   * everything per key (|k|^2, |k - kbar|^2, k.mu) as fp32 sums over the
 //     lane's quarter of the dimensions, added over the four lane groups;
 //   * the column sums as one fp32 accumulator per dimension and lane.
-// The 16-row tiles pad R = (H_q / H_kv) w to the next multiple of 16.
+// R = (H_q / H_kv) w is padded to 16, 32 or 64 rows.
 #include "ecokv_fast.h"
 
 namespace ecokv {
